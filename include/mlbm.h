@@ -355,7 +355,9 @@ mlbm_status mlbm_init_adjoint(const mlbm_plan *plan, const double *u0x, const do
  * and keeps the fastest for every later step and graph. ms_out (host, may be
  * NULL, room for MLBM_STEP_VARIANTS floats) receives the measured milliseconds
  * per step of each variant, *n_variants (host, may be NULL) their count. The contents of
- * g_a and g_b are advanced (start again from mlbm_init afterwards). Synchronous. FP64 plans have a single variant. */
+ * g_a and g_b are advanced (start again from mlbm_init afterwards). Synchronous. FP64 plans have a single variant.
+ * Clouds of up to 49,152 nodes that are not stepped as a batch take one kernel
+ * whatever the variant, so theirs time alike. */
 mlbm_status mlbm_autotune(mlbm_plan *plan, void *g_a, void *g_b, int32_t n_steps,
                           float *ms_out, int32_t *n_variants, hipStream_t stream);
 

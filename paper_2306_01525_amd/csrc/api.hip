@@ -219,7 +219,7 @@ mlbm_status check_singular(mlbm_plan *plan, hipStream_t s) {
 // Gather tables of the LDS-staged step and of the adjoint. Their kernels
 // record per cloud (stats + kStats * cloud): [0] the largest LDS need of a
 // step tile, [1] step tiles without tables, [2] the largest inverse halo,
-// [3] adjoint tiles without one. The tables are enqueued for every cloud
+// [3] adjoint tiles without one, [4] the largest halo of a step tile. The tables are enqueued for every cloud
 // first; finish_tables then reads all the records at once (one
 // synchronisation), or, while the stream is being captured, takes the
 // capacity bounds instead.
@@ -243,6 +243,7 @@ mlbm_status finish_tables(mlbm_plan *plan, hipStream_t s) {
                 cp.lds_bytes = cp.prm.precision != MLBM_FP64 && cp.K <= 30
                                    ? std::min(cap, kCaptureLds) : cap;
                 cp.fallback_tiles = -1;
+                cp.nh_max = cp.hcap;
             }
             if (cp.tdescT) cp.adj_ni = cp.adj_cap;
         }
@@ -256,6 +257,7 @@ mlbm_status finish_tables(mlbm_plan *plan, hipStream_t s) {
         if (cp.tdesc) {
             cp.lds_bytes = (unsigned)h[kStats * c];
             cp.fallback_tiles = h[kStats * c + 1];
+            cp.nh_max = h[kStats * c + 4];
         }
         if (cp.tdescT) cp.adj_ni = h[kStats * c + 2];
     }

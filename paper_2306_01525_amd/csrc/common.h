@@ -70,7 +70,7 @@ constexpr int kTile = 256;      // nodes per workgroup in the step kernels
 constexpr int kHaloCap = 1024;  // largest halo a tile stages (10-bit positions)
 constexpr int kStepVariants = MLBM_STEP_VARIANTS; // FP32 step tuning variants
 constexpr int kBuildLanes = 4;   // clouds of one plan built concurrently
-constexpr int kStats = 4;        // build records per cloud (tile tables)
+constexpr int kStats = 5;        // build records per cloud (tile tables)
 
 inline int poly_count(int m) { return (m + 1) * (m + 2) / 2; }
 
@@ -113,6 +113,7 @@ struct CloudPlan {
     uint32_t *nbrL = nullptr;     // [ntiles][ocap][ceil(K/3)] positions in H_t, 3 x 10 bit
     int32_t *hlist = nullptr;     // [ntiles][hcap] global index of H_t entries
     unsigned lds_bytes = 0;       // dynamic LDS of the step launch (0: no tables)
+    int nh_max = 0;               // largest |H_t| of a tile with tables
     int fallback_tiles = -1;      // tiles stepped with global gathers (-1: unknown)
     int variant = 0;              // FP32 step tuning variant (mlbm_autotune)
     // transposed streaming (adjoint): per direction k = 1..8, CSR over the
@@ -327,7 +328,8 @@ hipError_t launch_links(const uint8_t *ntype, const int32_t *perm, const double 
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 
 // ---- tile tables (tiles.hip) ----
-// stats[0] <- max LDS bytes over tiles, stats[1] <- number of fallback tiles
+// stats[0] <- max LDS bytes over tiles, stats[1] <- number of fallback tiles,
+// stats[4] <- largest |H_t| of a tile with tables
 hipError_t launch_tiles(const CloudPlan &cp, int32_t *stats, hipStream_t s);
 
 // ---- sort / scan (sort.hip) ----

@@ -22,6 +22,8 @@
 // are read once, unit-stride across the lanes of a wavefront. The populations
 // gathered through nbr are re-used by neighbouring nodes and are served from
 // L2; nodes are in Hilbert order so the gathers of a workgroup stay local.
+#include <algorithm>
+
 #include "common.h"
 
 namespace mlbm {
@@ -47,20 +49,18 @@ __device__ __forceinline__ void bounce_back(unsigned links, T (&f)[kQ]) {
 }
 
 // Moments, wall rule, BGK collision with force, and the stores of one node.
-// WALL: 0 none; 1 equilibrium wall nodes (ntype = node types); 2 bounce-back
-// (ntype = the nodes' link masks).
+// WALL: 0 none; 1 equilibrium wall nodes (node = its type); 2 bounce-back
+// (node = its link mask). (ax, ay): the node's body force.
 // Directions k0 <= k < k1 are stored (all of them by default; the two lanes
 // of a node in the split step store one part each).
 template <bool FORCE, int WALL, bool REC>
-__device__ __forceinline__ void collide_store32(int n, int p, float (&f)[kQ],
-                                                float *__restrict__ go,
-                                                const float *__restrict__ force,
-                                                const uint8_t *__restrict__ ntype, float rtau,
-                                                float rho0, float rho_w,
+__device__ __forceinline__ void collide_at32(int n, int p, float (&f)[kQ],
+                                                float *__restrict__ go, unsigned node, float ax,
+                                                float ay, float rtau, float rho0, float rho_w,
                                                 float *__restrict__ frec, int32_t *err,
                                                 const int32_t *perm, int uoff, int k0 = 0,
                                                 int k1 = kQ) {
-    if (WALL == 1 && ntype[p]) {
+    if (WALL == 1 && node) {
 #pragma unroll
         for (int k = 0; k < kQ; ++k) {
             if (k < k0 || k >= k1) continue;
@@ -70,7 +70,7 @@ __device__ __forceinline__ void collide_store32(int n, int p, float (&f)[kQ],
         }
         return;
     }
-    if (WALL == 2) bounce_back(ntype[p], f);
+    if (WALL == 2) bounce_back(node, f);
     float drho = 0.0f, jx = 0.0f, jy = 0.0f;
 #pragma unroll
     for (int k = 0; k < kQ; ++k) {
@@ -82,11 +82,6 @@ __device__ __forceinline__ void collide_store32(int n, int p, float (&f)[kQ],
     const float ux = jx / rho, uy = jy / rho;
     const float uu = ux * ux + uy * uy;
     if (k0 == 0) check_speed(err, uu, perm, p, uoff);
-    float ax = 0.0f, ay = 0.0f;
-    if (FORCE) {
-        ax = force[p];
-        ay = force[n + p];
-    }
 #pragma unroll
     for (int k = 0; k < kQ; ++k) {
         if (k < k0 || k >= k1) continue;
@@ -97,6 +92,21 @@ __device__ __forceinline__ void collide_store32(int n, int p, float (&f)[kQ],
         go[(int64_t)k * n + p] = v;
         if (REC) frec[(int64_t)k * n + p] = f[k];
     }
+}
+
+// The same with the node's mark and force read here.
+template <bool FORCE, int WALL, bool REC>
+__device__ __forceinline__ void collide_store32(int n, int p, float (&f)[kQ],
+                                                float *__restrict__ go,
+                                                const float *__restrict__ force,
+                                                const uint8_t *__restrict__ ntype, float rtau,
+                                                float rho0, float rho_w,
+                                                float *__restrict__ frec, int32_t *err,
+                                                const int32_t *perm, int uoff, int k0 = 0,
+                                                int k1 = kQ) {
+    collide_at32<FORCE, WALL, REC>(n, p, f, go, WALL ? ntype[p] : 0u, FORCE ? force[p] : 0.0f,
+                                   FORCE ? force[n + p] : 0.0f, rtau, rho0, rho_w, frec, err, perm,
+                                   uoff, k0, k1);
 }
 
 // One workgroup per tile of kTile nodes. Tiles with gather tables (tdesc
@@ -431,22 +441,23 @@ __global__ void k_set_desc(Step32Args *dst, Step32Args v) { *dst = v; }
 // FP64, plain populations
 // ------------------------------------------------------------------------
 template <bool FORCE, int WALL, bool REC>
-__device__ __forceinline__ void collide_store64(int n, int p, double (&f)[kQ],
-                                                double *__restrict__ go,
-                                                const double *__restrict__ force,
-                                                const uint8_t *__restrict__ ntype, double rtau,
+__device__ __forceinline__ void collide_at64(int n, int p, double (&f)[kQ],
+                                                double *__restrict__ go, unsigned node,
+                                                double ax, double ay, double rtau,
                                                 double rho_w, double *__restrict__ frec,
-                                                int32_t *err, const int32_t *perm, int uoff) {
-    if (WALL == 1 && ntype[p]) {
+                                                int32_t *err, const int32_t *perm, int uoff,
+                                                int k0 = 0, int k1 = kQ) {
+    if (WALL == 1 && node) {
 #pragma unroll
         for (int k = 0; k < kQ; ++k) {
+            if (k < k0 || k >= k1) continue;
             const double v = lat_w(k) * rho_w;
             go[(int64_t)k * n + p] = v;
             if (REC) frec[(int64_t)k * n + p] = v;
         }
         return;
     }
-    if (WALL == 2) bounce_back(ntype[p], f);
+    if (WALL == 2) bounce_back(node, f);
     double rho = 0.0, jx = 0.0, jy = 0.0;
 #pragma unroll
     for (int k = 0; k < kQ; ++k) {
@@ -456,14 +467,10 @@ __device__ __forceinline__ void collide_store64(int n, int p, double (&f)[kQ],
     }
     const double ux = jx / rho, uy = jy / rho;
     const double uu = ux * ux + uy * uy;
-    check_speed(err, uu, perm, p, uoff);
-    double ax = 0.0, ay = 0.0;
-    if (FORCE) {
-        ax = force[p];
-        ay = force[n + p];
-    }
+    if (k0 == 0) check_speed(err, uu, perm, p, uoff);
 #pragma unroll
     for (int k = 0; k < kQ; ++k) {
+        if (k < k0 || k >= k1) continue;
         const double eu = lat_ex(k) * ux + lat_ey(k) * uy;
         const double feq = lat_w(k) * rho * (1.0 + 3.0 * eu + 4.5 * eu * eu - 1.5 * uu);
         double v = f[k] - (f[k] - feq) * rtau;
@@ -471,6 +478,17 @@ __device__ __forceinline__ void collide_store64(int n, int p, double (&f)[kQ],
         go[(int64_t)k * n + p] = v;
         if (REC) frec[(int64_t)k * n + p] = f[k];
     }
+}
+
+template <bool FORCE, int WALL, bool REC>
+__device__ __forceinline__ void collide_store64(int n, int p, double (&f)[kQ],
+                                                double *__restrict__ go,
+                                                const double *__restrict__ force,
+                                                const uint8_t *__restrict__ ntype, double rtau,
+                                                double rho_w, double *__restrict__ frec,
+                                                int32_t *err, const int32_t *perm, int uoff) {
+    collide_at64<FORCE, WALL, REC>(n, p, f, go, WALL ? ntype[p] : 0u, FORCE ? force[p] : 0.0,
+                                   FORCE ? force[n + p] : 0.0, rtau, rho_w, frec, err, perm, uoff);
 }
 
 // Same structure as the FP32 step, with the same tile tables: a tile stages
@@ -578,6 +596,224 @@ __global__ __launch_bounds__(kTile) void k_step64(
     for (int d = 0; d < 8; ++d) f[d + 1] = acc[d];
     collide_store64<FORCE, WALL, REC>(n, p, f, go, force, ntype, rtau, rho_w, frec, err, perm,
                                       uoff);
+}
+
+// ------------------------------------------------------------------------
+// Small clouds, both precisions
+// ------------------------------------------------------------------------
+
+// Arguments of the small-cloud step.
+template <class T> struct WideArgs {
+    int n, K, ocap, hcap;
+    const T *W;
+    const int32_t *nbr, *owner;
+    const T *force;
+    const uint8_t *ntype;
+    T rtau, rho0, rho_w;
+    T *frec;
+    const int32_t *tdesc;
+    const uint16_t *ownerL;
+    const uint32_t *nbrL;
+    const int32_t *hlist;
+    int32_t *err;
+    const int32_t *perm;
+    int uoff;
+    int nhcap;   // halo nodes that the launch's LDS holds
+};
+
+// A value at a byte offset from a uniform base: a scalar address and a 32-bit
+// lane offset, without 64-bit vector arithmetic.
+template <class V>
+__device__ __forceinline__ V load_at(const void *base, uint32_t off) {
+    return *reinterpret_cast<const V *>(static_cast<const char *>(base) + off);
+}
+
+__device__ __forceinline__ float wide_fma(float w, float x, float acc) {
+    return __builtin_fmaf(w, x, acc);
+}
+__device__ __forceinline__ double wide_fma(double w, double x, double acc) {
+    return __builtin_fma(w, x, acc);
+}
+
+template <bool FORCE, int WALL, bool REC>
+__device__ __forceinline__ void wide_finish(const WideArgs<float> &a, int p, float (&f)[kQ],
+                                            float *go, unsigned node, float ax, float ay,
+                                            int k0, int k1) {
+    collide_at32<FORCE, WALL, REC>(a.n, p, f, go, node, ax, ay, a.rtau, a.rho0, a.rho_w, a.frec,
+                                   a.err, a.perm, a.uoff, k0, k1);
+}
+template <bool FORCE, int WALL, bool REC>
+__device__ __forceinline__ void wide_finish(const WideArgs<double> &a, int p, double (&f)[kQ],
+                                            double *go, unsigned node, double ax, double ay,
+                                            int k0, int k1) {
+    collide_at64<FORCE, WALL, REC>(a.n, p, f, go, node, ax, ay, a.rtau, a.rho_w, a.frec, a.err,
+                                   a.perm, a.uoff, k0, k1);
+}
+
+// The step for clouds that leave the chip mostly idle (wide_dirs). There the
+// tile kernels spend their time waiting: one workgroup per 256 nodes leaves
+// most CUs empty, and each of its lanes goes through its weights in turn, a
+// wait for memory and for LDS per slot. Here 32 D nodes make a workgroup and
+// a lane takes D directions of one node, so the same work is spread over
+// eight (D = 1) or four times the CUs; a lane asks for the weights of its
+// first 36 slots and for its tables before it waits for anything, so that
+// their round trips run under the halo's (tables, then populations); and the
+// slots are taken six at a time without branches. Every workgroup stages the
+// halo of its whole tile. Sums and collision are in the tile kernels' order,
+// so the states are bitwise the same. 6,400 nodes, K 25: FP64 32.4 -> 6.1 us
+// a step, FP32 8.3 -> 5.4; 1,600 nodes, K 12: FP32 5.6 -> 4.7, FP64 8.8 -> 4.8.
+// Of those, 2.7 us go by for a launch and one trip to memory, two more for the
+// halo's.
+template <class T, int MODE, bool FORCE, int WALL, bool REC, int D>
+__global__ __launch_bounds__(256) void k_step_wide(WideArgs<T> a, const T *__restrict__ g,
+                                                   T *__restrict__ go, int64_t nblocks) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    typedef T TD __attribute__((ext_vector_type(D)));
+    constexpr int NN = 32 * D;          // nodes of the workgroup
+    constexpr int PER = kTile / NN;     // workgroups per tile
+    constexpr int CH = 6, NC = 6;       // weight slots per chunk, chunks held
+    constexpr int U = kHaloCap / 256;
+    // FP32 rows of weights are two float4 a slot, FP64 rows four double2
+    constexpr int RPS = sizeof(T) == 4 ? 2 : 4, EPR = 8 / RPS, LPR = EPR / D;
+    const int64_t b = xcd_tile(nblocks);
+    if (b >= nblocks) return;
+    const int n = a.n, K = a.K, Kw = (K + 2) / 3;
+    const int64_t tile = b / PER;
+    const int first = (int)(b - tile * PER) * NN;   // first node of the workgroup in its tile
+    if (tile * kTile + first >= n) return;          // uniform
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // LPR lanes share a node's row of EPR weights; a wavefront holds 64 / LPR
+    // nodes of one row, and the rows follow one another over the wavefronts
+    constexpr int WPR = NN * LPR / 64;              // wavefronts per row
+    const int row = wv / WPR;
+    const int nd = (wv % WPR) * (64 / LPR) + lane / LPR;    // node within the workgroup
+    const int d0 = row * EPR + (lane % LPR) * D;            // first of this lane's directions, from 0
+    const int pt = (int)(tile * kTile) + first + nd;
+    const int p = min(pt, n - 1);                   // a lane past the last node repeats it
+    const T *wbase = a.W + (int64_t)row * n * EPR;
+    const uint32_t woff = (uint32_t)(p * EPR + (lane % LPR) * D) * sizeof(T);
+    auto weights = [&](int j) { return load_at<TD>(wbase + (int64_t)j * 8 * n, woff); };
+    int q[U] = {};
+    if (a.tdesc) {   // (every tile has room for kHaloCap entries: no wait for its count)
+        const int32_t *hl = a.hlist + tile * (int64_t)a.hcap;
+#pragma unroll
+        for (int u = 0; u < U; ++u) q[u] = load_at<int32_t>(hl, (uint32_t)(tid + u * 256) * 4);
+    }
+    const int nh0 = a.tdesc ? a.tdesc[2 * tile + 1] : 0;
+    const int nh = nh0 <= a.nhcap ? nh0 : 0;
+    T acc[D];
+#pragma unroll
+    for (int i = 0; i < D; ++i) acc[i] = 0;
+    // the values of the node this lane finishes, asked for with the tables
+    const int fn = tid & (NN - 1), part = tid / NN;   // 256 / NN lanes finish a node
+    const int fp = (int)(tile * kTile) + first + fn;
+    const int fq = min(fp, n - 1);
+    const T f0 = g[fq];
+    const unsigned node = WALL ? a.ntype[fq] : 0u;
+    const T ax = FORCE ? a.force[fq] : (T)0, ay = FORCE ? a.force[n + fq] : (T)0;
+    T *gl = reinterpret_cast<T *>(smem);                // [8][nh]
+    if (nh > 0) {
+        int ol[D];
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+            ol[i] = MODE == MLBM_STENCIL_OWN ? p - (int)(tile * kTile)
+                                             : (int)a.ownerL[(int64_t)(d0 + i) * n + p];
+        // Chunks of six slots, without branches inside a chunk, so that its
+        // loads and LDS reads are in flight together. Slots from K on repeat
+        // the weights of slot K - 1 and read the zero cell behind the halo
+        // (adding a zero to a sum that starts at +0 changes nothing).
+        TD w[NC][CH];
+        uint32_t wd[NC][2][D];
+        const uint32_t *nl = a.nbrL + tile * (int64_t)a.ocap * Kw;
+        auto load = [&](int c) {
+#pragma unroll
+            for (int j = 0; j < CH; ++j) w[c % NC][j] = weights(min(c * CH + j, K - 1));
+        };
+        auto words = [&](int c) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < D; ++i)
+                    wd[c % NC][h][i] =
+                        MODE == MLBM_STENCIL_OWN && i
+                            ? wd[c % NC][h][0]
+                            : load_at<uint32_t>(nl + min(2 * c + h, Kw - 1), (uint32_t)(ol[i] * Kw) * 4);
+        };
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            if (c * CH < K) load(c);
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+            if (c * CH < K) words(c);
+        T v[U][8];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const bool in = tid + u * 256 < nh;
+            if (in && (unsigned)q[u] >= (unsigned)n) {   // a bad table must not fault
+                q[u] = 0;
+                report_index(a.err);
+            }
+            if (in) {
+#pragma unroll
+                for (int d = 0; d < 8; ++d)
+                    v[u][d] = load_at<T>(g + (int64_t)(d + 1) * n, (uint32_t)q[u] * sizeof(T));
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (tid + u * 256 < nh) {
+#pragma unroll
+                for (int d = 0; d < 8; ++d) gl[d * nh + tid + u * 256] = v[u][d];
+            }
+        if (tid == 0) gl[8 * nh] = 0;
+        __syncthreads();
+        const T *glp = gl + d0 * nh;
+        const int zero = (8 - d0) * nh;
+#pragma unroll
+        for (int c = 0; c < kMaxK / CH; ++c) {
+            if (c * CH < K) {
+                T x[CH][D];
+#pragma unroll
+                for (int j = 0; j < CH; ++j)
+#pragma unroll
+                    for (int i = 0; i < D; ++i) {
+                        const int at = (int)((wd[c % NC][j / 3][i] >> (10 * (j % 3))) & 1023u);
+                        x[j][i] = glp[c * CH + j < K ? i * nh + at : zero];
+                    }
+#pragma unroll
+                for (int j = 0; j < CH; ++j)
+#pragma unroll
+                    for (int i = 0; i < D; ++i) acc[i] = wide_fma(w[c % NC][j][i], x[j][i], acc[i]);
+                if (c + NC < kMaxK / CH && (c + NC) * CH < K) {
+                    load(c + NC);
+                    words(c + NC);
+                }
+            }
+        }
+        __syncthreads();   // the halo is read by everyone: its space takes the sums
+    } else {
+        int s[D];
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+            s[i] = MODE == MLBM_STENCIL_OWN ? p : a.owner[(int64_t)(d0 + i) * n + p];
+        for (int j = 0; j < K; ++j) {
+            const TD wt = weights(j);
+#pragma unroll
+            for (int i = 0; i < D; ++i)
+                acc[i] = wide_fma(wt[i], g[(int64_t)(d0 + i + 1) * n + a.nbr[(int64_t)j * n + s[i]]],
+                                  acc[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < D; ++i) gl[(d0 + i) * NN + nd] = acc[i];
+    __syncthreads();
+    if (fp >= n) return;
+    T f[kQ];
+    f[0] = f0;
+#pragma unroll
+    for (int d = 0; d < 8; ++d) f[d + 1] = gl[d * NN + fn];
+    wide_finish<FORCE, WALL, REC>(a, fp, f, go, node, ax, ay, part ? part * D + 1 : 0, part * D + D + 1);
 }
 
 // ------------------------------------------------------------------------
@@ -878,11 +1114,81 @@ void launch32_tuned(const CloudPlan &cp, const void *gin, void *gout, void *frec
     }
 }
 
+template <class T> WideArgs<T> wide_args(const CloudPlan &cp, void *frec) {
+    WideArgs<T> a{};
+    a.n = cp.n;
+    a.K = cp.K;
+    a.ocap = cp.ocap;
+    a.hcap = cp.hcap;
+    if constexpr (sizeof(T) == 8) {
+        a.W = cp.W64;
+        a.force = cp.force64;
+    } else {
+        a.W = cp.W32;
+        a.force = cp.force32;
+    }
+    a.nbr = cp.nbr;
+    a.owner = cp.owner;
+    a.ntype = cp.prm.wall_kind == 2 ? cp.links : cp.ntype;
+    a.rtau = (T)(1.0 / cp.prm.tau);
+    a.rho0 = (T)cp.prm.rho0;
+    a.rho_w = (T)cp.prm.rho_wall;
+    a.frec = (T *)frec;
+    a.tdesc = cp.lds_bytes ? cp.tdesc : nullptr;
+    a.ownerL = cp.ownerL;
+    a.nbrL = cp.nbrL;
+    a.hlist = cp.hlist;
+    a.err = cp.err;
+    a.perm = cp.perm;
+    a.uoff = (int)cp.off;
+    // (64 KiB of LDS at most: a tile past that gathers from global memory)
+    a.nhcap = std::min(cp.nh_max, (int)(65536 / sizeof(T) - 2) / 8);
+    return a;
+}
+
+template <class T, int MODE, bool FORCE, int WALL, bool REC>
+void launch_wide(const CloudPlan &cp, int dirs, const void *gin, void *gout, void *frec,
+                 hipStream_t s) {
+    const int nodes = 32 * dirs;   // of a workgroup
+    const int64_t nb = ((int64_t)cp.n + nodes - 1) / nodes;
+    const WideArgs<T> a = wide_args<T>(cp, frec);
+    // the halo's populations and a zero, then the sums of the workgroup's nodes in their place
+    const unsigned lds = (unsigned)(8 * std::max(a.nhcap, nodes) + 2) * sizeof(T);
+    auto kernel = dirs == 1 ? k_step_wide<T, MODE, FORCE, WALL, REC, 1>
+                            : k_step_wide<T, MODE, FORCE, WALL, REC, 2>;
+    hipLaunchKernelGGL(kernel, dim3(xcd_grid(nb)), dim3(256), lds, s, a, (const T *)gin, (T *)gout,
+                       nb);
+}
+
+// Directions a lane takes in the small-cloud step, 0 for the tile kernels.
+// One (32 nodes a workgroup) as long as that gives every CU at most one
+// workgroup; two (64 nodes) until the halos that each workgroup stages for
+// itself cost more than the tile kernels' unfilled chip. us per step at K 30 on
+// 8,100 / 12,100 / 44,100 / 57,600 / 102,400 / 144,400 nodes (K 15 at 102,400):
+//   FP32 tile kernel 8.9 / 8.9 / 16.1 / 16.8 / 12.5 / 25.7
+//   FP32 one         5.5 / 6.4 / 13.1 / 16.2 / 17.8 / 32.4
+//   FP32 two         6.8 / 6.9 / 13.1 / 16.3 / 16.8 / 31.3
+//   FP64 tile kernel 37.6 / 38.3 / 40.8 / 41.9 / 29.4 / 58.3
+//   FP64 one         6.2 / 8.2 / 20.8 / 25.1 / 27.2 / 69.6
+//   FP64 two         7.1 / 7.5 / 20.1 / 24.2 / 25.8 / 61.9
+// At K 12 to 15 FP32 breaks even near 50,000 nodes and FP64 near 110,000.
+inline int wide_dirs(int n, int precision) {
+    if (n <= 8192) return 1;
+    return n <= (precision == MLBM_FP64 ? 102400 : 49152) ? 2 : 0;
+}
+
 template <int MODE, bool FORCE, int WALL, bool REC>
 hipError_t step_variant(const CloudPlan &cp, int precision, const void *gin, void *gout,
                         void *frec, hipStream_t s) {
     const int n = cp.n;
     const int64_t nblocks = (n + kTile - 1) / kTile;
+    if (const int dirs = wide_dirs(n, precision)) {
+        if (precision == MLBM_FP64)
+            launch_wide<double, MODE, FORCE, WALL, REC>(cp, dirs, gin, gout, frec, s);
+        else
+            launch_wide<float, MODE, FORCE, WALL, REC>(cp, dirs, gin, gout, frec, s);
+        return hipGetLastError();
+    }
     if (precision == MLBM_FP64) {
         hipLaunchKernelGGL((k_step64<MODE, FORCE, WALL, REC>), dim3(xcd_grid(nblocks)),
                            dim3(kTile), cp.lds_bytes, s, n, cp.K, nblocks, (const double *)gin,

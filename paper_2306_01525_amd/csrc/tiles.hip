@@ -202,6 +202,7 @@ __global__ __launch_bounds__(1024) void k_tiles(int n, int K, int mode,
             // LDS bytes of this tile in the step kernel: 8 directions x nh
             // populations (float) + no x ceil(K/3) index words
             atomicMax(&stats[0], 8 * nh * 4 + no * ((K + 2) / 3) * 4);
+            atomicMax(&stats[4], nh);
         } else {
             atomicAdd(&stats[1], 1);
         }

@@ -278,3 +278,83 @@ def test_extreme_stencil_sizes_match_oracle(label, K, m, mode, steps, tol64):
             tol = tol64 if prec == 1 else (lambda s: max(tol_fp32(s), tol64(s)))
             _compare(ref, got, tol, "%s/%s" % (label, "fp64" if prec else "fp32"))
         plan.close()
+
+
+# Sizes around the lines between the step kernels: 32 nodes a workgroup up to
+# 8,192 nodes, 64 up to 49,152 (FP32) or 102,400 (FP64), whole tiles above;
+# partial workgroups and tiles, and stencils that fill their last chunk of six
+# slots or leave one to five of it open.
+SIZE_CASES = [
+    # (nx, ny, K, degree, mode, precision)
+    (5, 5, 6, 2, 1, 0), (8, 4, 7, 2, 1, 1), (11, 3, 8, 2, 1, 0), (13, 5, 9, 2, 1, 1),
+    (51, 5, 12, 2, 1, 0), (16, 16, 20, 3, 0, 1),
+    (128, 64, 25, 3, 0, 0), (128, 64, 30, 4, 0, 1), (82, 100, 26, 2, 0, 0), (83, 99, 35, 4, 0, 1),
+    (97, 89, 47, 4, 0, 1), (256, 192, 20, 3, 0, 0), (257, 192, 20, 3, 0, 0),
+    (320, 320, 20, 2, 0, 1), (321, 320, 20, 2, 0, 1),
+]
+
+
+@pytest.mark.parametrize("nx,ny,K,m,mode,prec", SIZE_CASES,
+                         ids=["%dx%d-K%d-m%d-%d-f%d" % (a, b, k, m, o, 64 if p else 32)
+                              for a, b, k, m, o, p in SIZE_CASES])
+def test_step_kernels_at_the_edges_of_their_sizes(nx, ny, K, m, mode, prec):
+    """The first step of each kernel at the edges of its sizes, node by node
+    against the oracle's step on the plan's own stencils and weights, within
+    the bound of the step's rounding, and every variant and the recording step
+    bitwise the same."""
+    from paper_2306_01525_amd import Plan
+    c, ux, uy = tgv_case(nx, K, m, mode, seed=23, ny=ny, length_y=2 * np.pi * ny / nx, jitter=0.2)
+    dx = min(c.h, 0.4 * min(c.period))
+    tau = 0.8
+    say("n", c.n, "K", K, "precision", prec)
+    plan = Plan.build(c.x, c.y, c.period, _params(dx, K, m, mode, prec, tau))
+    nbr, own, W = (plan.export(a) for a in ("nbr", "owner", "W"))
+    f0 = oracle.equilibrium(np.ones(c.n), ux, uy)
+    r_o, u_o, v_o = oracle.moments(oracle.run(f0, nbr, own, W, tau, 1))
+    b = first_step_rounding_bounds(nbr, own, W, f0, 2.0 ** -53 if prec else EPS32)
+    r_g, u_g, v_g = _gpu_run(plan, ux, uy, [1])[1]
+    worst = max(float((np.abs(p - q) / b).max())
+                for p, q in ((r_g, r_o), (r_g * u_g, r_o * u_o), (r_g * v_g, r_o * v_o)))
+    say("  largest |moment difference| / bound %.2e" % worst)
+    assert worst <= 1.0
+    if c.n >= 1000:
+        state = None
+        for v in range(10 if prec == 0 else 1):
+            if prec == 0:
+                plan.set_variant(v)
+            g = plan.step(plan.init(ux, uy), plan.new_state(), 2)
+            rec = torch.empty((2, 9, plan.n), dtype=g.dtype, device=g.device)
+            r = plan.step_record(plan.init(ux, uy), plan.new_state(), 2, rec)
+            assert torch.equal(g, r), v
+            if state is None:
+                state = (g.clone(), rec.clone())
+            assert torch.equal(g, state[0]) and torch.equal(rec, state[1]), v
+    plan.close()
+
+
+@pytest.mark.parametrize("prec", [0, 1])
+def test_bounce_back_on_whole_tiles_matches_oracle(prec):
+    """The channel with bounce-back walls and force above the sizes of the
+    small-cloud step, 1 and 5 steps."""
+    from paper_2306_01525_amd import Plan
+    c = annulus_case(0.0075)
+    assert c.n > 102400
+    r = np.hypot(c.x, c.y)
+    s = np.where(r < 1.5, -1.0, 1.0)
+    nx, ny = s * c.x / r, s * c.y / r
+    force, tau = 1e-7, 1.0
+    ux, uy = -1e-3 * (r - 1) * (2 - r) * c.y / r, 1e-3 * (r - 1) * (2 - r) * c.x / r
+    ax, ay = oracle.azimuthal_force(c.x, c.y, force, None)
+    links = oracle.bounce_links(nx, ny, c.node_type)
+    plan = Plan.build(c.x, c.y, c.period,
+                      _params(1 / 160, 15, 2, 0, prec, tau, force_kind=1, force_mag=force,
+                              wall_kind=2), node_type=c.node_type, normals=(nx, ny))
+    nbr, own, W = (plan.export(a) for a in ("nbr", "owner", "W"))
+    got = _gpu_run(plan, ux, uy, [1, 5])
+    plan.close()
+    f = oracle.equilibrium(np.ones(c.n), ux, uy)
+    ref = {}
+    for steps in (1, 5):
+        f = oracle.run(f, nbr, own, W, tau, steps - (1 if ref else 0), ax, ay, links=links)
+        ref[steps] = oracle.moments(f)
+    _compare(ref, got, (lambda s: TOL_FP64) if prec else tol_fp32, "bounce/f%d" % (64 if prec else 32))
