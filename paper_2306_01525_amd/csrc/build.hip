@@ -6,6 +6,8 @@
 // distances and then by user index, as in the definition of the stencil.
 #include <cfloat>
 #include <climits>
+#include <type_traits>
+#include <utility>
 
 #include "common.h"
 
@@ -367,33 +369,18 @@ __device__ __forceinline__ void rhs_point(const RhsList &L, int s, int t, int &p
     }
 }
 
-// Largest 32-bit key over each group of 64/SYS lanes of a wavefront (all
-// lanes active; SYS = 1 or 2), the same in every lane of the group: DPP
-// exchanges inside each row of 16 lanes (swap neighbours, swap pairs, mirror
-// the half-rows, mirror the row) leave the row's largest key in all its lanes;
-// the rows of a group are then combined from scalar reads.
-template <int SYS>
-__device__ __forceinline__ uint32_t group_max_u32(uint32_t v, int half) {
+// Largest 32-bit key over the lanes of a wavefront (all active), the same in
+// every lane: DPP exchanges inside each row of 16 lanes (swap neighbours, swap
+// pairs, mirror the half-rows, mirror the row) leave the row's largest key in
+// all its lanes; the rows are then combined from scalar reads.
+__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
     v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, false));
     v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, false));
     v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, false));
     v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, false));
     const uint32_t r0 = __builtin_amdgcn_readlane(v, 0), r1 = __builtin_amdgcn_readlane(v, 16);
     const uint32_t r2 = __builtin_amdgcn_readlane(v, 32), r3 = __builtin_amdgcn_readlane(v, 48);
-    if constexpr (SYS == 1)
-        return max(max(r0, r1), max(r2, r3));
-    else
-        return half ? max(r2, r3) : max(r0, r1);
-}
-
-// Row stride (doubles) of the pivot-row buffers: NB + R + 1 values, padded
-// so that the two buffers of a paired wavefront start at least four LDS
-// banks apart and their same-index reads do not collide.
-constexpr int row_stride(int NB, int R, int SYS) {
-    int rs = NB + R + 1;
-    if (SYS == 2)
-        while ((2 * rs) % 64 < 8 || (2 * rs) % 64 > 56) ++rs;
-    return rs;
+    return max(max(r0, r1), max(r2, r3));
 }
 
 // The double in lane l of a wavefront (l uniform), in scalar registers.
@@ -424,26 +411,23 @@ __device__ __forceinline__ void wave_lds_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// One wavefront solves the local systems of SYS owner nodes (SYS = 2 when a
-// system has at most 32 unknowns: lanes 0-31 and 32-63 then hold one system
-// each), Phi w = phi(p) (eqs. rbf_interp_set_augmented and shape_vector) of
-// owner s for every departure point that uses the stencil of s, by
-// Gauss-Jordan elimination with partial pivoting. Lane r of a system's group
-// holds row r of the system (K RBF rows, M polynomial rows, then identity
-// rows that pad the system to NB unknowns) in registers. Rows are never
-// moved: the pivot of column k is a not-yet-used lane with the largest |a_k|,
-// compared on the upper 32 bits of its binary64 encoding (exponent and 20
-// mantissa bits, so within a factor 1 + 2^-20 of the largest, which keeps the
-// growth bound of partial pivoting; ties: lowest lane). It copies its row and
-// its reciprocal 1/a_k to its group's LDS buffer, and every other lane of the
-// group, pivot rows of earlier steps included, subtracts its multiple of that
-// row and keeps the multiplier in a_k. At the end the pivot row of step j
-// holds a_j x_j = b, so unknown j (the weight of stencil member j, j < K) is
-// one product with the kept reciprocal away, with no back substitution. The
-// right-hand sides (departure points) are taken R at a time: the first group
-// is eliminated along with the matrix, later groups by replaying the stored
-// multipliers.
-template <int NB, int R, int SYS, bool REPLAY>
+// One wavefront solves the local system of an owner node, Phi w = phi(p)
+// (eqs. rbf_interp_set_augmented and shape_vector) of owner s for every
+// departure point that uses the stencil of s, by Gauss-Jordan elimination with
+// partial pivoting. Lane r holds row r of the system (K RBF rows, M polynomial
+// rows, then identity rows that pad the system to NB unknowns) in registers.
+// Rows are never moved: the pivot of column k is a not-yet-used lane with the
+// largest |a_k|, compared on the upper 32 bits of its binary64 encoding
+// (exponent and 20 mantissa bits, so within a factor 1 + 2^-20 of the largest,
+// which keeps the growth bound of partial pivoting; ties: lowest lane). Its row
+// and its reciprocal 1/a_k are broadcast, and every other lane, pivot rows of
+// earlier steps included, subtracts its multiple of that row and keeps the
+// multiplier in a_k. At the end the pivot row of step j holds a_j x_j = b, so
+// unknown j (the weight of stencil member j, j < K) is one product with the
+// kept reciprocal away, with no back substitution. The right-hand sides
+// (departure points) are taken R at a time: the first group is eliminated
+// along with the matrix, later groups by replaying the stored multipliers.
+template <int NB, int R, bool REPLAY>
 __device__ __forceinline__ void rbf_solve(const Geo *__restrict__ geo,
                                           const double *__restrict__ xs,
                                           const double *__restrict__ ys,
@@ -451,43 +435,30 @@ __device__ __forceinline__ void rbf_solve(const Geo *__restrict__ geo,
                                           const int32_t *__restrict__ nbr, RhsList L, int n,
                                           int K, int m, double dx, double *__restrict__ W64,
                                           int32_t *__restrict__ dev_err) {
-    static_assert(SYS == 1 || (SYS == 2 && NB <= 32), "two systems need 32 lanes each");
-    constexpr int LW = 64 / SYS;                   // lanes per system
-    constexpr int KT = SYS == 2 ? 32 : kMaxK;      // table rows per system
     constexpr int MP = 15;   // monomials of degree <= 4 (table row stride, odd)
-    constexpr int RS = row_stride(NB, R, SYS);
-    __shared__ double s_row[4][SYS * RS];
     __shared__ double2 s_c[4][64];
-    __shared__ double s_P[4][SYS * KT * MP];
-    __shared__ double2 s_q[4][SYS * R];
-    __shared__ int2 s_pk[4][SYS * R];
-    const int lane = threadIdx.x & 63;
-    const int half = SYS == 2 ? lane >> 5 : 0;     // this lane's system
-    const int ll = lane & (LW - 1);                // row within it
+    __shared__ double s_P[4][kMaxK * MP];
+    __shared__ double2 s_q[4][R];
+    __shared__ int2 s_pk[4][R];
+    const int lane = threadIdx.x & 63, ll = lane;   // lane: row of the system
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // each XCD takes a contiguous range of owners: the shape vectors they
     // store land at neighbouring nodes, so the L2 of one XCD collects whole
     // lines of them (grid xcd_grid of the workgroup count)
-    const int64_t blk = xcd_tile(((int64_t)n + 4 * SYS - 1) / (4 * SYS));
-    const int64_t s0 = (blk * 4 + wv) * SYS;
-    if (s0 >= n) return;   // uniform across the wavefront
-    // a group past the last node solves its neighbour's system again and
-    // stores nothing
-    const bool live = s0 + half < n;
-    const int s = (int)(live ? s0 + half : s0);
+    const int64_t blk = xcd_tile(((int64_t)n + 3) / 4);
+    const int64_t so = blk * 4 + wv;
+    if (so >= n) return;   // uniform across the wavefront
+    const int s = (int)so;
     // (without REPLAY every owner has at most R departure points)
-    const int count = live ? (L.ptr ? L.ptr[s + 1] - L.ptr[s] : 8) : 0;
-    int cmax = __builtin_amdgcn_readlane(count, 0);
-    if constexpr (SYS == 2) cmax = max(cmax, __builtin_amdgcn_readlane(count, 32));
-    if (cmax == 0) return;
+    const int count = __builtin_amdgcn_readfirstlane(L.ptr ? L.ptr[s + 1] - L.ptr[s] : 8);
+    if (count == 0) return;
     const Geo g = *geo;
     const int M = (m + 1) * (m + 2) / 2;
     const int nn = K + M;
-    double *row = s_row[wv] + half * RS;
-    double *P = s_P[wv] + half * KT * MP;
-    const double2 *cw = s_c[wv] + half * LW;
-    double2 *qw = s_q[wv] + half * R;
-    int2 *pkw = s_pk[wv] + half * R;
+    double *P = s_P[wv];
+    const double2 *cw = s_c[wv];
+    double2 *qw = s_q[wv];
+    int2 *pkw = s_pk[wv];
 
     // stencil member coordinates relative to the centre s, scaled by the
     // stencil radius (the interpolant is invariant to this; it helps the
@@ -500,7 +471,7 @@ __device__ __forceinline__ void rbf_solve(const Geo *__restrict__ geo,
     }
     double rad = sqrt(rx * rx + ry * ry);
 #pragma unroll
-    for (int off = LW / 2; off > 0; off >>= 1) rad = fmax(rad, __shfl_xor(rad, off));
+    for (int off = 32; off > 0; off >>= 1) rad = fmax(rad, __shfl_xor(rad, off));
     if (!(rad > 0.0)) rad = 1.0;
     const double sx = rx / rad, sy = ry / rad;
     s_c[wv][lane] = make_double2(sx, sy);
@@ -552,7 +523,7 @@ __device__ __forceinline__ void rbf_solve(const Geo *__restrict__ geo,
     for (int c = 0; c < NB; ++c) rs += fabs(a[c]);
     if (ll >= NB) rs = 0.0;
 #pragma unroll
-    for (int off = LW / 2; off > 0; off >>= 1) rs = fmax(rs, __shfl_xor(rs, off));
+    for (int off = 32; off > 0; off >>= 1) rs = fmax(rs, __shfl_xor(rs, off));
     const double tiny = 1e3 * DBL_EPSILON * rs;
     bool singular = false;
     // elimination step at which this lane was the pivot (-1: padding lane)
@@ -607,154 +578,81 @@ __device__ __forceinline__ void rbf_solve(const Geo *__restrict__ geo,
 
     double b[R];
     load_rhs(0, b);
-    if constexpr (SYS == 1) {
-        // One system per wavefront: the pivot row is broadcast through scalar
-        // registers (two lane reads per value, used directly as the scalar
-        // operand of the updates) instead of LDS, which the four SIMDs of a
-        // compute unit share and which every lane would otherwise read the
-        // whole row from. Lane k keeps the pivot lane of step k for the
-        // replay of further groups.
-        // Steps from nn on pivot on the identity rows that pad the system
-        // and change nothing, and columns from nn on stay zero in every row
-        // that holds a pivot before (a zero pivot there only happens in a
-        // singular system, which is reported): both are skipped with uniform
-        // branches.
-        int plog = 0;
-#pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            if (k >= nn) continue;
-            const uint32_t key =
-                pstep > k ? ((uint32_t)(__double_as_longlong(a[k]) >> 32) & 0x7FFFFFFFu) | 1u : 0u;
-            const double rk = recip(a[k]);
-            const uint32_t km = group_max_u32<1>(key, 0);
-            const int pl = __builtin_amdgcn_readfirstlane(__builtin_ctzll(__ballot(key == km)));
-            const double pv = readlane_d(a[k], pl), pi = readlane_d(rk, pl);
-            if (!(fabs(pv) > tiny)) singular = true;
-            if (lane == pl) {
-                pstep = k;
-                pinv = pi;
-            }
-            if (lane == k) plog = pl;
-            const double l = lane != pl ? a[k] * pi : 0.0;
-            // (four lane reads ahead of their updates, so that the scalar
-            // results are not waited for one by one)
-#pragma unroll
-            for (int c = k + 1; c < NB; c += 4) {
-                if (c >= nn) continue;
-                const double r0 = readlane_d(a[c], pl);
-                const double r1 = c + 1 < NB ? readlane_d(a[c + 1], pl) : 0.0;
-                const double r2 = c + 2 < NB ? readlane_d(a[c + 2], pl) : 0.0;
-                const double r3 = c + 3 < NB ? readlane_d(a[c + 3], pl) : 0.0;
-                a[c] = __builtin_fma(-l, r0, a[c]);
-                if (c + 1 < NB) a[c + 1] = __builtin_fma(-l, r1, a[c + 1]);
-                if (c + 2 < NB) a[c + 2] = __builtin_fma(-l, r2, a[c + 2]);
-                if (c + 3 < NB) a[c + 3] = __builtin_fma(-l, r3, a[c + 3]);
-            }
-#pragma unroll
-            for (int t = 0; t < R; t += 2) {
-                const double r0 = readlane_d(b[t], pl), r1 = readlane_d(b[t + 1], pl);
-                b[t] = __builtin_fma(-l, r0, b[t]);
-                b[t + 1] = __builtin_fma(-l, r1, b[t + 1]);
-            }
-            if (lane != pl) a[k] = l;
-        }
-        store(0, b);
-        for (int c0 = R; REPLAY && c0 < cmax; c0 += R) {
-            load_rhs(c0, b);
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                if (k >= nn) continue;
-                const int pk = __builtin_amdgcn_readlane(plog, k);
-                const double l = lane != pk ? a[k] : 0.0;
-#pragma unroll
-                for (int t = 0; t < R; ++t) b[t] = __builtin_fma(-l, readlane_d(b[t], pk), b[t]);
-            }
-            store(c0, b);
-        }
-        if (singular && count > 0 && ll == 0) atomicMin(dev_err, perm[s] + 1);
-        return;
-    }
-    // elimination, carrying the first group of right-hand sides (padding
-    // steps and columns skipped as above)
+    // The pivot row is broadcast through scalar
+    // registers (two lane reads per value, used directly as the scalar
+    // operand of the updates) instead of LDS, which the four SIMDs of a
+    // compute unit share and which every lane would otherwise read the
+    // whole row from. Lane k keeps the pivot lane of step k for the
+    // replay of further groups.
+    // Steps from nn on pivot on the identity rows that pad the system
+    // and change nothing, and columns from nn on stay zero in every row
+    // that holds a pivot before (a zero pivot there only happens in a
+    // singular system, which is reported): both are skipped with uniform
+    // branches.
+    int plog = 0;
 #pragma unroll
     for (int k = 0; k < NB; ++k) {
         if (k >= nn) continue;
         const uint32_t key =
             pstep > k ? ((uint32_t)(__double_as_longlong(a[k]) >> 32) & 0x7FFFFFFFu) | 1u : 0u;
         const double rk = recip(a[k]);
-        const uint32_t km = group_max_u32<SYS>(key, half);
-        // every group has an open lane (NB - k of them), so its mask is not empty
-        const uint64_t hit = __ballot(key == km);
-        int pl;
-        if constexpr (SYS == 1) {
-            pl = __builtin_amdgcn_readfirstlane(__builtin_ctzll(hit));
-        } else {
-            const int pa = __builtin_amdgcn_readfirstlane(__builtin_ctz((uint32_t)hit));
-            const int pb = __builtin_amdgcn_readfirstlane(32 + __builtin_ctz((uint32_t)(hit >> 32)));
-            pl = half ? pb : pa;
-        }
+        const uint32_t km = wave_max_u32(key);
+        const int pl = __builtin_amdgcn_readfirstlane(__builtin_ctzll(__ballot(key == km)));
+        const double pv = readlane_d(a[k], pl), pi = readlane_d(rk, pl);
+        if (!(fabs(pv) > tiny)) singular = true;
         if (lane == pl) {
-#pragma unroll
-            for (int c = k; c < NB; ++c) row[c] = a[c];
-#pragma unroll
-            for (int t = 0; t < R; ++t) row[NB + t] = b[t];
-            row[NB + R] = rk;
             pstep = k;
-            pinv = rk;
+            pinv = pi;
         }
-        wave_lds_sync();
-        if (!(fabs(row[k]) > tiny)) singular = true;
-        const double l = lane != pl ? a[k] * row[NB + R] : 0.0;
-        // (the LDS reads are issued 16 at a time, which bounds the registers
-        // they hold; the updates are explicit fused multiply-adds, since only
-        // the distances that decide stencil ties must round like the oracle)
+        if (lane == k) plog = pl;
+        const double l = lane != pl ? a[k] * pi : 0.0;
+        // (four lane reads ahead of their updates, so that the scalar
+        // results are not waited for one by one)
 #pragma unroll
-        for (int c0 = k + 1; c0 < NB; c0 += 4) {
-            if (c0 >= nn) continue;
-#pragma unroll
-            for (int c = c0; c < c0 + 4 && c < NB; ++c) a[c] = __builtin_fma(-l, row[c], a[c]);
-            if ((c0 - k + 3) % 16 == 0) __builtin_amdgcn_sched_barrier(0);
+        for (int c = k + 1; c < NB; c += 4) {
+            if (c >= nn) continue;
+            const double r0 = readlane_d(a[c], pl);
+            const double r1 = c + 1 < NB ? readlane_d(a[c + 1], pl) : 0.0;
+            const double r2 = c + 2 < NB ? readlane_d(a[c + 2], pl) : 0.0;
+            const double r3 = c + 3 < NB ? readlane_d(a[c + 3], pl) : 0.0;
+            a[c] = __builtin_fma(-l, r0, a[c]);
+            if (c + 1 < NB) a[c + 1] = __builtin_fma(-l, r1, a[c + 1]);
+            if (c + 2 < NB) a[c + 2] = __builtin_fma(-l, r2, a[c + 2]);
+            if (c + 3 < NB) a[c + 3] = __builtin_fma(-l, r3, a[c + 3]);
         }
 #pragma unroll
-        for (int t = 0; t < R; ++t) b[t] = __builtin_fma(-l, row[NB + t], b[t]);
+        for (int t = 0; t < R; t += 2) {
+            const double r0 = readlane_d(b[t], pl), r1 = readlane_d(b[t + 1], pl);
+            b[t] = __builtin_fma(-l, r0, b[t]);
+            b[t + 1] = __builtin_fma(-l, r1, b[t + 1]);
+        }
         if (lane != pl) a[k] = l;
-        wave_lds_sync();
     }
     store(0, b);
-    // further groups: replay the stored multipliers
-    for (int c0 = R; REPLAY && c0 < cmax; c0 += R) {
+    for (int c0 = R; REPLAY && c0 < count; c0 += R) {
         load_rhs(c0, b);
 #pragma unroll
         for (int k = 0; k < NB; ++k) {
             if (k >= nn) continue;
-            if (pstep == k) {
+            const int pk = __builtin_amdgcn_readlane(plog, k);
+            const double l = lane != pk ? a[k] : 0.0;
 #pragma unroll
-                for (int t = 0; t < R; ++t) row[NB + t] = b[t];
-            }
-            wave_lds_sync();
-            if (pstep != k) {
-#pragma unroll
-                for (int t = 0; t < R; ++t) b[t] = __builtin_fma(-a[k], row[NB + t], b[t]);
-            }
-            wave_lds_sync();
+            for (int t = 0; t < R; ++t) b[t] = __builtin_fma(-l, readlane_d(b[t], pk), b[t]);
         }
         store(c0, b);
     }
-    // a system whose weights no departure point uses (count 0, or a group
-    // past the last node) reports nothing, as if it had not been solved
-    if (singular && count > 0 && ll == 0) atomicMin(dev_err, perm[s] + 1);
+    if (singular && ll == 0) atomicMin(dev_err, perm[s] + 1);
 }
 
-// Occupancy against registers: 24 and 32 unknowns fit four wavefronts per
-// SIMD, 48 three, 64 two (with the replay, nothing spills except at 48
-// without it; a small spill costs less than the latency fewer wavefronts leave
-// exposed). Up to 32 unknowns a wavefront holds two systems.
-template <int NB, int R, int WPE, int SYS, bool REPLAY>
+// Two wavefronts per SIMD with the replay, three without it, which keeps fewer
+// registers alive (a small spill costs less than the latency that fewer
+// wavefronts leave exposed).
+template <int NB, int R, int WPE, bool REPLAY>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void k_rbf(
     const Geo *__restrict__ geo, const double *__restrict__ xs, const double *__restrict__ ys,
     const int32_t *__restrict__ perm, const int32_t *__restrict__ nbr, RhsList L, int n, int K,
     int m, double dx, double *__restrict__ W64, int32_t *__restrict__ dev_err) {
-    rbf_solve<NB, R, SYS, REPLAY>(geo, xs, ys, perm, nbr, L, n, K, m, dx, W64, dev_err);
+    rbf_solve<NB, R, REPLAY>(geo, xs, ys, perm, nbr, L, n, K, m, dx, W64, dev_err);
 }
 
 // ---- the same solve with the FP64 matrix cores ------------------------------
@@ -781,7 +679,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WPE))) void
 // its right-hand-side entry times 1/d_j. Owners with more than 16 departure
 // points solve again for each further group of 16. Each lane assembles its own
 // tile entries (monomials from a per-member table in LDS).
-// The FP64 matrix-core rate of gfx950 equals its FP64 vector rate: what the
+// It serves 33 to 48 unknowns beyond the sizes of k_rbf_null, and what that
+// one leaves. The FP64 matrix-core rate of gfx950 equals its FP64 vector rate: what the
 // products save is issue slots (108 products a system at 48 unknowns against
 // about 2,700 vector FMAs). The pivot steps (reduction, lane reads) stay
 // serial and dominate what remains.
@@ -798,10 +697,13 @@ template <int CTRL> __device__ __forceinline__ double dpp_d(double v) {
 // Three wavefronts per SIMD at 48 unknowns (167 VGPRs, a 20-byte spill);
 // without the hint the compiler keeps the tiles in 460 registers and runs one.
 template <int RT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RT == 3 ? 3 : 2))) void k_rbf_mfma(
-    const Geo *__restrict__ geo, const double *__restrict__ xs, const double *__restrict__ ys,
-    const int32_t *__restrict__ perm, const int32_t *__restrict__ nbr, RhsList L, int n, int K,
-    int m, double dx, double *__restrict__ W64, int32_t *__restrict__ dev_err) {
+__device__ __forceinline__ void rbf_mfma_solve(const int s, const Geo &g,
+                                               const double *__restrict__ xs,
+                                               const double *__restrict__ ys,
+                                               const int32_t *__restrict__ perm,
+                                               const int32_t *__restrict__ nbr, RhsList L, int n,
+                                               int K, int m, double dx, double *__restrict__ W64,
+                                               int32_t *__restrict__ dev_err) {
     constexpr int NB = 16 * RT, CT = RT + 1, NC = 16 * CT;
     __shared__ double2 s_c[64];          // scaled stencil members
     __shared__ double2 s_q[16];          // scaled departure points of the group
@@ -819,13 +721,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RT == 3 ? 3 
     constexpr int PQ = NB * 15;          // the departure points' monomials follow the members'
     static_assert(PQ + 16 * 15 <= 4 * NC * 4, "the monomial tables fit in s_U");
     const int lane = threadIdx.x;
-    // owners in XCD-contiguous ranges, as in k_rbf (grid xcd_grid(n))
-    const int64_t so = xcd_tile(n);
-    if (so >= n) return;
-    const int s = (int)so;
     const int count = L.ptr ? L.ptr[s + 1] - L.ptr[s] : 8;
     if (count == 0) return;
-    const Geo g = *geo;
     const int M = (m + 1) * (m + 2) / 2;
     const int nn = K + M;
 
@@ -994,7 +891,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RT == 3 ? 3 
                             ? ((uint32_t)(__double_as_longlong(pv[j]) >> 32) & 0x7FFFFFFFu) | 1u
                             : 0u;
                     const double rk = recip(pv[j]);
-                    const uint32_t km = group_max_u32<1>(key, 0);
+                    const uint32_t km = wave_max_u32(key);
                     const int pl =
                         __builtin_amdgcn_readfirstlane(__builtin_ctzll(__ballot(key == km)));
                     const double pvv = readlane_d(pv[j], pl), pi = readlane_d(rk, pl);
@@ -1084,6 +981,486 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(RT == 3 ? 3 
         wave_lds_sync();
     }
     if (singular && lane == 0) atomicMin(dev_err, perm[s] + 1);
+}
+
+template <int RT>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_rbf_mfma(
+    const Geo *__restrict__ geo, const double *__restrict__ xs, const double *__restrict__ ys,
+    const int32_t *__restrict__ perm, const int32_t *__restrict__ nbr, RhsList L, int n, int K,
+    int m, double dx, double *__restrict__ W64, int32_t *__restrict__ dev_err) {
+    // owners in XCD-contiguous ranges, as in k_rbf (grid xcd_grid(n))
+    const int64_t s = xcd_tile(n);
+    if (s >= n) return;
+    rbf_mfma_solve<RT>((int)s, *geo, xs, ys, perm, nbr, L, n, K, m, dx, W64, dev_err);
+}
+
+// The same for the owners that k_rbf_null left: redo[0] of them, from redo[1]
+// on, in whatever order. Usually none, so the grid is small and walks the list.
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_rbf_redo(
+    const Geo *__restrict__ geo, const double *__restrict__ xs, const double *__restrict__ ys,
+    const int32_t *__restrict__ perm, const int32_t *__restrict__ nbr, RhsList L, int n, int K,
+    int m, double dx, const int32_t *__restrict__ redo, double *__restrict__ W64,
+    int32_t *__restrict__ dev_err) {
+    const int count = min(redo[0], n);
+    for (int i = blockIdx.x; i < count; i += gridDim.x)
+        rbf_mfma_solve<3>(redo[1 + i], *geo, xs, ys, perm, nbr, L, n, K, m, dx, W64, dev_err);
+}
+
+// ---- the same systems by the null space of the polynomials --------------------
+// Phi = [[R, P], [P^T, 0]] with r^3 positive definite on the null space of P^T
+// (r^3 is conditionally positive definite of order 2 and the polynomials hold
+// the linear ones), so only the M columns of P need a pivot search:
+//  1. P = L U with row pivoting (M steps over the K members); the M pivot
+//     members are "set 1", the other N2 = K - M "set 2", X = P2 P1^-1;
+//  2. S = R22 - X R12 - (R21 - X R11) X^T, symmetric positive definite, is
+//     factored without a search;
+//  3. per departure point y = p P1^-1 (two triangular solves with L and U),
+//     S w2 = phi2 - X phi1 - (R21 - X R11) y^T and w1 = y - w2 X.
+// At K 30, degree 4 that is 15 pivot searches and about 24k multiply-adds a
+// system with its eight points, against 45 and 62k for the elimination of Phi.
+//
+// Sixteen lanes take a system, four systems a wavefront. After step 1 the
+// members are dealt out again, set 1 in pivot order, so that everything that
+// follows names its lanes at compile time: the matrices are held a row per
+// lane, and every multiply-add takes its second factor from a fixed lane of
+// the sixteen as it goes (v_fmac_f64 with DPP row_newbcast, the one DPP
+// pattern that double precision has), without LDS and without a broadcast of
+// its own. Departure points are a lane each, sixteen at a time.
+// The pivot rows of step 1, which only become known there, go through LDS,
+// straight to their place in pivot order.
+//
+// Bound by issue: about 7,000 instructions a wavefront, a third of them FP64
+// multiply-adds, two wavefronts a SIMD. 262,144 nodes, K 30, degree 4, paper
+// rule: 4.46 -> 0.92 ms for the solves against the elimination of Phi on the
+// matrix cores. The shape vectors' error against a solve with refinement falls
+// too, on the lattices of the studies from 4.3e-16 - 1.7e-15 to 2.9e-16 -
+// 5.0e-16 of an interpolated field. Blocks of eight multiply-adds instead of
+// four (fewer wait states) measured the same.
+//
+// A system with a pivot near the singularity threshold is left to k_rbf_redo,
+// whose general elimination decides whether it is singular: `redo` gets its
+// owner. The line, 1e6 eps (8 K + M), is at least 1e3 times that threshold
+// (1e3 eps |Phi|, with distances of at most 2 stencil radii).
+
+// acc[i] += (NEG ? -1 : 1) src(lane L0 + i) m for i < C <= 4, the lane taken within each
+// group of sixteen. The wait states that a DPP read of a fresh result needs
+// come first, inside the block.
+#define MLBM_BC " row_mask:0xf bank_mask:0xf"
+template <int L0, int C, bool NEG>
+__device__ __forceinline__ void fmac_lanes(double *acc, double src, double m) {
+    if constexpr (C == 4) {
+        if constexpr (NEG)
+            asm("s_nop 1\n\tv_fmac_f64_dpp %0, -%4, %5 row_newbcast:%6" MLBM_BC
+                "\n\tv_fmac_f64_dpp %1, -%4, %5 row_newbcast:%7" MLBM_BC
+                "\n\tv_fmac_f64_dpp %2, -%4, %5 row_newbcast:%8" MLBM_BC
+                "\n\tv_fmac_f64_dpp %3, -%4, %5 row_newbcast:%9" MLBM_BC
+                : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3])
+                : "v"(src), "v"(m), "i"(L0), "i"(L0 + 1), "i"(L0 + 2), "i"(L0 + 3));
+        else
+            asm("s_nop 1\n\tv_fmac_f64_dpp %0, %4, %5 row_newbcast:%6" MLBM_BC
+                "\n\tv_fmac_f64_dpp %1, %4, %5 row_newbcast:%7" MLBM_BC
+                "\n\tv_fmac_f64_dpp %2, %4, %5 row_newbcast:%8" MLBM_BC
+                "\n\tv_fmac_f64_dpp %3, %4, %5 row_newbcast:%9" MLBM_BC
+                : "+&v"(acc[0]), "+&v"(acc[1]), "+&v"(acc[2]), "+&v"(acc[3])
+                : "v"(src), "v"(m), "i"(L0), "i"(L0 + 1), "i"(L0 + 2), "i"(L0 + 3));
+    } else if constexpr (C > 0) {
+        if constexpr (NEG)
+            asm("s_nop 1\n\tv_fmac_f64_dpp %0, -%1, %2 row_newbcast:%3" MLBM_BC
+                : "+&v"(acc[0]) : "v"(src), "v"(m), "i"(L0));
+        else
+            asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3" MLBM_BC
+                : "+&v"(acc[0]) : "v"(src), "v"(m), "i"(L0));
+        fmac_lanes<L0 + 1, C - 1, NEG>(acc + 1, src, m);
+    }
+}
+
+// acc[i] += (NEG ? -1 : 1) src[i / 16](lane i % 16) m for I0 <= i < I1.
+template <int I0, int I1, bool NEG>
+__device__ __forceinline__ void fmac_rows(double *acc, const double *src, double m) {
+    if constexpr (I0 < I1) {
+        constexpr int end = I1 < (I0 / 16 + 1) * 16 ? I1 : (I0 / 16 + 1) * 16;
+        constexpr int C = end - I0 < 4 ? end - I0 : 4;
+        fmac_lanes<I0 % 16, C, NEG>(acc + I0, src[I0 / 16], m);
+        fmac_rows<I0 + C, I1, NEG>(acc, src, m);
+    }
+}
+
+// acc += (NEG ? -1 : 1) sum over I0 <= i < I1 of src[i / 16](lane i % 16) m[i].
+template <int I0, int I1, bool NEG>
+__device__ __forceinline__ void fmac_dot(double &acc, const double *src, const double *m) {
+    if constexpr (I0 < I1) {
+        constexpr int end = I1 < (I0 / 16 + 1) * 16 ? I1 : (I0 / 16 + 1) * 16;
+        constexpr int C = end - I0 < 4 ? 1 : 4;
+        constexpr int L0 = I0 % 16;
+        if constexpr (C == 4 && NEG)
+            asm("s_nop 1\n\tv_fmac_f64_dpp %0, -%1, %2 row_newbcast:%6" MLBM_BC
+                "\n\tv_fmac_f64_dpp %0, -%1, %3 row_newbcast:%7" MLBM_BC
+                "\n\tv_fmac_f64_dpp %0, -%1, %4 row_newbcast:%8" MLBM_BC
+                "\n\tv_fmac_f64_dpp %0, -%1, %5 row_newbcast:%9" MLBM_BC
+                : "+&v"(acc)
+                : "v"(src[I0 / 16]), "v"(m[I0]), "v"(m[I0 + 1]), "v"(m[I0 + 2]), "v"(m[I0 + 3]),
+                  "i"(L0), "i"(L0 + 1), "i"(L0 + 2), "i"(L0 + 3));
+        else if constexpr (C == 4)
+            asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%6" MLBM_BC
+                "\n\tv_fmac_f64_dpp %0, %1, %3 row_newbcast:%7" MLBM_BC
+                "\n\tv_fmac_f64_dpp %0, %1, %4 row_newbcast:%8" MLBM_BC
+                "\n\tv_fmac_f64_dpp %0, %1, %5 row_newbcast:%9" MLBM_BC
+                : "+&v"(acc)
+                : "v"(src[I0 / 16]), "v"(m[I0]), "v"(m[I0 + 1]), "v"(m[I0 + 2]), "v"(m[I0 + 3]),
+                  "i"(L0), "i"(L0 + 1), "i"(L0 + 2), "i"(L0 + 3));
+        else
+            fmac_lanes<L0, 1, NEG>(&acc, src[I0 / 16], m[I0]);
+        fmac_dot<I0 + C, I1, NEG>(acc, src, m);
+    }
+}
+
+// acc[c] += src[c](lane L) m for C0 <= c < C1.
+template <int L, int C0, int C1>
+__device__ __forceinline__ void fmac_lane(double *acc, const double *src, double m) {
+    if constexpr (C1 - C0 >= 4) {
+        asm("s_nop 1\n\tv_fmac_f64_dpp %0, %4, %8 row_newbcast:%9" MLBM_BC
+            "\n\tv_fmac_f64_dpp %1, %5, %8 row_newbcast:%9" MLBM_BC
+            "\n\tv_fmac_f64_dpp %2, %6, %8 row_newbcast:%9" MLBM_BC
+            "\n\tv_fmac_f64_dpp %3, %7, %8 row_newbcast:%9" MLBM_BC
+            : "+&v"(acc[C0]), "+&v"(acc[C0 + 1]), "+&v"(acc[C0 + 2]), "+&v"(acc[C0 + 3])
+            : "v"(src[C0]), "v"(src[C0 + 1]), "v"(src[C0 + 2]), "v"(src[C0 + 3]), "v"(m), "i"(L));
+        fmac_lane<L, C0 + 4, C1>(acc, src, m);
+    } else if constexpr (C0 < C1) {
+        asm("s_nop 1\n\tv_fmac_f64_dpp %0, %1, %2 row_newbcast:%3" MLBM_BC
+            : "+&v"(acc[C0]) : "v"(src[C0]), "v"(m), "i"(L));
+        fmac_lane<L, C0 + 1, C1>(acc, src, m);
+    }
+}
+
+// The same on rows of their own: acc[c] += acc[c](lane L) m.
+template <int L, int C0, int C1>
+__device__ __forceinline__ void fmac_self(double *acc, double m) {
+    if constexpr (C1 - C0 >= 4) {
+        asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %4 row_newbcast:%5" MLBM_BC
+            "\n\tv_fmac_f64_dpp %1, %1, %4 row_newbcast:%5" MLBM_BC
+            "\n\tv_fmac_f64_dpp %2, %2, %4 row_newbcast:%5" MLBM_BC
+            "\n\tv_fmac_f64_dpp %3, %3, %4 row_newbcast:%5" MLBM_BC
+            : "+&v"(acc[C0]), "+&v"(acc[C0 + 1]), "+&v"(acc[C0 + 2]), "+&v"(acc[C0 + 3])
+            : "v"(m), "i"(L));
+        fmac_self<L, C0 + 4, C1>(acc, m);
+    } else if constexpr (C0 < C1) {
+        asm("s_nop 1\n\tv_fmac_f64_dpp %0, %0, %1 row_newbcast:%2" MLBM_BC
+            : "+&v"(acc[C0]) : "v"(m), "i"(L));
+        fmac_self<L, C0 + 1, C1>(acc, m);
+    }
+}
+
+// v of lane L of each group of sixteen.
+template <int L> __device__ __forceinline__ double lane_of(double v) {
+    double r;
+    asm("s_nop 1\n\tv_mov_b64_dpp %0, %1 row_newbcast:%2" MLBM_BC : "=v"(r) : "v"(v), "i"(L));
+    return r;
+}
+template <int L> __device__ __forceinline__ int lane_of(int v) {
+    return __builtin_amdgcn_update_dpp(0, v, 0x150 + L, 0xF, 0xF, true);
+}
+#undef MLBM_BC
+
+// r^3 for the offset (dx, dy): the hardware's estimate y of 1 / sqrt(d2) gives
+// g = d2 y and h = y / 2, one step with the residual 1/2 - g h doubles the
+// digits of both, and g + (d2 - g^2) h is the root to the last place or two.
+// 1e-300 keeps a zero distance off the pole.
+__device__ __forceinline__ double cube_of(double dx, double dy) {
+    const double d2 = __builtin_fma(dx, dx, __builtin_fma(dy, dy, 1e-300));
+    const double y = __builtin_amdgcn_rsq(d2);
+    double g = d2 * y, h = 0.5 * y;
+    const double e = __builtin_fma(-g, h, 0.5);
+    g = __builtin_fma(g, e, g);
+    h = __builtin_fma(h, e, h);
+    g = __builtin_fma(__builtin_fma(-g, g, d2), h, g);
+    return d2 * g;
+}
+
+// f(0), ..., f(N - 1) with the index as a compile-time constant.
+template <class F, int... I>
+__device__ __forceinline__ void each_index(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, class F> __device__ __forceinline__ void each(F &&f) {
+    each_index(static_cast<F &&>(f), std::make_integer_sequence<int, N>{});
+}
+
+// The M monomials of (x, y), in the order of eq. poly_sets.
+template <int M> __device__ __forceinline__ void monomials(double x, double y, double (&q)[M]) {
+    constexpr int D = M == 6 ? 2 : M == 10 ? 3 : 4;
+    double xp[D + 1], yp[D + 1];
+    xp[0] = yp[0] = 1.0;
+#pragma unroll
+    for (int e = 1; e <= D; ++e) {
+        xp[e] = xp[e - 1] * x;
+        yp[e] = yp[e - 1] * y;
+    }
+#pragma unroll
+    for (int d = 0, i = 0; d <= D; ++d)
+#pragma unroll
+        for (int j = 0; j <= d; ++j, ++i) q[i] = xp[d - j] * yp[j];
+}
+
+// M polynomials, at most NP members beyond them (N2 <= NP, rows past N2 are an
+// identity), K <= 32.
+template <int M, int NP>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_rbf_null(
+    const Geo *__restrict__ geo, const double *__restrict__ xs, const double *__restrict__ ys,
+    const int32_t *__restrict__ nbr, RhsList L, int n, int K, double dx,
+    double *__restrict__ W64, int32_t *__restrict__ redo) {
+    constexpr int NS = (NP + 15) / 16;      // members of set 2 per lane
+    constexpr int RS = (M + 4) / 2 * 2;     // a member's row: LU row, x, y, slot (16-byte aligned)
+    constexpr int SS = 32 * RS + 2;         // a system's rows; its neighbours use other banks
+    __shared__ __align__(16) double s_rows[4 * SS];
+    const int lane = threadIdx.x, grp = lane >> 4, ll = lane & 15;
+    // owners in XCD-contiguous ranges, as in k_rbf (grid xcd_grid of the wavefronts)
+    const int64_t s0 = xcd_tile(((int64_t)n + 3) / 4) * 4;
+    if (s0 >= n) return;
+    const bool live = s0 + grp < n;
+    const int s = (int)(live ? s0 + grp : n - 1);
+    const int count = live ? (L.ptr ? L.ptr[s + 1] - L.ptr[s] : 8) : 0;
+    const int cmax = max(max(__builtin_amdgcn_readlane(count, 0), __builtin_amdgcn_readlane(count, 16)),
+                         max(__builtin_amdgcn_readlane(count, 32), __builtin_amdgcn_readlane(count, 48)));
+    if (cmax == 0) return;
+    const Geo g = *geo;
+    const int N2 = K - M;
+    double *rows = s_rows + grp * SS;
+
+    // members ll and ll + 16, relative to the owner and scaled by the radius
+    double sx[2], sy[2], P[2][M];
+    bool used[2];
+    const double cx = xs[s], cy = ys[s];
+    double far = 0.0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int r = ll + 16 * h;
+        used[h] = r >= K;
+        sx[h] = sy[h] = 0.0;
+        if (r < K) {
+            const int q = nbr[(int64_t)r * n + s];
+            sx[h] = min_image(xs[q] - cx, g.Lx);
+            sy[h] = min_image(ys[q] - cy, g.Ly);
+        }
+        far = fmax(far, sx[h] * sx[h] + sy[h] * sy[h]);
+    }
+    far = fmax(far, dpp_d<0xB1>(far));
+    far = fmax(far, dpp_d<0x4E>(far));
+    far = fmax(far, dpp_d<0x141>(far));
+    far = fmax(far, dpp_d<0x140>(far));
+    const double irad = far > 0.0 ? recip(sqrt(far)) : 1.0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        sx[h] *= irad;
+        sy[h] *= irad;
+        monomials<M>(sx[h], sy[h], P[h]);
+    }
+    const double line = 1e6 * DBL_EPSILON * (8 * K + M);
+    bool bad = false;
+    auto store_row = [&](int at, int h) {
+        double *o = rows + at * RS;
+#pragma unroll
+        for (int c = 0; c < M; ++c) o[c] = P[h][c];
+        o[M] = sx[h];
+        o[M + 1] = sy[h];
+        reinterpret_cast<int *>(o + M + 2)[0] = ll + 16 * h;
+    };
+
+    // 1. P = L U: the pivot row goes to its place in pivot order, every lane
+    // reads it back; rows that were pivots before are updated along and ignored
+    double uinv = 0.0;
+    each<M>([&](auto T) {
+        constexpr int t = T;
+        uint32_t key[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+            key[h] = used[h] ? 0u : ((uint32_t)(__double_as_longlong(P[h][t]) >> 32) & 0x7FFFFFFFu) | 1u;
+        uint32_t top = max(key[0], key[1]);
+        top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0xB1, 0xF, 0xF, true));
+        top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x4E, 0xF, 0xF, true));
+        top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x141, 0xF, 0xF, true));
+        top = max(top, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)top, 0x140, 0xF, 0xF, true));
+        const bool hit0 = key[0] == top, hit1 = key[1] == top;
+        const uint64_t hits = __ballot(hit0 || hit1);
+        const bool me = ll == __builtin_ctz((uint32_t)(hits >> (16 * grp)) | 0x10000u);
+        if (me && hit0) {
+            store_row(t, 0);
+            used[0] = true;
+        }
+        if (me && !hit0) {
+            store_row(t, 1);
+            used[1] = true;
+        }
+        wave_lds_sync();
+        double U[M];
+#pragma unroll
+        for (int c = 0; c < M; ++c)
+            if (c >= t) U[c] = rows[t * RS + c];
+        if (!(fabs(U[t]) > line)) bad = true;
+        const double pi = recip(U[t]);
+        if (ll == t) uinv = pi;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const double l = P[h][t] * pi;
+            P[h][t] = l;
+#pragma unroll
+            for (int c = 0; c < M; ++c)
+                if (c > t) P[h][c] = __builtin_fma(-l, U[c], P[h][c]);
+        }
+    });
+    // set 2 behind set 1, in stencil order
+    {
+        const uint32_t f0 = (uint32_t)(__ballot(!used[0]) >> (16 * grp)) & 0xFFFFu;
+        const uint32_t f1 = (uint32_t)(__ballot(!used[1]) >> (16 * grp)) & 0xFFFFu;
+        const uint32_t below = (1u << ll) - 1u;
+        if (!used[0]) store_row(M + __popc(f0 & below), 0);
+        if (!used[1]) store_row(M + __popc(f0) + __popc(f1 & below), 1);
+    }
+    wave_lds_sync();
+    double LU[M], x1, y1, X[NS][M], x2[NS], y2[NS];
+    int slot1, slot2[NS];
+    {
+        const double *o = rows + min(ll, M - 1) * RS;
+#pragma unroll
+        for (int c = 0; c < M; ++c) LU[c] = o[c];
+        x1 = o[M];
+        y1 = o[M + 1];
+        slot1 = reinterpret_cast<const int *>(o + M + 2)[0];
+    }
+#pragma unroll
+    for (int r = 0; r < NS; ++r) {
+        const bool in = ll + 16 * r < N2;
+        const double *o = rows + (in ? M + ll + 16 * r : 0) * RS;
+#pragma unroll
+        for (int c = 0; c < M; ++c) X[r][c] = in ? o[c] : 0.0;
+        x2[r] = o[M];
+        y2[r] = o[M + 1];
+        slot2[r] = reinterpret_cast<const int *>(o + M + 2)[0];
+    }
+    // X = L2 L1^-1
+    each<M>([&](auto T) {
+        constexpr int t = M - 1 - T;
+#pragma unroll
+        for (int r = 0; r < NS; ++r) fmac_dot<t + 1, M, true>(X[r][t], &LU[t], X[r]);
+    });
+
+    // 2. S, row ll + 16 r in lane ll, with T1 = R21 - X R11 on the way
+    double S[NS][NP], T1[M][NS];
+    each<NP>([&](auto C) {
+        constexpr int c = C;
+        const double bx = lane_of<c % 16>(x2[c / 16]), by = lane_of<c % 16>(y2[c / 16]);
+#pragma unroll
+        for (int r = 0; r < NS; ++r) S[r][c] = cube_of(x2[r] - bx, y2[r] - by);
+    });
+    double XT[M][NS];   // X by column, as the broadcasts take it
+#pragma unroll
+    for (int j = 0; j < M; ++j)
+#pragma unroll
+        for (int r = 0; r < NS; ++r) XT[j][r] = X[r][j];
+    each<M>([&](auto J) {
+        constexpr int j = J;
+        const double bx = lane_of<j>(x1), by = lane_of<j>(y1);
+        const double r11 = cube_of(x1 - bx, y1 - by);
+        double r21[NS];
+#pragma unroll
+        for (int r = 0; r < NS; ++r) {
+            r21[r] = cube_of(x2[r] - bx, y2[r] - by);
+            T1[j][r] = r21[r];
+            fmac_dot<0, M, true>(T1[j][r], &r11, X[r]);
+        }
+#pragma unroll
+        for (int r = 0; r < NS; ++r) {
+            fmac_rows<0, NP, true>(S[r], r21, X[r][j]);
+            fmac_rows<0, NP, true>(S[r], XT[j], T1[j][r]);
+        }
+    });
+#pragma unroll
+    for (int c = 0; c < NP; ++c)
+#pragma unroll
+        for (int r = 0; r < NS; ++r)
+            if (c >= N2) S[r][c] = ll + 16 * r == c ? 1.0 : 0.0;
+    // S = L D L^T without a search: -L below the diagonal, D L^T on and above it
+    double dinv[NS];
+#pragma unroll
+    for (int r = 0; r < NS; ++r) dinv[r] = 0.0;
+    each<NP>([&](auto Kc) {
+        constexpr int k = Kc, rk = k / 16;
+        const double d = lane_of<k % 16>(S[rk][k]);
+        if (!(d > line)) bad = true;
+        const double di = recip(d);
+        if (ll == k % 16) dinv[rk] = di;
+        double nl[NS];
+#pragma unroll
+        for (int r = rk; r < NS; ++r) {
+            const bool under = ll + 16 * r > k;
+            nl[r] = under ? -S[r][k] * di : 0.0;
+            S[r][k] = under ? nl[r] : S[r][k];
+        }
+#pragma unroll
+        for (int r = NS - 1; r > rk; --r) fmac_lane<k % 16, k + 1, NP>(S[r], S[rk], nl[r]);
+        fmac_self<k % 16, k + 1, NP>(S[rk], nl[rk]);
+    });
+    if (bad && count > 0 && ll == 0) redo[1 + atomicAdd(&redo[0], 1)] = s;
+    double ST[NP][NS];   // S by column
+#pragma unroll
+    for (int c = 0; c < NP; ++c)
+#pragma unroll
+        for (int r = 0; r < NS; ++r) ST[c][r] = S[r][c];
+
+    // 3. departure points, one a lane
+    for (int c0 = 0; c0 < cmax; c0 += 16) {
+        const bool on = c0 + ll < count;
+        int p = 0, dir = 1;
+        double qx = 0.0, qy = 0.0;
+        if (on) {
+            rhs_point(L, s, c0 + ll, p, dir);
+            qx = (L.ptr ? min_image(xs[p] - lat_ex(dir) * dx - cx, g.Lx) : -lat_ex(dir) * dx) * irad;
+            qy = (L.ptr ? min_image(ys[p] - lat_ey(dir) * dx - cy, g.Ly) : -lat_ey(dir) * dx) * irad;
+        }
+        double y[M], b[NP];
+        monomials<M>(qx, qy, y);
+        each<M>([&](auto T) {   // y U
+            constexpr int t = T;
+            fmac_dot<0, t, true>(y[t], &LU[t], y);
+            y[t] *= lane_of<t>(uinv);
+        });
+        each<M>([&](auto T) {   // y L1
+            constexpr int t = M - 1 - T;
+            fmac_dot<t + 1, M, true>(y[t], &LU[t], y);
+        });
+        each<NP>([&](auto I) {
+            constexpr int i = I;
+            b[i] = cube_of(qx - lane_of<i % 16>(x2[i / 16]), qy - lane_of<i % 16>(y2[i / 16]));
+        });
+        each<M>([&](auto J) {
+            constexpr int j = J;
+            const double f1 = cube_of(qx - lane_of<j>(x1), qy - lane_of<j>(y1));
+            fmac_rows<0, NP, true>(b, XT[j], f1);
+            fmac_rows<0, NP, true>(b, T1[j], y[j]);
+        });
+        each<NP>([&](auto Kc) {
+            constexpr int k = Kc;
+            fmac_rows<k + 1, NP, false>(b, ST[k], b[k]);
+        });
+        each<NP>([&](auto Kc) {
+            constexpr int k = NP - 1 - Kc;
+            b[k] *= lane_of<k % 16>(dinv[k / 16]);
+            fmac_rows<0, k, true>(b, ST[k], b[k]);
+        });
+        each<M>([&](auto J) {
+            constexpr int j = J;
+            fmac_dot<0, NP, true>(y[j], XT[j], b);
+        });
+        each<M>([&](auto J) {
+            constexpr int j = J;
+            const int at = lane_of<j>(slot1);
+            if (on) W64[w64_at(dir, at, n, p)] = y[j];
+        });
+        each<NP>([&](auto I) {
+            constexpr int i = I;
+            const int at = lane_of<i % 16>(slot2[i / 16]);
+            if (on && i < N2) W64[w64_at(dir, at, n, p)] = b[i];
+        });
+    }
 }
 
 // Owner -> departure-point lists of the paper's stencil rule (CSR): count,
@@ -1274,38 +1651,30 @@ hipError_t launch_owner(const Geo *geo, const double *xs, const double *ys,
     return hipGetLastError();
 }
 
-template <int NB>
-static hipError_t launch_rbf_nb(const Geo *geo, const double *xs, const double *ys,
-                                const int32_t *perm, const int32_t *nbr, RhsList L, int n, int K,
-                                int m, double dx, double *W64, int32_t *dev_err, hipStream_t s) {
-    // 48 unknowns: the matrix-core solver (measured 10 % faster on the
-    // 262,144-node lattice, K 30, degree 4); at 64 unknowns the register
-    // tiles leave two wavefronts per SIMD and the row-per-lane solver is faster
-    if constexpr (NB == 48) {
-        hipLaunchKernelGGL((k_rbf_mfma<NB / 16>), dim3(xcd_grid(n)), dim3(64), 0, s, geo, xs, ys,
-                           perm, nbr, L, n, K, m, dx, W64, dev_err);
-        return hipGetLastError();
-    }
-    constexpr int wpe = NB <= 32 ? 4 : NB == 64 ? 2 : 3;
-    constexpr int sys = NB <= 32 ? 2 : 1;   // systems per wavefront
-    dim3 grid(xcd_grid(blocks_for(n, 4 * sys))), block(256);
-    // own-node stencils (exactly 8 departure points per owner) take the
-    // kernel without the replay, which need not keep the multipliers (the
-    // register allocator would park them in scratch memory). Splitting the
-    // paper rule's owners the same way (at most 8 departure points, then the
-    // rest) measured slower: the second launch runs a sparse tail.
-    if (L.ptr)
-        hipLaunchKernelGGL((k_rbf<NB, 8, wpe, sys, true>), grid, block, 0, s, geo, xs, ys, perm,
-                           nbr, L, n, K, m, dx, W64, dev_err);
-    else   // fewer registers live: one more wavefront per SIMD at 64 unknowns (at 24
-           // and 32 four is the most the registers allow either way)
-        hipLaunchKernelGGL((k_rbf<NB, 8, NB <= 32 ? 4 : wpe + 1, sys, false>), grid, block, 0, s,
-                           geo, xs, ys, perm, nbr, L, n, K, m, dx, W64, dev_err);
+// Sizes of k_rbf_null: N2 = K - M members beyond the polynomials, rounded up.
+template <int M>
+static hipError_t launch_rbf_null(const Geo *geo, const double *xs, const double *ys,
+                                  const int32_t *perm, const int32_t *nbr, RhsList L, int n, int K,
+                                  int m, double dx, int32_t *redo, double *W64, int32_t *dev_err,
+                                  hipStream_t s) {
+    const int N2 = K - M;
+    auto kernel = N2 <= 8 ? k_rbf_null<M, 8> : N2 <= 12 ? k_rbf_null<M, 12> : k_rbf_null<M, 16>;
+    if constexpr (M == 10)
+        if (N2 > 16) kernel = N2 <= 20 ? k_rbf_null<M, 20> : k_rbf_null<M, 24>;
+    if constexpr (M == 6)
+        if (N2 > 16) kernel = N2 <= 20 ? k_rbf_null<M, 20> : k_rbf_null<M, 28>;
+    hipError_t e = launch_fill_i32(redo, 0, 1, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(xcd_grid(blocks_for(n, 4))), dim3(64), 0, s, geo, xs, ys, nbr, L,
+                       n, K, dx, W64, redo);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_rbf_redo, dim3(256), dim3(64), 0, s, geo, xs, ys, perm, nbr, L, n, K, m, dx,
+                       redo, W64, dev_err);
     return hipGetLastError();
 }
 
 size_t rbf_temp_bytes(int n) {
-    const size_t a = ((size_t)n * 4 + 255) & ~size_t(255);
+    const size_t a = (((size_t)n + 1) * 4 + 255) & ~size_t(255);
     const size_t b = (((size_t)n + 1) * 4 + 255) & ~size_t(255);
     const size_t c = ((size_t)8 * n * 4 + 255) & ~size_t(255);
     return a + b + c + scan_temp_bytes(n) + 256;
@@ -1320,7 +1689,7 @@ hipError_t launch_rbf(const Geo *geo, const double *xs, const double *ys,
     if (mode == MLBM_STENCIL_PAPER) {
         char *b = (char *)tmp;
         int32_t *cnt = (int32_t *)b;
-        b += ((size_t)n * 4 + 255) & ~size_t(255);
+        b += (((size_t)n + 1) * 4 + 255) & ~size_t(255);
         int32_t *ptr = (int32_t *)b;
         b += (((size_t)n + 1) * 4 + 255) & ~size_t(255);
         int32_t *pts = (int32_t *)b;
@@ -1339,11 +1708,42 @@ hipError_t launch_rbf(const Geo *geo, const double *xs, const double *ys,
         L.ptr = ptr;
         L.pts = pts;
     }
-    const int nn = K + poly_count(m);
-    if (nn <= 24) return launch_rbf_nb<24>(geo, xs, ys, perm, nbr, L, n, K, m, dx, W64, dev_err, s);
-    if (nn <= 32) return launch_rbf_nb<32>(geo, xs, ys, perm, nbr, L, n, K, m, dx, W64, dev_err, s);
-    if (nn <= 48) return launch_rbf_nb<48>(geo, xs, ys, perm, nbr, L, n, K, m, dx, W64, dev_err, s);
-    return launch_rbf_nb<64>(geo, xs, ys, perm, nbr, L, n, K, m, dx, W64, dev_err, s);
+    // Stencils of up to 32 nodes take the null-space solver (31 at degree 4,
+    // where its registers end): 262,144 nodes, whole build, before -> with it,
+    // K 30 degree 4 5.7 -> 2.3 ms, K 25 degree 3 4.9 -> 1.8, K 25 degree 2
+    // 3.3 -> 1.9, K 20 degree 3 3.1 -> 1.6, K 15 degree 2 2.0 -> 1.1, K 12
+    // degree 2 (own stencils) 1.5 -> 0.7. Its list of owners to solve again
+    // takes the place of the list fill's counters, which are done with.
+    int32_t *redo = (int32_t *)tmp;
+    if (K <= (m == 4 ? 31 : 32)) {
+        if (m == 2)
+            return launch_rbf_null<6>(geo, xs, ys, perm, nbr, L, n, K, m, dx, redo, W64, dev_err, s);
+        if (m == 3)
+            return launch_rbf_null<10>(geo, xs, ys, perm, nbr, L, n, K, m, dx, redo, W64, dev_err, s);
+        return launch_rbf_null<15>(geo, xs, ys, perm, nbr, L, n, K, m, dx, redo, W64, dev_err, s);
+    }
+    // Larger ones the general elimination: up to 48 unknowns on the matrix
+    // cores (10 % faster than a row per lane, 262,144 nodes, 45 unknowns); at
+    // 64 the register tiles leave two wavefronts per SIMD and a row per lane
+    // is faster (K 47: 10.3 against 11.2 ms build)
+    if (K + poly_count(m) <= 48) {
+        hipLaunchKernelGGL(k_rbf_mfma<3>, dim3(xcd_grid(n)), dim3(64), 0, s, geo, xs, ys, perm, nbr, L,
+                           n, K, m, dx, W64, dev_err);
+        return hipGetLastError();
+    }
+    // own-node stencils (exactly 8 departure points per owner) take the
+    // kernel without the replay, which need not keep the multipliers (the
+    // register allocator would park them in scratch memory). Splitting the
+    // paper rule's owners the same way (at most 8 departure points, then the
+    // rest) measured slower: the second launch runs a sparse tail.
+    const dim3 grid(xcd_grid(blocks_for(n, 4))), block(256);
+    if (L.ptr)
+        hipLaunchKernelGGL((k_rbf<64, 8, 2, true>), grid, block, 0, s, geo, xs, ys, perm, nbr, L, n, K,
+                           m, dx, W64, dev_err);
+    else
+        hipLaunchKernelGGL((k_rbf<64, 8, 3, false>), grid, block, 0, s, geo, xs, ys, perm, nbr, L, n, K,
+                           m, dx, W64, dev_err);
+    return hipGetLastError();
 }
 
 hipError_t launch_pack_w32(const double *W64, int n, int K, float *W32, hipStream_t s) {

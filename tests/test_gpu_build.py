@@ -348,3 +348,52 @@ def test_fp32_weights_only_plan_steps_like_the_full_plan():
         q.close()
     for a, b in zip(*grads):
         assert torch.equal(a, b)
+
+
+# Sizes of the null-space solver (K up to 32, 31 at degree 4): members beyond the
+# polynomials at the edges of its compiled sizes (0, 8, 12, 16, 20, 24 and 28),
+# and the first stencils past it
+SOLVER_CASES = [(6, 2), (7, 2), (14, 2), (15, 2), (18, 2), (19, 2), (22, 2), (23, 2), (26, 2),
+                (27, 2), (32, 2), (33, 2), (10, 3), (18, 3), (19, 3), (26, 3), (27, 3), (31, 3),
+                (32, 3), (33, 3), (16, 4), (23, 4), (24, 4), (27, 4), (28, 4), (31, 4), (32, 4)]
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("K,m", SOLVER_CASES)
+def test_weights_at_the_edges_of_the_solver_sizes(K, m, mode):
+    """Shape vectors against the oracle's within the conditioning bound, on a
+    cloud whose last wavefront is partial."""
+    from paper_2306_01525_amd import Params, Plan
+    c, _, _ = tgv_case(13, K, m, mode, seed=29, ny=11, length_y=2 * np.pi * 11 / 13, jitter=0.2)
+    nbr, own, W = oracle.build_plan(c, c.h, K, m, mode)
+    wb = weight_bounds(c, nbr, own, W, K, m)
+    plan = Plan.build(c.x, c.y, c.period,
+                      Params(dx=c.h, K=K, degree=m, tau=0.8, stencil_mode=mode, precision=1))
+    np.testing.assert_array_equal(plan.export("nbr"), nbr)
+    dW = np.abs(plan.export("W")[:, 1:, :] - W[:, 1:, :]).max(axis=2)
+    say("K %d degree %d mode %d: n %d, most points of a node %d, max |dW| %.2e, of its bound %.2e"
+        % (K, m, mode, c.n, np.bincount(own[:, 1:].ravel()).max(), dW.max(),
+           (dW / wb[:, 1:]).max()))
+    assert (dW <= wb[:, 1:]).all()
+    assert plan.device_error() == 0
+    plan.close()
+
+
+@pytest.mark.parametrize("K,m", [(12, 2), (20, 3), (30, 4)])
+@pytest.mark.parametrize("gap", [1e-2, 1e-4])
+def test_weights_of_a_node_pair_close_together(gap, K, m):
+    """Two nodes a hundredth and a ten-thousandth of a spacing apart: the
+    latter's systems (condition numbers near 1e9 and beyond) are solved again
+    by the general elimination. Both within the conditioning bound."""
+    from paper_2306_01525_amd import Params, Plan
+    c, _, _ = tgv_case(20, K, m, 0, seed=3)
+    c.x[101], c.y[101] = c.x[57] + gap * c.h, c.y[57] + 0.3 * gap * c.h
+    nbr, own, W = oracle.build_plan(c, c.h, K, m, 0)
+    wb = weight_bounds(c, nbr, own, W, K, m)
+    plan = Plan.build(c.x, c.y, c.period,
+                      Params(dx=c.h, K=K, degree=m, tau=0.8, stencil_mode=0, precision=1))
+    dW = np.abs(plan.export("W")[:, 1:, :] - W[:, 1:, :]).max(axis=2)
+    say("gap %.0e K %d degree %d: max |dW| %.2e, of its bound %.2e"
+        % (gap, K, m, dW.max(), (dW / wb[:, 1:]).max()))
+    assert (dW <= wb[:, 1:]).all()
+    plan.close()
