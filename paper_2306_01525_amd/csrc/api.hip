@@ -425,8 +425,9 @@ mlbm_status build_cloud(mlbm_plan *plan, CloudPlan &cp, const mlbm_cloud &c,
                         std::max(1, 2 * bw.hb), s));
     MLBM_HIP(launch_scatter_sorted(cp.geo, c.x, c.y, c.node_type, cp.perm, bw.skeys, n, cp.xs,
                                    cp.ys, cp.ntype, cp.iperm, bw.cstart, bw.cend, bw.gx * bw.gy, s));
+    // (the solver's workspace is not in use yet: its head takes the search's list)
     MLBM_HIP(launch_knn(cp.geo, cp.xs, cp.ys, cp.perm, cp.iperm, bw.cstart, bw.cend, n, p.K,
-                        cp.nbr, s));
+                        (int32_t *)bw.rbf_tmp, cp.nbr, s));
     if (p.stencil_mode == MLBM_STENCIL_PAPER)
         MLBM_HIP(launch_owner(cp.geo, cp.xs, cp.ys, cp.perm, cp.iperm, bw.cstart, bw.cend, n,
                               p.dx, cp.owner, s));

@@ -29,6 +29,15 @@ __device__ __forceinline__ double dist2(double ax, double ay, double bx, double 
     return dx * dx + dy * dy;
 }
 
+// Orders the LDS accesses of one wavefront: LDS operations of a wavefront
+// complete in issue order, so only the compiler has to be kept from moving
+// accesses across this point.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Index of cell (x, y) along the Hilbert curve of a 2^order x 2^order grid
 // (the classic quadrant-rotation construction).
 __device__ uint32_t hilbert_index(uint32_t x, uint32_t y, int order) {
@@ -229,19 +238,16 @@ __device__ __forceinline__ void for_ring(const Geo &g, const int32_t *__restrict
 
 // Stencil of node p: p itself, then the K-1 closest other nodes by
 // (squared distance, user index). Rings of cells are scanned outwards until
-// every unscanned node is provably farther than the current (K-1)-th.
+// every unscanned node is provably farther than the current (K-1)-th. One
+// lane a node; it serves the nodes that k_knn leaves.
 template <int KMAX>
-__global__ __launch_bounds__(256) void k_knn(const Geo *__restrict__ geo,
-                                             const double *__restrict__ xs,
+__device__ __forceinline__ void knn_by_rings(const Geo &g, const double *__restrict__ xs,
                                              const double *__restrict__ ys,
                                              const int32_t *__restrict__ perm,
                                              const int32_t *__restrict__ iperm,
                                              const int32_t *__restrict__ cstart,
-                                             const int32_t *__restrict__ cend, int n, int K,
+                                             const int32_t *__restrict__ cend, int n, int K, int p,
                                              int32_t *__restrict__ nbr) {
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    const Geo g = *geo;
     const int live = K - 1, first = KMAX - live;
     double bd[KMAX];
     int bu[KMAX];
@@ -284,6 +290,186 @@ __global__ __launch_bounds__(256) void k_knn(const Geo *__restrict__ geo,
 #pragma unroll
     for (int q = 0; q < KMAX; ++q)
         if (q >= first) nbr[(int64_t)(q - first + 1) * n + p] = iperm[bu[q]];
+}
+
+
+__global__ __launch_bounds__(64) void k_knn_redo(
+    const Geo *__restrict__ geo, const double *__restrict__ xs, const double *__restrict__ ys,
+    const int32_t *__restrict__ perm, const int32_t *__restrict__ iperm,
+    const int32_t *__restrict__ cstart, const int32_t *__restrict__ cend, int n, int K,
+    const int32_t *__restrict__ redo, int32_t *__restrict__ nbr) {
+    const int count = min(redo[0], n);
+    for (int i = blockIdx.x * 64 + threadIdx.x; i < count; i += gridDim.x * 64)
+        knn_by_rings<kMaxK>(*geo, xs, ys, perm, iperm, cstart, cend, n, K, redo[1 + i], nbr);
+}
+
+// The same stencils, eight lanes a node. The nodes within a radius that
+// should hold a few more than K - 1 (from the count of the 5 x 5 cells around)
+// are listed in LDS; a list that comes out short, or longer than CAP, is taken
+// again with another radius. The place of an entry in the stencil is then the
+// number of entries before it, counted by comparing it with all of them: five
+// entries a lane and one LDS read for every entry of the list. (Inserting each
+// candidate into a sorted list in registers costs every lane of a wavefront a
+// pass over the list whenever one lane takes it, and one lane a node leaves a
+// small cloud's few wavefronts waiting for cells and nodes in turn: 909 us
+// against 209 on 262,144 nodes, K 30, and 182 against 20 on 10,201, K 25.)
+// Equal distances are decided by the user index in a second pass, which only
+// lists that have them (lattices) take. Lists that no radius brings into [K - 1, CAP] (more than
+// CAP nodes at one distance) go to k_knn_redo.
+constexpr int kKnnLanes = 8;
+template <int CAP>
+__global__ __launch_bounds__(256) void k_knn(
+    const Geo *__restrict__ geo, const double *__restrict__ xs, const double *__restrict__ ys,
+    const int32_t *__restrict__ perm, const int32_t *__restrict__ cstart,
+    const int32_t *__restrict__ cend, int n, int K, int32_t *__restrict__ redo,
+    int32_t *__restrict__ nbr) {
+    constexpr int G = kKnnLanes, QB = 256 / G, E = CAP / G;
+    __shared__ double s_d[QB][CAP + 1];   // (odd strides: the groups read distinct banks)
+    __shared__ int s_q[QB][CAP + 1];
+    __shared__ int s_cnt[QB];
+    __shared__ unsigned s_occ[QB][2];
+    const int64_t nb = ((int64_t)n + QB - 1) / QB, blk = xcd_tile(nb);
+    if (blk >= nb) return;
+    const Geo g = *geo;
+    const int grp = threadIdx.x / G, gl = threadIdx.x % G;
+    const int64_t pt = blk * QB + grp;
+    const bool live = pt < n;
+    const int p = live ? (int)pt : n - 1;
+    const double px = xs[p], py = ys[p];
+    const bool perx = g.Lx > 0.0, pery = g.Ly > 0.0;
+    int cx, cy;
+    cell_of(g, px, py, cx, cy);
+    // cell (ix, iy) of the grid, or -1 outside an open one
+    auto cell = [&](int ix, int iy) {
+        if (perx) ix += ix < 0 ? g.gx : ix >= g.gx ? -g.gx : 0;
+        if (pery) iy += iy < 0 ? g.gy : iy >= g.gy ? -g.gy : 0;
+        return ix < 0 || iy < 0 || ix >= g.gx || iy >= g.gy ? -1 : iy * g.gx + ix;
+    };
+    const int need = K - 1;
+    double lim2;   // squared radius of the list
+    {
+        int sum = 0, cells = 0;
+        if (g.gx >= 5 && g.gy >= 5) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int i = gl + t * G;
+                const int c = i < 25 ? cell(cx + i % 5 - 2, cy + i / 5 - 2) : -1;
+                if (c >= 0) {
+                    sum += cend[c] - cstart[c];
+                    ++cells;
+                }
+            }
+        }
+#pragma unroll
+        for (int off = 1; off < G; off <<= 1) {
+            sum += __shfl_xor(sum, off);
+            cells += __shfl_xor(cells, off);
+        }
+        const double per_cell = cells ? (double)sum / cells : (double)n / ((double)g.gx * g.gy);
+        lim2 = (1.15 * need + 5.0) / (3.14159265 * per_cell) * g.cw * g.ch;
+    }
+    int cnt = 0;
+    bool ok = false;
+    double lo2 = 0.0, hi2 = DBL_MAX;   // squared radii known to hold too few, too many
+    for (int tries = 0; tries < 16 && !ok; ++tries) {
+        if (gl == 0) s_cnt[grp] = 0;
+        wave_lds_sync();
+        auto take = [&](int q) {
+            const double d = dist2(px, py, xs[q], ys[q], g.Lx, g.Ly);
+            if (d < lim2 && q != p) {
+                const int at = atomicAdd(&s_cnt[grp], 1);
+                if (at < CAP) {
+                    s_d[grp][at] = d;
+                    s_q[grp][at] = q;
+                }
+            }
+        };
+        // every node closer than the radius lies at most rx, ry cells away
+        // (the margin covers the rounding of a node's cell)
+        const double lim = sqrt(lim2) * (1.0 + 1e-9);
+        const double fx = floor(lim / g.cw) + 1.0, fy = floor(lim / g.ch) + 1.0;
+        if ((perx && 2.0 * fx + 1.0 > g.gx) || (pery && 2.0 * fy + 1.0 > g.gy)) {
+            for (int q = gl; q < n; q += G) take(q);   // a block would meet cells twice
+        } else {
+            // (an open grid: the block ends at its edge)
+            const int rx = (int)fmin(fx, (double)g.gx), ry = (int)fmin(fy, (double)g.gy);
+            const int x0 = perx ? cx - rx : max(cx - rx, 0);
+            const int x1 = perx ? cx + rx : min(cx + rx, g.gx - 1);
+            const int y0 = pery ? cy - ry : max(cy - ry, 0);
+            const int y1 = pery ? cy + ry : min(cy + ry, g.gy - 1);
+            const int w = x1 - x0 + 1, count = w * (y1 - y0 + 1);
+            int ix = gl % w, iy = gl / w;
+            const int sx = G % w, sy = G / w;
+            for (int t = gl; t < count; t += G) {
+                const int c = cell(x0 + ix, y0 + iy);
+                const int e = cend[c];
+                for (int q = cstart[c]; q < e; ++q) take(q);
+                ix += sx;
+                iy += sy;
+                if (ix >= w) {
+                    ix -= w;
+                    ++iy;
+                }
+            }
+        }
+        wave_lds_sync();
+        cnt = s_cnt[grp];
+        wave_lds_sync();
+        ok = cnt >= need && cnt <= CAP;
+        if (!ok) {
+            (cnt < need ? lo2 : hi2) = lim2;
+            const double f = (1.15 * need + 5.0) / (cnt > 0 ? cnt : 1);
+            lim2 *= cnt < need ? fmin(fmax(f, 1.1), 4.0) : fmin(fmax(f, 0.25), 0.95);
+            if (!(lim2 > lo2 && lim2 < hi2)) lim2 = sqrt(lo2) * sqrt(hi2);
+        }
+    }
+    if (!ok) {
+        if (live && gl == 0) redo[1 + atomicAdd(&redo[0], 1)] = p;
+        cnt = 0;   // (the lanes stay: the steps below work across the wavefront)
+    }
+    double d[E];
+    int rank[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        d[e] = e * G + gl < cnt ? s_d[grp][e * G + gl] : -1.0;
+        rank[e] = 0;
+    }
+    int top = cnt;   // the wavefront's longest list
+#pragma unroll
+    for (int off = G; off < 64; off <<= 1) top = max(top, __shfl_xor(top, off));
+    top = __builtin_amdgcn_readfirstlane(top);
+#pragma unroll 4
+    for (int j = 0; j < cnt; ++j) {
+        const double dj = s_d[grp][j];
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (e * G < top) rank[e] += dj < d[e];
+    }
+    // two entries at one place: equal distances
+    if (gl < 2) s_occ[grp][gl] = 0u;
+    wave_lds_sync();
+    bool tie = false;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (e * G + gl < cnt && rank[e] < need) {
+            const unsigned bit = 1u << (rank[e] & 31);
+            if (atomicOr(&s_occ[grp][rank[e] >> 5], bit) & bit) tie = true;
+        }
+    if (__any(tie)) {
+#pragma unroll
+        for (int e = 0; e < E; ++e)
+            if (e * G + gl < cnt) {
+                const int u = perm[s_q[grp][e * G + gl]];
+                for (int j = 0; j < cnt; ++j)
+                    if (s_d[grp][j] == d[e] && perm[s_q[grp][j]] < u) ++rank[e];
+            }
+    }
+    if (!live || !ok) return;
+    if (gl == 0) nbr[p] = p;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+        if (e * G + gl < cnt && rank[e] < need)
+            nbr[(int64_t)(rank[e] + 1) * n + p] = s_q[grp][e * G + gl];
 }
 
 // Owner of each departure point x_p - e_k dx (k = 1..8): the closest node,
@@ -400,15 +586,6 @@ __device__ __forceinline__ double recip(double x) {
     r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
     r = __builtin_fma(r, __builtin_fma(-x, r, 1.0), r);
     return r;
-}
-
-// Orders the LDS accesses of one wavefront: LDS operations of a wavefront
-// complete in issue order, so only the compiler has to be kept from moving
-// accesses across this point.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // One wavefront solves the local system of an owner node, Phi w = phi(p)
@@ -1629,16 +1806,16 @@ hipError_t launch_scatter_sorted(const Geo *geo, const double *x, const double *
 
 hipError_t launch_knn(const Geo *geo, const double *xs, const double *ys,
                       const int32_t *perm, const int32_t *iperm, const int32_t *cstart,
-                      const int32_t *cend, int n, int K, int32_t *nbr, hipStream_t s) {
-    dim3 grid(blocks_for(n, 256)), block(256);
-    if (K - 1 <= 16)
-        hipLaunchKernelGGL(k_knn<16>, grid, block, 0, s, geo, xs, ys, perm, iperm, cstart, cend, n, K, nbr);
-    else if (K - 1 <= 24)   // (the list's cost per candidate grows with its length)
-        hipLaunchKernelGGL(k_knn<24>, grid, block, 0, s, geo, xs, ys, perm, iperm, cstart, cend, n, K, nbr);
-    else if (K - 1 <= 32)
-        hipLaunchKernelGGL(k_knn<32>, grid, block, 0, s, geo, xs, ys, perm, iperm, cstart, cend, n, K, nbr);
-    else
-        hipLaunchKernelGGL(k_knn<48>, grid, block, 0, s, geo, xs, ys, perm, iperm, cstart, cend, n, K, nbr);
+                      const int32_t *cend, int n, int K, int32_t *redo, int32_t *nbr,
+                      hipStream_t s) {
+    hipError_t e = launch_fill_i32(redo, 0, 1, s);
+    if (e != hipSuccess) return e;
+    const dim3 grid(xcd_grid(blocks_for(n, 256 / kKnnLanes)));
+    auto kernel = K <= 16 ? k_knn<32> : K <= 32 ? k_knn<64> : k_knn<96>;   // room for a third more
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, geo, xs, ys, perm, cstart, cend, n, K, redo, nbr);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    hipLaunchKernelGGL(k_knn_redo, dim3(64), dim3(64), 0, s, geo, xs, ys, perm, iperm, cstart, cend, n,
+                       K, redo, nbr);
     return hipGetLastError();
 }
 

@@ -306,7 +306,8 @@ hipError_t launch_scatter_sorted(const Geo *geo, const double *x, const double *
                                  int32_t *cend, int ncells, hipStream_t s);
 hipError_t launch_knn(const Geo *geo, const double *xs, const double *ys,
                       const int32_t *perm, const int32_t *iperm, const int32_t *cstart,
-                      const int32_t *cend, int n, int K, int32_t *nbr, hipStream_t s);
+                      const int32_t *cend, int n, int K, int32_t *redo, int32_t *nbr,
+                      hipStream_t s);   // redo: room for n + 1
 hipError_t launch_owner(const Geo *geo, const double *xs, const double *ys,
                         const int32_t *perm, const int32_t *iperm, const int32_t *cstart,
                         const int32_t *cend, int n, double dx, int32_t *owner,

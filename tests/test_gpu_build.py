@@ -397,3 +397,43 @@ def test_weights_of_a_node_pair_close_together(gap, K, m):
         % (gap, K, m, dW.max(), (dW / wb[:, 1:]).max()))
     assert (dW <= wb[:, 1:]).all()
     plan.close()
+
+
+def _search_clouds():
+    """(label, x, y, period, dx): exact lattices (many equal distances), clouds
+    smaller than the search block, an open strip, uniform random nodes, and a
+    lattice with 130 nodes inside a billionth of a spacing (no radius lists
+    them in part, for the nodes around it)."""
+    r = np.random.Generator(np.random.PCG64(41))
+    out = []
+    for nx, ny in ((24, 24), (9, 7)):
+        c = tgv_case(nx, 12, 2, 1, jitter=0.0, ny=ny, length=float(nx), length_y=float(ny))[0]
+        out.append(("lattice%dx%d" % (nx, ny), c.x, c.y, c.period, 1.0))
+    out.append(("open-strip", r.uniform(0, 60, 300), r.uniform(0, 3, 300), (0.0, 0.0), 0.5))
+    out.append(("random", r.uniform(0, 30, 1100), r.uniform(0, 36, 1100), (30.0, 36.0), 1.0))
+    c = tgv_case(20, 12, 2, 1, seed=5, length=20.0)[0]
+    a, d = r.uniform(0, 2 * np.pi, 130), 1e-9 * r.uniform(0.1, 1, 130)
+    out.append(("crowd", np.concatenate([c.x, 10.3 + d * np.cos(a)]),
+                np.concatenate([c.y, 9.7 + d * np.sin(a)]), c.period, 1.0))
+    return out
+
+
+@pytest.mark.parametrize("K", [6, 16, 17, 32, 33, 48])
+@pytest.mark.parametrize("which", range(5))
+def test_stencil_search_is_exact(which, K):
+    """Stencils and owners bit-exact against the oracle's, K at the edges of
+    the search's list sizes. The plan is captured, so that a singular local
+    system (the crowd's neighbours have them) does not end the build."""
+    from paper_2306_01525_amd import Params, Plan
+    label, x, y, period, dx = _search_clouds()[which]
+    m = 4 if K > 32 else 3 if K > 16 else 2
+    say("cloud", label, "n", x.shape[0], "K", K)
+    st = torch.cuda.Stream()
+    z = np.zeros(x.shape[0])
+    plan, _, _, _ = Plan.build_graph([(x, y, period, None)],
+                                     [Params(dx=dx, K=K, degree=m, tau=0.8)], z, z, 0, st)
+    plan.graph_launch(st)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(plan.export("nbr"), oracle.knn(x, y, period, K))
+    np.testing.assert_array_equal(plan.export("owner"), oracle.owners(x, y, period, dx, 0))
+    plan.close()
