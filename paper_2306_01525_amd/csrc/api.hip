@@ -429,8 +429,8 @@ mlbm_status build_cloud(mlbm_plan *plan, CloudPlan &cp, const mlbm_cloud &c,
     MLBM_HIP(launch_knn(cp.geo, cp.xs, cp.ys, cp.perm, cp.iperm, bw.cstart, bw.cend, n, p.K,
                         (int32_t *)bw.rbf_tmp, cp.nbr, s));
     if (p.stencil_mode == MLBM_STENCIL_PAPER)
-        MLBM_HIP(launch_owner(cp.geo, cp.xs, cp.ys, cp.perm, cp.iperm, bw.cstart, bw.cend, n,
-                              p.dx, cp.owner, s));
+        MLBM_HIP(launch_owner(cp.geo, cp.xs, cp.ys, cp.perm, bw.cstart, bw.cend, n, p.dx, cp.owner,
+                              s));
     MLBM_HIP(launch_rbf(cp.geo, cp.xs, cp.ys, cp.perm, cp.nbr, cp.owner, n, p.K, p.degree, p.dx,
                         p.stencil_mode, bw.rbf_tmp, bw.rbf_bytes, cp.W64, plan->dev_err, s));
     if (cp.W32) MLBM_HIP(launch_pack_w32(cp.W64, n, p.K, cp.W32, s));

@@ -473,53 +473,58 @@ __global__ __launch_bounds__(256) void k_knn(
 }
 
 // Owner of each departure point x_p - e_k dx (k = 1..8): the closest node,
-// ties to the lower user index.
+// ties to the lower user index. One thread a departure point: the cells of a
+// ring are loads that wait for one another, so a small cloud needs every
+// wavefront it can get (10,201 nodes: 126 us with one thread a node, 18 now;
+// 262,144 nodes: 176 and 117).
 __global__ __launch_bounds__(256) void k_owner(const Geo *__restrict__ geo,
                                                const double *__restrict__ xs,
                                                const double *__restrict__ ys,
                                                const int32_t *__restrict__ perm,
-                                               const int32_t *__restrict__ iperm,
                                                const int32_t *__restrict__ cstart,
                                                const int32_t *__restrict__ cend, int n,
                                                double dx, int32_t *__restrict__ owner) {
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
+    // eight directions of 32 nodes a workgroup, which share their cells
+    const int64_t nb = ((int64_t)n + 31) / 32, blk = xcd_tile(nb);
+    if (blk >= nb) return;
+    const int p = (int)(blk * 32) + (threadIdx.x & 31), k = (threadIdx.x >> 5) + 1;
     if (p >= n) return;
     const Geo g = *geo;
     const double cmin = fmin(g.cw, g.ch);
-    for (int k = 1; k < kQ; ++k) {
-        double qx = xs[p] - lat_ex(k) * dx;
-        double qy = ys[p] - lat_ey(k) * dx;
-        // cell of the departure point (wrapped into the periodic box)
-        double wx = qx, wy = qy;
-        if (g.Lx > 0.0) wx = wx - g.Lx * floor(wx / g.Lx);
-        if (g.Ly > 0.0) wy = wy - g.Ly * floor(wy / g.Ly);
-        int cx, cy;
-        cell_of(g, wx, wy, cx, cy);
-        double bd = DBL_MAX;
-        int bu = INT_MAX;
-        auto take = [&](int q) {
-            double d = dist2(qx, qy, xs[q], ys[q], g.Lx, g.Ly);
-            int u = perm[q];
-            if (d < bd || (d == bd && u < bu)) {
-                bd = d;
-                bu = u;
-            }
-        };
-        for (int r = 0;; ++r) {
-            bool wraps = (g.Lx > 0.0 && 2 * r + 1 > g.gx) || (g.Ly > 0.0 && 2 * r + 1 > g.gy);
-            if (wraps) {
-                bd = DBL_MAX;
-                bu = INT_MAX;
-                for (int q = 0; q < n; ++q) take(q);
-                break;
-            }
-            for_ring(g, cstart, cend, cx, cy, r, take);
-            double reach = r * cmin;
-            if (bd < reach * reach) break;
-            if (r > g.gx && r > g.gy) break;
+    const double qx = xs[p] - lat_ex(k) * dx;
+    const double qy = ys[p] - lat_ey(k) * dx;
+    // cell of the departure point (wrapped into the periodic box)
+    double wx = qx, wy = qy;
+    if (g.Lx > 0.0) wx = wx - g.Lx * floor(wx / g.Lx);
+    if (g.Ly > 0.0) wy = wy - g.Ly * floor(wy / g.Ly);
+    int cx, cy;
+    cell_of(g, wx, wy, cx, cy);
+    double bd = DBL_MAX;
+    int bu = INT_MAX, bq = 0;
+    auto take = [&](int q) {
+        const double d = dist2(qx, qy, xs[q], ys[q], g.Lx, g.Ly);
+        if (!(d <= bd)) return;
+        const int u = perm[q];
+        if (d < bd || u < bu) {
+            bd = d;
+            bu = u;
+            bq = q;
         }
-        owner[(int64_t)(k - 1) * n + p] = iperm[bu];
+    };
+    for (int r = 0;; ++r) {
+        bool wraps = (g.Lx > 0.0 && 2 * r + 1 > g.gx) || (g.Ly > 0.0 && 2 * r + 1 > g.gy);
+        if (wraps) {
+            bd = DBL_MAX;
+            bu = INT_MAX;
+            for (int q = 0; q < n; ++q) take(q);
+            break;
+        }
+        for_ring(g, cstart, cend, cx, cy, r, take);
+        double reach = r * cmin;
+        if (bd < reach * reach) break;
+        if (r > g.gx && r > g.gy) break;
     }
+    owner[(int64_t)(k - 1) * n + p] = bq;
 }
 
 // x^e for 0 <= e <= 4, without branches on e, so that a lane-dependent
@@ -1820,11 +1825,10 @@ hipError_t launch_knn(const Geo *geo, const double *xs, const double *ys,
 }
 
 hipError_t launch_owner(const Geo *geo, const double *xs, const double *ys,
-                        const int32_t *perm, const int32_t *iperm, const int32_t *cstart,
-                        const int32_t *cend, int n, double dx, int32_t *owner,
-                        hipStream_t s) {
-    hipLaunchKernelGGL(k_owner, dim3(blocks_for(n, 256)), dim3(256), 0, s, geo, xs, ys, perm,
-                       iperm, cstart, cend, n, dx, owner);
+                        const int32_t *perm, const int32_t *cstart, const int32_t *cend, int n,
+                        double dx, int32_t *owner, hipStream_t s) {
+    hipLaunchKernelGGL(k_owner, dim3(xcd_grid(blocks_for(n, 32))), dim3(256), 0, s, geo, xs, ys,
+                       perm, cstart, cend, n, dx, owner);
     return hipGetLastError();
 }
 

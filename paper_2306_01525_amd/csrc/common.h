@@ -309,9 +309,8 @@ hipError_t launch_knn(const Geo *geo, const double *xs, const double *ys,
                       const int32_t *cend, int n, int K, int32_t *redo, int32_t *nbr,
                       hipStream_t s);   // redo: room for n + 1
 hipError_t launch_owner(const Geo *geo, const double *xs, const double *ys,
-                        const int32_t *perm, const int32_t *iperm, const int32_t *cstart,
-                        const int32_t *cend, int n, double dx, int32_t *owner,
-                        hipStream_t s);
+                        const int32_t *perm, const int32_t *cstart, const int32_t *cend, int n,
+                        double dx, int32_t *owner, hipStream_t s);
 // workspace of the paper-mode owner lists: counts [n], offsets [n+1],
 // points [8n], scan temp
 size_t rbf_temp_bytes(int n);

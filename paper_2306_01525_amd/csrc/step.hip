@@ -1266,6 +1266,9 @@ __global__ __launch_bounds__(256) void k_lbm_step(int nx, int ny, int64_t nblock
 // Interpolation alone (Sec. 4, Fig. interp_test): the streaming operator of
 // the plan applied to a scalar field, in FP64 with the FP64 shape vectors.
 // out[k-1][u] = sum_j W_k[j](p) field[user(nbr[j][owner_k(p)])], u = user(p).
+// One thread a departure point, six slots at a time: member, user index and
+// value are three loads one after another, which one thread a node went
+// through 8 K times in turn (10,201 nodes, K 25: 95 us, 11 now).
 __global__ __launch_bounds__(256) void k_interpolate(int n, int K, int mode,
                                                      const double *__restrict__ W64,
                                                      const int32_t *__restrict__ nbr,
@@ -1273,23 +1276,43 @@ __global__ __launch_bounds__(256) void k_interpolate(int n, int K, int mode,
                                                      const int32_t *__restrict__ perm,
                                                      const double *__restrict__ field,
                                                      int64_t out_stride, double *__restrict__ out) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
+    // pairs of directions side by side, as the shape vectors lie: 128 nodes a
+    // workgroup and pair
+    const int64_t nb = ((int64_t)n + 127) / 128, blk = xcd_tile(nb);
+    if (blk >= nb) return;
+    const int p = (int)(blk * 128) + (int)(threadIdx.x >> 1);
+    const int k = 2 * (int)blockIdx.y + (int)(threadIdx.x & 1) + 1;
     if (p >= n) return;
     const int u = perm[p];
-    for (int k = 1; k < kQ; ++k) {
-        const int s = mode == MLBM_STENCIL_OWN ? p : owner[(int64_t)(k - 1) * n + p];
-        double acc = 0.0;
-        for (int j = 0; j < K; ++j)
-            acc = __builtin_fma(W64[w64_at(k, j, n, p)], field[perm[nbr[(int64_t)j * n + s]]], acc);
-        out[(int64_t)(k - 1) * out_stride + u] = acc;
+    const int s = mode == MLBM_STENCIL_OWN ? p : owner[(int64_t)(k - 1) * n + p];
+    double acc = 0.0;
+    constexpr int CH = 6;
+    int j = 0;
+    for (; j + CH <= K; j += CH) {
+        int q[CH];
+        double w[CH], v[CH];
+#pragma unroll
+        for (int i = 0; i < CH; ++i) {
+            q[i] = nbr[(int64_t)(j + i) * n + s];
+            w[i] = W64[w64_at(k, j + i, n, p)];
+        }
+#pragma unroll
+        for (int i = 0; i < CH; ++i) q[i] = perm[q[i]];
+#pragma unroll
+        for (int i = 0; i < CH; ++i) v[i] = field[q[i]];
+#pragma unroll
+        for (int i = 0; i < CH; ++i) acc = __builtin_fma(w[i], v[i], acc);
     }
+    for (; j < K; ++j)
+        acc = __builtin_fma(W64[w64_at(k, j, n, p)], field[perm[nbr[(int64_t)j * n + s]]], acc);
+    out[(int64_t)(k - 1) * out_stride + u] = acc;
 }
 
 }  // namespace
 
 hipError_t launch_interpolate(const CloudPlan &cp, const double *field, int64_t out_stride,
                               double *out, hipStream_t s) {
-    hipLaunchKernelGGL(k_interpolate, dim3(blocks_for(cp.n, 256)), dim3(256), 0, s, cp.n, cp.K,
+    hipLaunchKernelGGL(k_interpolate, dim3(xcd_grid(blocks_for(cp.n, 128)), 4), dim3(256), 0, s, cp.n, cp.K,
                        cp.prm.stencil_mode, cp.W64, cp.nbr, cp.owner, cp.perm, field, out_stride,
                        out);
     return hipGetLastError();

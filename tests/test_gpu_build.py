@@ -437,3 +437,24 @@ def test_stencil_search_is_exact(which, K):
     np.testing.assert_array_equal(plan.export("nbr"), oracle.knn(x, y, period, K))
     np.testing.assert_array_equal(plan.export("owner"), oracle.owners(x, y, period, dx, 0))
     plan.close()
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("nx,ny,K", [(5, 5, 6), (13, 5, 7), (43, 3, 11), (16, 8, 12), (17, 15, 29)])
+def test_interpolation_at_ragged_sizes(nx, ny, K, mode):
+    """The interpolation operator against its definition on the plan's own
+    stencils and weights; slots left over from groups of six, partial
+    workgroups. Both sum K products in FP64: off by at most K 2^-53 of the sum
+    of their magnitudes, twice."""
+    from paper_2306_01525_amd import Params, Plan
+    c, _, _ = tgv_case(nx, K, 2, mode, seed=31, ny=ny, length_y=2 * np.pi * ny / nx, jitter=0.2)
+    dx = min(c.h, 0.4 * min(c.period))
+    plan = Plan.build(c.x, c.y, c.period,
+                      Params(dx=dx, K=K, degree=2, tau=0.8, stencil_mode=mode, precision=1))
+    f = np.random.Generator(np.random.PCG64(7)).standard_normal(c.n)
+    got = plan.interpolate(f).cpu().numpy()
+    nbr, own, W = (plan.export(a) for a in ("nbr", "owner", "W"))
+    for k in range(1, 9):
+        terms = W[:, k] * f[nbr[own[:, k]]]
+        assert (np.abs(got[k - 1] - terms.sum(1)) <= 2 * K * 2.0 ** -53 * np.abs(terms).sum(1)).all()
+    plan.close()
