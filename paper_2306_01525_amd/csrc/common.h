@@ -361,7 +361,9 @@ hipError_t launch_residual(const CloudPlan &cp, int precision, const void *g, do
 hipError_t launch_interpolate(const CloudPlan &cp, const double *field, int64_t out_stride,
                               double *out, hipStream_t s);
 // standard lattice Boltzmann on a periodic nx x ny lattice, state [9][ny][nx]
-hipError_t launch_lbm_step(int nx, int ny, int precision, double tau, double rho0,
+// steps <= lbm_steps_per_launch
+int lbm_steps_per_launch(int nx, int ny, int precision);
+hipError_t launch_lbm_step(int nx, int ny, int precision, double tau, double rho0, int steps,
                            const void *g, void *go, hipStream_t s);
 hipError_t launch_lbm_init(int n, int precision, double rho0, const double *rho, const double *ux,
                            const double *uy, void *g, hipStream_t s);

@@ -1263,6 +1263,110 @@ __global__ __launch_bounds__(256) void k_lbm_step(int nx, int ny, int64_t nblock
                                              nullptr, nullptr, nullptr, 0);
 }
 
+// One collision with the step's arithmetic, in registers.
+__device__ __forceinline__ void lbm_collide(float (&f)[kQ], float (&v)[kQ], float rtau, float rho0) {
+    collide_at32<false, 0, false>(1, 0, f, v, 0u, 0.0f, 0.0f, rtau, rho0, 0.0f, nullptr, nullptr,
+                                  nullptr, 0);
+}
+__device__ __forceinline__ void lbm_collide(double (&f)[kQ], double (&v)[kQ], double rtau, double) {
+    collide_at64<false, 0, false>(1, 0, f, v, 0u, 0.0, 0.0, rtau, 0.0, nullptr, nullptr, nullptr, 0);
+}
+
+// S steps in one pass over memory. A workgroup makes a block of TX x TY nodes:
+// the first step pulls from global memory for the block and S - 1 nodes around
+// it, the next ones pull from LDS, each for one node less on every side, and
+// the last writes the block. Every population is pulled by one node only, so
+// LDS needs no copy of the input, and one buffer: the new values wait in
+// registers until all have been read. The arithmetic is that of single steps
+// and so are the bits.
+// A step alone is bound by memory, 72 (FP32) or 144 bytes a node, or on a
+// small lattice by its launch and two trips to memory; S steps share those.
+// 3 or 4 of them: FP32 2048^2 49.2 -> 28.3 us a step, 1024^2 12.1 -> 8.6,
+// 512^2 4.5 -> 3.6, 160^2 3.4 -> 1.8; FP64 115 -> 51.7, 23.1 -> 12.1, 7.1 ->
+// 4.9, 3.5 -> 2.0. What bounds them now is the arithmetic of the block and the
+// nodes around it, at 512 threads and three workgroups a CU.
+template <class T, int TX, int CAP, int NTH, int S>
+__global__ __launch_bounds__(NTH) void k_lbm_steps(int nx, int ny, int64_t nblocks,
+                                                   const T *__restrict__ g, T *__restrict__ go,
+                                                   T rtau, T rho0) {
+    constexpr int R = S - 1, W = TX + 2 * R, H = CAP / W, TY = H - 2 * R, N = W * H;
+    constexpr int NPT = (N + NTH - 1) / NTH;
+    static_assert(TY > 0 && S > 1, "room for the block");
+    __shared__ T s[kQ][N];
+    const int64_t b = xcd_tile(nblocks);
+    if (b >= nblocks) return;
+    const int bx = (nx + TX - 1) / TX, by = (int)(b / bx);
+    const int x0 = (int)(b - (int64_t)by * bx) * TX - R, y0 = by * TY - R;
+    const int tid = threadIdx.x;
+    const int64_t n = (int64_t)nx * ny;
+    T v[NPT][kQ];
+#pragma unroll
+    for (int i = 0; i < NPT; ++i) {
+        const int at = tid + i * NTH;
+        if (at < N) {
+            // (blocks may reach past the lattice, and around a small one more than once)
+            int x = (x0 + at % W) % nx, y = (y0 + at / W) % ny;
+            x += x < 0 ? nx : 0;
+            y += y < 0 ? ny : 0;
+            T f[kQ];
+#pragma unroll
+            for (int k = 0; k < kQ; ++k) {
+                int sx = x - (int)lat_ex(k), sy = y - (int)lat_ey(k);
+                sx = sx < 0 ? sx + nx : (sx >= nx ? sx - nx : sx);
+                sy = sy < 0 ? sy + ny : (sy >= ny ? sy - ny : sy);
+                f[k] = g[(int64_t)k * n + (int64_t)sy * nx + sx];
+            }
+            lbm_collide(f, v[i], rtau, rho0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NPT; ++i)
+        if (tid + i * NTH < N) {
+#pragma unroll
+            for (int k = 0; k < kQ; ++k) s[k][tid + i * NTH] = v[i][k];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int m = 1; m < S; ++m) {
+#pragma unroll
+        for (int i = 0; i < NPT; ++i) {
+            const int at = tid + i * NTH, lx = at % W, ly = at / W;
+            if (lx >= m && lx < W - m && ly >= m && ly < H - m) {
+                T f[kQ];
+#pragma unroll
+                for (int k = 0; k < kQ; ++k) f[k] = s[k][at - (int)lat_ey(k) * W - (int)lat_ex(k)];
+                lbm_collide(f, v[i], rtau, rho0);
+                if (m == S - 1 && x0 + lx < nx && y0 + ly < ny) {
+#pragma unroll
+                    for (int k = 0; k < kQ; ++k)
+                        go[(int64_t)k * n + (int64_t)(y0 + ly) * nx + (x0 + lx)] = v[i][k];
+                }
+            }
+        }
+        if (m < S - 1) {
+            __syncthreads();
+#pragma unroll
+            for (int i = 0; i < NPT; ++i) {
+                const int at = tid + i * NTH, lx = at % W, ly = at / W;
+                if (lx >= m && lx < W - m && ly >= m && ly < H - m) {
+#pragma unroll
+                    for (int k = 0; k < kQ; ++k) s[k][at] = v[i][k];
+                }
+            }
+            __syncthreads();
+        }
+    }
+}
+
+template <class T, int TX, int CAP, int NTH, int S>
+void launch_lbm_steps(int nx, int ny, double rtau, double rho0, const void *g, void *go,
+                      hipStream_t s) {
+    constexpr int TY = CAP / (TX + 2 * (S - 1)) - 2 * (S - 1);
+    const int64_t nb = (int64_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY);
+    hipLaunchKernelGGL((k_lbm_steps<T, TX, CAP, NTH, S>), dim3(xcd_grid(nb)), dim3(NTH), 0, s, nx, ny,
+                       nb, (const T *)g, (T *)go, (T)rtau, (T)rho0);
+}
+
 // Interpolation alone (Sec. 4, Fig. interp_test): the streaming operator of
 // the plan applied to a scalar field, in FP64 with the FP64 shape vectors.
 // out[k-1][u] = sum_j W_k[j](p) field[user(nbr[j][owner_k(p)])], u = user(p).
@@ -1464,15 +1568,47 @@ hipError_t launch_l2_final(const double *part, int64_t nparts, double *out, hipS
     return hipGetLastError();
 }
 
-hipError_t launch_lbm_step(int nx, int ny, int precision, double tau, double rho0,
+// Steps per launch and blocks. Up to 131,072 nodes blocks of about 500 nodes,
+// of which more CUs get one (160^2: 1.8 us a step against 2.6 with the large
+// ones; 512^2: 4.1 against 3.6); above, blocks that fill a third of a CU's LDS.
+// Four steps in a launch, three in between where four lose to the nodes that
+// neighbouring blocks compute twice (FP32 512^2 3.6 against 4.1 us; FP64
+// 1024^2 12.1 against 13.2).
+constexpr int64_t kLbmSmall = 131072;
+int lbm_steps_per_launch(int nx, int ny, int precision) {
+    const int64_t n = (int64_t)nx * ny;
+    return n > kLbmSmall && n <= (precision == MLBM_FP64 ? 1 << 21 : 1 << 20) ? 3 : 4;
+}
+
+template <class T, int TX, int CAP, int NTH>
+void launch_lbm_fused(int nx, int ny, double rtau, double rho0, int steps, const void *g, void *go,
+                      hipStream_t s) {
+    if (steps == 2) launch_lbm_steps<T, TX, CAP, NTH, 2>(nx, ny, rtau, rho0, g, go, s);
+    else if (steps == 3) launch_lbm_steps<T, TX, CAP, NTH, 3>(nx, ny, rtau, rho0, g, go, s);
+    else launch_lbm_steps<T, TX, CAP, NTH, 4>(nx, ny, rtau, rho0, g, go, s);
+}
+
+hipError_t launch_lbm_step(int nx, int ny, int precision, double tau, double rho0, int steps,
                            const void *g, void *go, hipStream_t s) {
-    const int64_t nblocks = (int64_t)ny * ((nx + 255) / 256);
-    if (precision == MLBM_FP64)
-        hipLaunchKernelGGL(k_lbm_step<double>, dim3(xcd_grid(nblocks)), dim3(256), 0, s, nx, ny,
-                           nblocks, (const double *)g, (double *)go, 1.0 / tau, rho0);
-    else
-        hipLaunchKernelGGL(k_lbm_step<float>, dim3(xcd_grid(nblocks)), dim3(256), 0, s, nx, ny,
-                           nblocks, (const float *)g, (float *)go, 1.0 / tau, rho0);
+    const double rtau = 1.0 / tau;
+    if (steps == 1) {
+        const int64_t nblocks = (int64_t)ny * ((nx + 255) / 256);
+        if (precision == MLBM_FP64)
+            hipLaunchKernelGGL(k_lbm_step<double>, dim3(xcd_grid(nblocks)), dim3(256), 0, s, nx, ny,
+                               nblocks, (const double *)g, (double *)go, rtau, rho0);
+        else
+            hipLaunchKernelGGL(k_lbm_step<float>, dim3(xcd_grid(nblocks)), dim3(256), 0, s, nx, ny,
+                               nblocks, (const float *)g, (float *)go, rtau, rho0);
+        return hipGetLastError();
+    }
+    const bool small = (int64_t)nx * ny <= kLbmSmall;
+    if (precision == MLBM_FP64) {
+        if (small) launch_lbm_fused<double, 32, 512, 256>(nx, ny, rtau, rho0, steps, g, go, s);
+        else launch_lbm_fused<double, 32, 728, 256>(nx, ny, rtau, rho0, steps, g, go, s);
+    } else {
+        if (small) launch_lbm_fused<float, 32, 512, 256>(nx, ny, rtau, rho0, steps, g, go, s);
+        else launch_lbm_fused<float, 64, 1456, 512>(nx, ny, rtau, rho0, steps, g, go, s);
+    }
     return hipGetLastError();
 }
 

@@ -85,3 +85,24 @@ def test_mlbm_on_regular_lattice_equals_lbm(mode):
     e = rel_l2(np.stack([um, vm]), np.stack([ul, vl]))
     say("mode %d: MLBM on the lattice vs LBM after %d steps: %.2e" % (mode, steps, e))
     assert e < TOL_FP64
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("nx,ny", [(1, 1), (2, 3), (5, 70), (31, 7), (32, 10), (33, 65), (512, 256),
+                                   (513, 256), (577, 431), (1025, 1030), (2049, 1030)])
+def test_steps_in_one_launch_equal_single_steps(nx, ny, precision):
+    """Several steps in one launch give bitwise the states of single steps:
+    lattices smaller than a block, partial blocks, both block sizes and steps
+    per launch; the result is in the second buffer after an odd number."""
+    from paper_2306_01525_amd.lbm import Lattice
+    lat = Lattice(nx, ny, 0.7, precision)
+    r = np.random.Generator(np.random.PCG64(nx * 7 + ny))
+    u, v = 0.02 * r.standard_normal((2, nx * ny))
+    one, other = lat.init(u, v), lat.new_state()
+    for steps in range(1, 10):
+        lat.step(one, other, 1)
+        one, other = other, one
+        a, b = lat.init(u, v), lat.new_state()
+        res = lat.step(a, b, steps)
+        assert res is (b if steps % 2 else a)
+        assert torch.equal(res, one), steps
