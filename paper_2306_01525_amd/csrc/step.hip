@@ -663,7 +663,10 @@ __device__ __forceinline__ void wide_finish(const WideArgs<double> &a, int p, do
 // so the states are bitwise the same. 6,400 nodes, K 25: FP64 32.4 -> 6.1 us
 // a step, FP32 8.3 -> 5.4; 1,600 nodes, K 12: FP32 5.6 -> 4.7, FP64 8.8 -> 4.8.
 // Of those, 2.7 us go by for a launch and one trip to memory, two more for the
-// halo's.
+// halo's. Own-node stencils of few nodes gather from global memory instead:
+// 1,600 nodes, K 12, 4.7 -> 4.0 (FP32) and 4.8 -> 4.5 us (FP64); at K 20 both
+// ways cost the same, at K 30 the halo is cheaper (FP64 6.0 against 6.3), and
+// with two directions a lane it is at every K (22,500 nodes FP64 6.4 / 8.4).
 template <class T, int MODE, bool FORCE, int WALL, bool REC, int D>
 __global__ __launch_bounds__(256) void k_step_wide(WideArgs<T> a, const T *__restrict__ g,
                                                    T *__restrict__ go, int64_t nblocks) {
@@ -694,13 +697,16 @@ __global__ __launch_bounds__(256) void k_step_wide(WideArgs<T> a, const T *__res
     const T *wbase = a.W + (int64_t)row * n * EPR;
     const uint32_t woff = (uint32_t)(p * EPR + (lane % LPR) * D) * sizeof(T);
     auto weights = [&](int j) { return load_at<TD>(wbase + (int64_t)j * 8 * n, woff); };
+    // own-node stencils of up to 18 nodes: a lane's populations are fewer than
+    // its share of the halo, and need the stencil alone (no halo list, no LDS)
+    const bool direct = MODE == MLBM_STENCIL_OWN && D == 1 && K <= 3 * CH;
     int q[U] = {};
-    if (a.tdesc) {   // (every tile has room for kHaloCap entries: no wait for its count)
+    if (a.tdesc && !direct) {   // (every tile has room for kHaloCap entries: no wait for its count)
         const int32_t *hl = a.hlist + tile * (int64_t)a.hcap;
 #pragma unroll
         for (int u = 0; u < U; ++u) q[u] = load_at<int32_t>(hl, (uint32_t)(tid + u * 256) * 4);
     }
-    const int nh0 = a.tdesc ? a.tdesc[2 * tile + 1] : 0;
+    const int nh0 = a.tdesc && !direct ? a.tdesc[2 * tile + 1] : 0;
     const int nh = nh0 <= a.nhcap ? nh0 : 0;
     T acc[D];
 #pragma unroll
@@ -792,6 +798,39 @@ __global__ __launch_bounds__(256) void k_step_wide(WideArgs<T> a, const T *__res
             }
         }
         __syncthreads();   // the halo is read by everyone: its space takes the sums
+    } else if (direct) {
+        TD w[3][CH];
+        int at[3][CH];
+        T x[3][CH][D];
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (c * CH < K) {
+#pragma unroll
+                for (int j = 0; j < CH; ++j) {
+                    const int jj = min(c * CH + j, K - 1);
+                    at[c][j] = load_at<int32_t>(a.nbr + (int64_t)jj * n, (uint32_t)p * 4);
+                    w[c][j] = weights(jj);
+                }
+            }
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (c * CH < K) {
+#pragma unroll
+                for (int j = 0; j < CH; ++j)
+#pragma unroll
+                    for (int i = 0; i < D; ++i)
+                        x[c][j][i] = load_at<T>(g + (int64_t)(d0 + i + 1) * n,
+                                                (uint32_t)at[c][j] * sizeof(T));
+            }
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+            if (c * CH < K) {
+#pragma unroll
+                for (int j = 0; j < CH; ++j)
+#pragma unroll
+                    for (int i = 0; i < D; ++i)
+                        acc[i] = wide_fma(w[c][j][i], c * CH + j < K ? x[c][j][i] : (T)0, acc[i]);
+            }
     } else {
         int s[D];
 #pragma unroll

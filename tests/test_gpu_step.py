@@ -283,11 +283,12 @@ def test_extreme_stencil_sizes_match_oracle(label, K, m, mode, steps, tol64):
 # Sizes around the lines between the step kernels: 32 nodes a workgroup up to
 # 8,192 nodes, 64 up to 49,152 (FP32) or 102,400 (FP64), whole tiles above;
 # partial workgroups and tiles, and stencils that fill their last chunk of six
-# slots or leave one to five of it open.
+# slots or leave one to five of it open; own-node stencils of up to 18 nodes
+# gather directly.
 SIZE_CASES = [
     # (nx, ny, K, degree, mode, precision)
     (5, 5, 6, 2, 1, 0), (8, 4, 7, 2, 1, 1), (11, 3, 8, 2, 1, 0), (13, 5, 9, 2, 1, 1),
-    (51, 5, 12, 2, 1, 0), (16, 16, 20, 3, 0, 1),
+    (51, 5, 12, 2, 1, 0), (40, 40, 18, 2, 1, 1), (41, 39, 19, 3, 1, 0), (16, 16, 20, 3, 0, 1),
     (128, 64, 25, 3, 0, 0), (128, 64, 30, 4, 0, 1), (82, 100, 26, 2, 0, 0), (83, 99, 35, 4, 0, 1),
     (97, 89, 47, 4, 0, 1), (256, 192, 20, 3, 0, 0), (257, 192, 20, 3, 0, 0),
     (320, 320, 20, 2, 0, 1), (321, 320, 20, 2, 0, 1),
