@@ -340,6 +340,23 @@ mlbm_status mlbm_loss_seed(const mlbm_plan *plan, const void *f_T, const double 
 mlbm_status mlbm_step_adjoint(const mlbm_plan *plan, const void *f_n, const void *lamf_next,
                               void *lamf_n, double *dJ_dtau, hipStream_t stream);
 
+/* n_steps reversed steps: f_rec holds the recorded f^n of n_steps consecutive
+ * steps, as mlbm_step_record leaves them (n_steps * state_bytes), and the last
+ * one is reversed first. lamf_a: the adjoint after the last of them; ping-pong
+ * with lamf_b, *result_in_b (host) = 1 when the adjoint before the first is in
+ * lamf_b. Instead of a sum per step, dJ/dtau is kept in partial sums: parts
+ * (device FP64 [mlbm_adjoint_parts], caller-owned) is overwritten by the first
+ * reversed step when `first` is not 0 and added to otherwise, so several calls
+ * can share it; mlbm_adjoint_tau then adds their sum into dJ_dtau (device FP64
+ * [1]). The sums do not depend on how the steps are cut into calls.
+ * mlbm_adjoint_parts returns 0 for a plan without the adjoint. */
+int64_t mlbm_adjoint_parts(const mlbm_plan *plan);
+mlbm_status mlbm_steps_adjoint(const mlbm_plan *plan, const void *f_rec, int32_t n_steps,
+                               void *lamf_a, void *lamf_b, double *parts, int32_t first,
+                               int32_t *result_in_b, hipStream_t stream);
+mlbm_status mlbm_adjoint_tau(const mlbm_plan *plan, const double *parts, double *dJ_dtau,
+                             hipStream_t stream);
+
 /* dJ/du0 = (d feq(rho0, u0) / d u0)^T lamf_0, with f^0 = feq(rho0, u0) the
  * state before the first collision. u0x, u0y: device FP64 [n_total], user
  * order (NULL = 0); outputs device FP64 [n_total] each, user order. */

@@ -78,6 +78,10 @@ SIGNATURES = {
     "mlbm_lbm_moments": (_c_i32, [_c_i32, _c_i32, _c_i32, _c_d, _c_p, _c_p, _c_p, _c_p, _c_p]),
     "mlbm_loss_seed": (_c_i32, [_c_p, _c_p, _c_p, _c_p, _c_p, _c_p, _c_p]),
     "mlbm_step_adjoint": (_c_i32, [_c_p, _c_p, _c_p, _c_p, _c_p, _c_p]),
+    "mlbm_adjoint_parts": (_c_i64, [_c_p]),
+    "mlbm_steps_adjoint": (_c_i32, [_c_p, _c_p, _c_i32, _c_p, _c_p, _c_p, _c_i32, _P(_c_i32),
+                                    _c_p]),
+    "mlbm_adjoint_tau": (_c_i32, [_c_p, _c_p, _c_p, _c_p]),
     "mlbm_init_adjoint": (_c_i32, [_c_p, _c_p, _c_p, _c_p, _c_p, _c_p, _c_p]),
     "mlbm_autotune": (_c_i32, [_c_p, _c_p, _c_p, _c_i32, _c_p, _P(_c_i32), _c_p]),
     "mlbm_plan_set_variant": (_c_i32, [_c_p, _c_i32]),

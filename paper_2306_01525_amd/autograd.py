@@ -6,7 +6,7 @@ Gradients with respect to the initial velocity u0 and the relaxation time tau.
 Forward keeps the pre-collision state f at the start of every segment of C
 steps. Backward walks the segments in reverse: it recomputes the segment from
 its checkpoint while recording every pre-collision state (mlbm_step_record),
-then applies C reversed steps (mlbm_step_adjoint). Memory: (T/C + 1) + C states
+then applies C reversed steps (mlbm_steps_adjoint). Memory: (T/C + 1) + C states
 instead of T. With store_all the forward records all T + 1 states instead
 (T + 1 states of 36 bytes a node in FP32: 4.7 GB for 500 steps of 262,144
 nodes) and the backward runs the reversed steps alone, without recomputing.
@@ -98,10 +98,10 @@ class Rollout:
         lam = self.lam_T
         lam_other = plan.new_state()
         dtau = torch.zeros(1, dtype=torch.float64, device=plan.device)
+        parts = None
         if self.store:
-            for t in reversed(range(self.T)):
-                plan.step_adjoint(self.rec[t], lam, lam_other, dtau, stream=stream)
-                lam, lam_other = lam_other, lam
+            lam, _, parts = plan.steps_adjoint(self.rec, self.T, lam, lam_other, stream=stream)
+            plan.adjoint_tau(parts, dtau, stream=stream)
             gx, gy = plan.init_adjoint(self.u0[0], self.u0[1], lam, stream=stream)
             return gx, gy, dtau
         rec = torch.empty((self.C, 9, plan.n), dtype=plan.state_dtype, device=plan.device)
@@ -113,9 +113,9 @@ class Rollout:
             if L > 1:
                 plan.collide(self.ckpt[c], g, stream=stream)
                 plan.step_record(g, other, L - 1, rec[1:L], stream=stream)
-            for t in reversed(range(L)):
-                plan.step_adjoint(rec[t], lam, lam_other, dtau, stream=stream)
-                lam, lam_other = lam_other, lam
+            lam, lam_other, parts = plan.steps_adjoint(rec, L, lam, lam_other, parts,
+                                                       stream=stream)
+        plan.adjoint_tau(parts, dtau, stream=stream)
         gx, gy = plan.init_adjoint(self.u0[0], self.u0[1], lam, stream=stream)
         return gx, gy, dtau
 

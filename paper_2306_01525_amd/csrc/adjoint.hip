@@ -399,17 +399,21 @@ __global__ __launch_bounds__(256) void k_ell_fill(int n, int lw, const int32_t *
     }
 }
 
-// Workgroup sum of one double per lane (NT lanes) into part[at].
+// Workgroup sum of one double per lane (NT lanes), in a fixed order, into
+// part[at], or added to it.
 template <int NT = 256>
-__device__ __forceinline__ void block_sum_to(double v, double *part, int64_t at) {
-    __shared__ double sh[NT];
-    sh[threadIdx.x] = v;
+__device__ __forceinline__ void block_sum_to(double v, double *part, int64_t at, bool add = false) {
+    __shared__ double sh[NT / 64];
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
     __syncthreads();
-    for (int w = NT / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
+    if (threadIdx.x == 0) {
+        double a = add ? part[at] : 0.0;
+#pragma unroll
+        for (int w = 0; w < NT / 64; ++w) a += sh[w];
+        part[at] = a;
     }
-    if (threadIdx.x == 0) part[at] = sh[0];
 }
 
 __global__ __launch_bounds__(256) void k_sum_final(int64_t nparts, const double *__restrict__ part,
@@ -619,28 +623,45 @@ __global__ __launch_bounds__(1024) void k_adj_tiles(int n, int lw, int hcap, int
 // exchange their four row sums through LDS and finish the node together:
 // h = 0 reads f^n, passes its moments over and stores lambda_0..4 and the
 // tau partial, h = 1 stores lambda_5..8.
-template <class T>
-__global__ __launch_bounds__(2 * kTile) void k_adj_step(
+//
+// GR groups make a workgroup: four (a whole tile) where the tiles fill the
+// chip, one where they do not (adj_groups), each with the halo of its tile. The
+// small form (GR = 1) also takes a chunk of four triples at a time, asking for
+// the first one's weights before it waits for the halo, where the large one
+// goes triple by triple and lets its many wavefronts overlap. A step of
+// mlbm_steps_adjoint, GR = 4 -> 1 (us, FP32 / FP64, degree 4 and K = 30 where
+// not said): 1,600 nodes (K = 20) 10.2 -> 10.0 / 11.7 -> 10.7, 6,400 (K = 25)
+// 13.9 -> 12.1 / 23.7 -> 14.7, 14,400 17.7 -> 13.0 / 28.1 -> 16.1, 40,000
+// 19.1 -> 17.4 / 30.5 -> 27.3, 90,000 29.0 -> 28.3 / 55.7 -> 57.7, 262,144
+// 66 -> 82 / 132 -> 164: the small form stages four halos where the large one
+// stages one. What is left of a small step is its chain of dependent trips (row
+// bounds, units, halo, moments); loads of the moments and of the row bounds'
+// ends moved ahead of the walk measured 9.6 in FP32 and 16.4 in FP64 at 1,600.
+// A large step is bound by the traffic of the heads: 262,144 nodes FP32 read
+// about 0.42 GB in 66 us, 6.3 TB/s.
+template <class T, int GR>
+__global__ __launch_bounds__(128 * GR) void k_adj_step(
     int n, const T *__restrict__ fn, const T *__restrict__ lam_next, T *__restrict__ lam_n,
     const int32_t *__restrict__ ptr, const int32_t *__restrict__ col, const T *__restrict__ val,
     int lw, const int32_t *__restrict__ ecol, const T *__restrict__ eval,
     const int32_t *__restrict__ tdescT, const int32_t *__restrict__ ilist,
     const uint32_t *__restrict__ elocal, int hcap, double rtau, double rho0, int dev,
-    double *__restrict__ part, int32_t *err) {
+    double *__restrict__ part, int add, int32_t *err) {
+    constexpr int NTH = 128 * GR, PER = kTile / 64 / GR;   // workgroups per tile
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ T s_x[kTile / 64][2][4][64];   // row sums exchanged between the halves
-    __shared__ T s_m[kTile / 64][4][64];      // moments of f^n, from half 0 to half 1
-    __shared__ int s_hd[kTile / 64][2][64];   // head length over each half's rows
+    __shared__ T s_x[GR][2][4][64];   // row sums exchanged between the halves
+    __shared__ T s_m[GR][4][64];      // moments of f^n, from half 0 to half 1
+    __shared__ int s_hd[GR][2][64];   // head length over each half's rows
     typedef T T4 __attribute__((ext_vector_type(4)));
     typedef uint32_t U4 __attribute__((ext_vector_type(4)));
     typedef int32_t I4 __attribute__((ext_vector_type(4)));
-    const int64_t ntiles = ((int64_t)n + kTile - 1) / kTile;
-    const int64_t tt = xcd_tile(ntiles);
-    if (tt >= ntiles) return;
-    const int t = (int)tt, tid = threadIdx.x;
+    const int64_t nwg = ((int64_t)n + 64 * GR - 1) / (64 * GR);
+    const int64_t wg = xcd_tile(nwg);
+    if (wg >= nwg) return;
+    const int t = (int)(wg / PER), tid = threadIdx.x;
     const int wv = tid >> 6, lane = tid & 63;
-    const int hv = wv & 1, gq = wv >> 1;    // direction half, group within the tile
-    const int m = t * kTile + gq * 64 + lane;
+    const int hv = wv & 1, gq = wv >> 1;    // direction half, group within the workgroup
+    const int m = (int)(wg * GR + gq) * 64 + lane;
     const int ni = tdescT ? tdescT[t] : 0;
     T *L = reinterpret_cast<T *>(smem);   // [8][ni]
 
@@ -671,9 +692,41 @@ __global__ __launch_bounds__(2 * kTile) void k_adj_step(
     const int64_t grp = min(m, n - 1) >> 6;   // lanes past the last node: its group
     const int64_t gv = grp * 64 * lw, gw = grp * 64 * lw3;
     int64_t voff = 0, woff = 0;
+    // the words and weights of triples w .. w + C - 1, this lane's or zero
+    constexpr int C = GR == 1 ? 4 : 1;
+    U4 wd[C];
+    T4 v[C][3];
+    auto triples = [&](int w) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            const bool onw = 3 * (w + c) < hmax;
+            const uint64_t mw = __ballot(onw);
+            const int cw = __popcll(mw);
+            const int64_t aw = onw ? 2 * (gw + woff) + lanes_below(mw) + hv * cw : 2 * gw;
+            wd[c] = __builtin_nontemporal_load(elw + aw);
+            wd[c] = onw ? wd[c] : (U4)0;
+            woff += cw;
+#pragma unroll
+            for (int sft = 0; sft < 3; ++sft) {
+                const bool on = 3 * (w + c) + sft < hmax;
+                const uint64_t me = __ballot(on);
+                const int ce = __popcll(me);
+                const int64_t a = on ? 2 * (gv + voff) + lanes_below(me) + hv * ce : 2 * gv;
+                const T4 va = __builtin_nontemporal_load(ev + a);
+                v[c][sft] = on ? va : (T4)0;
+                voff += ce;
+            }
+        }
+    };
+    if (GR == 1 && ni > 0) {
+        __syncthreads();
+        hmax = max(hmax, s_hd[gq][1 - hv][lane]);
+        triples(0);
+    }
     if (ni > 0) {
         const int32_t *il = ilist + (int64_t)t * hcap;
-        for (int h = tid; h < ni; h += 2 * kTile) {
+#pragma unroll 4
+        for (int h = tid; h < ni; h += NTH) {
             int q = il[h];
             if ((unsigned)q >= (unsigned)n) {   // a bad table must not fault
                 q = 0;
@@ -691,32 +744,19 @@ __global__ __launch_bounds__(2 * kTile) void k_adj_step(
     const int ntrip = (wmax + 2) / 3;
     if (ni > 0) {
         const T *Lh = L + 4 * hv * ni;
-        for (int w = 0; w < ntrip; ++w) {
-            const bool onw = 3 * w < hmax;
-            const uint64_t mw = __ballot(onw);
-            const int cw = __popcll(mw);
-            const int64_t aw = onw ? 2 * (gw + woff) + lanes_below(mw) + hv * cw : 2 * gw;
-            U4 wd = __builtin_nontemporal_load(elw + aw);
-            wd = onw ? wd : (U4)0;
-            woff += cw;
-            T4 v[3];
+        for (int w = 0; w < ntrip; w += C) {
+            if (GR > 1 || w > 0) triples(w);
 #pragma unroll
-            for (int sft = 0; sft < 3; ++sft) {
-                const bool on = 3 * w + sft < hmax;
-                const uint64_t me = __ballot(on);
-                const int ce = __popcll(me);
-                const int64_t a = on ? 2 * (gv + voff) + lanes_below(me) + hv * ce : 2 * gv;
-                const T4 va = __builtin_nontemporal_load(ev + a);
-                v[sft] = on ? va : (T4)0;
-                voff += ce;
-            }
+            for (int c = 0; c < C; ++c) {
+                if (w + c >= ntrip) break;
 #pragma unroll
-            for (int sft = 0; sft < 3; ++sft) {
-                const int sh = 10 * sft;
-                acc[0] += v[sft].x * Lh[0 * ni + ((wd.x >> sh) & 1023u)];
-                acc[1] += v[sft].y * Lh[1 * ni + ((wd.y >> sh) & 1023u)];
-                acc[2] += v[sft].z * Lh[2 * ni + ((wd.z >> sh) & 1023u)];
-                acc[3] += v[sft].w * Lh[3 * ni + ((wd.w >> sh) & 1023u)];
+                for (int sft = 0; sft < 3; ++sft) {
+                    const int sh = 10 * sft;
+                    acc[0] += v[c][sft].x * Lh[0 * ni + ((wd[c].x >> sh) & 1023u)];
+                    acc[1] += v[c][sft].y * Lh[1 * ni + ((wd[c].y >> sh) & 1023u)];
+                    acc[2] += v[c][sft].z * Lh[2 * ni + ((wd[c].z >> sh) & 1023u)];
+                    acc[3] += v[c][sft].w * Lh[3 * ni + ((wd[c].w >> sh) & 1023u)];
+                }
             }
         }
     }
@@ -801,7 +841,7 @@ __global__ __launch_bounds__(2 * kTile) void k_adj_step(
                 lam_n[(int64_t)b * n + m] =
                     ((T)1 - rt) * lg[b] + rt * (A + Bx * (T)lat_ex(b) + By * (T)lat_ey(b));
     }
-    block_sum_to<2 * kTile>(dt, part, t);
+    block_sum_to<NTH>(dt, part, wg, add != 0);
 }
 
 // dJ/df_b for J = 1/2 sum |u - u*|^2: (r . (e_b - u)) / rho, r = u - u*.
@@ -950,30 +990,40 @@ hipError_t launch_loss_seed(const CloudPlan &cp, int precision, const void *fT,
     return hipGetLastError();
 }
 
+// Groups per workgroup of the reversed step. The small form is the faster one up
+// to 40,000 nodes in both precisions and the slower one in FP64 at 90,000
+// (figures at k_adj_step); 192 tiles are still less than one a CU.
+static int adj_groups(int n) { return n <= 49152 ? 1 : kTile / 64; }
+
+int64_t adjoint_parts(int n) { return blocks_for(n, 64 * adj_groups(n)); }
+
+template <class T, int GR>
+static void launch_adj(const CloudPlan &cp, int dev, const void *fn, const void *lam_next,
+                       void *lam_n, double *part, bool add, hipStream_t s) {
+    const unsigned lds = cp.adj_ni ? (unsigned)(8 * cp.adj_ni * sizeof(T)) : 0;
+    hipLaunchKernelGGL((k_adj_step<T, GR>), dim3(xcd_grid(adjoint_parts(cp.n))), dim3(128 * GR), lds,
+                       s, cp.n, (const T *)fn, (const T *)lam_next, (T *)lam_n, cp.tr_ptr, cp.tr_col,
+                       (const T *)cp.tr_val, cp.tr_lw, cp.ell_col, (const T *)cp.ell_val,
+                       cp.adj_ni ? cp.tdescT : nullptr, cp.ilist, cp.elocal, cp.hcap,
+                       1.0 / cp.prm.tau, cp.prm.rho0, dev, part, add ? 1 : 0, cp.err);
+}
+
 hipError_t launch_step_adjoint(const CloudPlan &cp, int precision, const void *fn,
-                               const void *lam_next, void *lam_n, double *dtau, double *part,
+                               const void *lam_next, void *lam_n, double *part, bool add,
                                hipStream_t s) {
-    const int n = cp.n;
-    const int64_t nb = blocks_for(n, 256);
-    const double rtau = 1.0 / cp.prm.tau;
-    const size_t esz = precision == MLBM_FP64 ? sizeof(double) : sizeof(float);
-    const unsigned lds = cp.adj_ni ? (unsigned)(8 * cp.adj_ni * esz) : 0;
-    const int32_t *td = cp.adj_ni ? cp.tdescT : nullptr;
+    const bool whole = adj_groups(cp.n) == kTile / 64;
     if (precision == MLBM_FP64)
-        hipLaunchKernelGGL(k_adj_step<double>, dim3(xcd_grid(nb)), dim3(2 * kTile), lds, s, n,
-                           (const double *)fn, (const double *)lam_next, (double *)lam_n,
-                           cp.tr_ptr, cp.tr_col, (const double *)cp.tr_val, cp.tr_lw,
-                           cp.ell_col, (const double *)cp.ell_val, td, cp.ilist, cp.elocal,
-                           cp.hcap, rtau, cp.prm.rho0, 0, part, cp.err);
+        whole ? launch_adj<double, kTile / 64>(cp, 0, fn, lam_next, lam_n, part, add, s)
+              : launch_adj<double, 1>(cp, 0, fn, lam_next, lam_n, part, add, s);
     else
-        hipLaunchKernelGGL(k_adj_step<float>, dim3(xcd_grid(nb)), dim3(2 * kTile), lds, s, n,
-                           (const float *)fn, (const float *)lam_next, (float *)lam_n,
-                           cp.tr_ptr, cp.tr_col, (const float *)cp.tr_val, cp.tr_lw,
-                           cp.ell_col, (const float *)cp.ell_val, td, cp.ilist, cp.elocal,
-                           cp.hcap, rtau, cp.prm.rho0, 1, part, cp.err);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(256), 0, s, nb, (const double *)part, dtau, 1);
+        whole ? launch_adj<float, kTile / 64>(cp, 1, fn, lam_next, lam_n, part, add, s)
+              : launch_adj<float, 1>(cp, 1, fn, lam_next, lam_n, part, add, s);
+    return hipGetLastError();
+}
+
+hipError_t launch_adjoint_tau(const CloudPlan &cp, const double *part, double *dtau,
+                              hipStream_t s) {
+    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(256), 0, s, adjoint_parts(cp.n), part, dtau, 1);
     return hipGetLastError();
 }
 

@@ -1178,15 +1178,59 @@ mlbm_status mlbm_loss_seed(const mlbm_plan *plan, const void *f_T, const double 
     return MLBM_OK;
 }
 
+namespace {
+mlbm_status check_adjoint(const CloudPlan *cp, const mlbm_plan *plan) {
+    if (cp && plan->c.size() != 1) return fail(MLBM_EUNSUPPORTED, "the adjoint needs a single-cloud plan");
+    if (!cp) return fail(MLBM_EINVAL, "null argument");
+    if (!cp->tr_ptr) return fail(MLBM_EINVAL, "plan was built without with_adjoint");
+    return MLBM_OK;
+}
+}  // namespace
+
 mlbm_status mlbm_step_adjoint(const mlbm_plan *plan, const void *f_n, const void *lamf_next,
                               void *lamf_n, double *dJ_dtau, hipStream_t s) {
     const CloudPlan *cp = single(plan);
     if (cp && plan->c.size() != 1) return fail(MLBM_EUNSUPPORTED, "the adjoint needs a single-cloud plan");
     if (!cp || !f_n || !lamf_next || !lamf_n || !dJ_dtau) return fail(MLBM_EINVAL, "null argument");
-    if (!cp->tr_ptr) return fail(MLBM_EINVAL, "plan was built without with_adjoint");
+    mlbm_status st = check_adjoint(cp, plan);
+    if (st != MLBM_OK) return st;
     if (lamf_next == lamf_n) return fail(MLBM_EINVAL, "adjoint buffers must differ");
-    MLBM_HIP(launch_step_adjoint(*cp, plan->precision, f_n, lamf_next, lamf_n, dJ_dtau,
-                                 plan->scratch64, s));
+    MLBM_HIP(launch_step_adjoint(*cp, plan->precision, f_n, lamf_next, lamf_n, plan->scratch64, false, s));
+    MLBM_HIP(launch_adjoint_tau(*cp, plan->scratch64, dJ_dtau, s));
+    return MLBM_OK;
+}
+
+int64_t mlbm_adjoint_parts(const mlbm_plan *plan) {
+    const CloudPlan *cp = single(plan);
+    return cp && check_adjoint(cp, plan) == MLBM_OK ? adjoint_parts(cp->n) : 0;
+}
+
+mlbm_status mlbm_steps_adjoint(const mlbm_plan *plan, const void *f_rec, int32_t n_steps,
+                               void *lamf_a, void *lamf_b, double *parts, int32_t first,
+                               int32_t *result_in_b, hipStream_t s) {
+    const CloudPlan *cp = single(plan);
+    mlbm_status st = check_adjoint(cp, plan);
+    if (st != MLBM_OK) return st;
+    if (!f_rec || !lamf_a || !lamf_b || !parts || n_steps < 0) return fail(MLBM_EINVAL, "null argument");
+    if (lamf_a == lamf_b) return fail(MLBM_EINVAL, "adjoint buffers must differ");
+    const size_t sb = (size_t)kQ * plan->n_total * state_elem_bytes(plan->precision);
+    void *cur = lamf_a, *nxt = lamf_b;
+    for (int32_t t = n_steps - 1; t >= 0; --t) {
+        MLBM_HIP(launch_step_adjoint(*cp, plan->precision, (const char *)f_rec + sb * t, cur, nxt,
+                                     parts, !(first && t == n_steps - 1), s));
+        std::swap(cur, nxt);
+    }
+    if (result_in_b) *result_in_b = n_steps & 1;
+    return MLBM_OK;
+}
+
+mlbm_status mlbm_adjoint_tau(const mlbm_plan *plan, const double *parts, double *dJ_dtau,
+                             hipStream_t s) {
+    const CloudPlan *cp = single(plan);
+    mlbm_status st = check_adjoint(cp, plan);
+    if (st != MLBM_OK) return st;
+    if (!parts || !dJ_dtau) return fail(MLBM_EINVAL, "null argument");
+    MLBM_HIP(launch_adjoint_tau(*cp, parts, dJ_dtau, s));
     return MLBM_OK;
 }
 

@@ -367,6 +367,26 @@ class Plan:
                                             _ptr(dtau), _stream(stream)))
         return lam_n
 
+    def steps_adjoint(self, f_rec, n_steps, lam_a, lam_b, parts=None, stream=None):
+        """n_steps reversed steps through the recorded f_rec[n_steps - 1] .. f_rec[0].
+        Returns (lam, other, parts): lam (lam_a or lam_b) the adjoint before the first
+        of them, parts the partial sums of dJ/dtau, which further calls add to."""
+        first = parts is None
+        if first:
+            parts = torch.empty(_lib.load().mlbm_adjoint_parts(self._h), dtype=torch.float64,
+                                device=self.device)
+            _order(stream, parts)
+        rb = ctypes.c_int32()
+        check(_lib.load().mlbm_steps_adjoint(self._h, _ptr(f_rec), int(n_steps), _ptr(lam_a),
+                                             _ptr(lam_b), _ptr(parts), int(first),
+                                             ctypes.byref(rb), _stream(stream)))
+        return (lam_b, lam_a, parts) if rb.value else (lam_a, lam_b, parts)
+
+    def adjoint_tau(self, parts, dtau, stream=None):
+        """Add the sum of the parts of steps_adjoint into dtau."""
+        check(_lib.load().mlbm_adjoint_tau(self._h, _ptr(parts), _ptr(dtau), _stream(stream)))
+        return dtau
+
     def init_adjoint(self, u0x, u0y, lam0, stream=None):
         gx = torch.empty(self.n, dtype=torch.float64, device=self.device)
         gy = torch.empty_like(gx)

@@ -212,3 +212,61 @@ def test_adjoint_sweep_against_oracle(case, precision):
     assert abs(gt - gt_o) <= tol * abs(gt_o)
     assert plan.device_error() == 0
     plan.close()
+
+
+# (nodes a row, rows, K, degree, mode): whole, partly filled and missing groups of
+# 64 nodes in the last tile; seven, four and eleven triples of row entries; and a
+# size on each side of the line between the small and the large workgroups
+REVERSED_CASES = [(8, 8, 20, 3, 0), (9, 13, 12, 2, 1), (16, 17, 20, 3, 0), (33, 31, 30, 4, 0),
+                  (221, 222, 12, 2, 0), (222, 222, 12, 2, 0)]
+
+
+@pytest.mark.parametrize("case", REVERSED_CASES, ids=["%dx%d-K%d-mode%d" % (
+    c[0], c[1], c[2], c[4]) for c in REVERSED_CASES])
+@pytest.mark.parametrize("precision", [1, 0])
+def test_several_reversed_steps_equal_single_ones_and_oracle(case, precision):
+    """steps_adjoint, in one call and cut in two, gives the adjoint of single
+    reversed steps bit for bit, whose sums of dJ/dtau it takes in another order:
+    at most some 40 roundings of 1.1e-16 deep, with terms up to a hundred times
+    the partial sums, 1e-12 of these. The gradient meets the oracle's within the
+    bounds of the imported-weights test; so does dJ/dtau in FP64, while in FP32 it
+    is a difference of populations that shrinks with the spacing over the
+    wavelength and has no bound of that kind (49,062 nodes: 1.9e-5)."""
+    from paper_2306_01525_amd import Params, Plan
+    nx, ny, K, m, mode = case
+    c = jittered_lattice(nx, seed=nx, length=float(nx), ny=ny, length_y=float(ny))
+    u0x, u0y = tgv_initial_velocity(c.x, c.y, float(nx), 0.02)
+    tx, ty = tgv_initial_velocity(c.x, c.y, float(nx), 0.015)
+    tau, steps = 0.7, 3
+    nbr, own, W = oracle.build_plan(c, 1.0, K, m, mode)
+    p = Params(dx=1.0, K=K, degree=m, tau=tau, stencil_mode=mode, precision=precision,
+               with_adjoint=1)
+    plan = Plan.from_arrays(c.x, c.y, nbr, own, W, p)
+    rec = torch.empty((steps + 1, 9, c.n), dtype=plan.state_dtype, device="cuda")
+    plan.init_f(u0x, u0y, f=rec[0])
+    plan.step_record(plan.collide(rec[0]), plan.new_state(), steps, rec[1:])
+    seed, _ = plan.loss_seed(rec[steps], tx, ty)
+    dtau = torch.zeros(1, dtype=torch.float64, device="cuda")
+    lam, other = seed.clone(), torch.empty_like(seed)
+    for t in reversed(range(steps)):
+        plan.step_adjoint(rec[t], lam, other, dtau)
+        lam, other = other, lam
+    one, _, parts = plan.steps_adjoint(rec, steps, seed.clone(), torch.empty_like(seed))
+    a, b, cut = plan.steps_adjoint(rec[1:], steps - 1, seed.clone(), torch.empty_like(seed))
+    a, b, cut = plan.steps_adjoint(rec, 1, a, b, cut)
+    assert torch.equal(one, lam) and torch.equal(a, lam)
+    assert torch.equal(parts, cut)
+    total = plan.adjoint_tau(parts, torch.zeros_like(dtau))
+    scale = float(parts.abs().sum())
+    say("reversed %s prec %d: dtau %.15e, single steps %.15e" % (case, precision, float(total),
+                                                              float(dtau)))
+    assert abs(float(total) - float(dtau)) <= 1e-12 * scale
+    _, gx_o, gy_o, gt_o = oracle.adjoint(nbr, own, W, tau, steps, 1.0, u0x, u0y, tx, ty)
+    gx, gy = plan.init_adjoint(u0x, u0y, a)
+    tol = 1e-10 if precision == 1 else 2e-6
+    eg = rel_l2(np.concatenate([gx.cpu().numpy(), gy.cpu().numpy()]),
+                np.concatenate([gx_o, gy_o]))
+    assert eg < tol
+    if precision == 1:
+        assert abs(float(total) - gt_o) <= tol * abs(gt_o)
+    plan.close()
