@@ -11,7 +11,7 @@
 // the partition-of-unity correction, or FP64).
 #include <climits>
 
-#include "common.h"
+#include "index_set.h"
 
 namespace mlbm {
 namespace {
@@ -449,42 +449,11 @@ __device__ __forceinline__ void moments_of(const T *f, int n, int p, int dev, do
 
 // Inverse halo of a tile of source nodes: every arriving node that the head
 // (first lw entries) of the transposed rows of the tile's nodes reads, sorted
-// (LDS hash set, then a bitonic network), capped at cap. The slot-major
+// (IndexSet), capped at cap. The slot-major
 // columns of those rows are rewritten as positions in that set, three 10-bit
 // fields per word: word w of row k of node m (compacted like the heads, over
 // triples of slots) holds slots 3w, 3w+1, 3w+2; fields past the end of the
 // row are 0.
-constexpr int kAHash = 4096;
-
-__device__ void bitonic_sort_a(int *a, int npow2) {
-    for (int k = 2; k <= npow2; k <<= 1) {
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            for (int i = threadIdx.x; i < npow2; i += blockDim.x) {
-                const int ixj = i ^ j;
-                if (ixj > i) {
-                    const bool up = (i & k) == 0;
-                    const int ai = a[i], aj = a[ixj];
-                    if ((ai > aj) == up) {
-                        a[i] = aj;
-                        a[ixj] = ai;
-                    }
-                }
-            }
-            __syncthreads();
-        }
-    }
-}
-
-__device__ __forceinline__ int lower_bound_a(const int *a, int len, int v) {
-    int lo = 0, hi = len;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (a[mid] < v) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
-
 __global__ __launch_bounds__(1024) void k_adj_tiles(int n, int lw, int hcap, int cap,
                                                     const int32_t *__restrict__ ptr,
                                                     const int32_t *__restrict__ col,
@@ -493,18 +462,11 @@ __global__ __launch_bounds__(1024) void k_adj_tiles(int n, int lw, int hcap, int
                                                     int32_t *__restrict__ ilist,
                                                     uint32_t *__restrict__ elocal,
                                                     int32_t *__restrict__ stats) {
-    __shared__ int hset[kAHash];
-    __shared__ int hsorted[kAHash];
-    __shared__ int s_n, s_over, s_fill;
+    __shared__ IndexSet set;
     const int t = blockIdx.x, tid = threadIdx.x;
     const int base = t * kTile, cnt = min(kTile, n - base);
     const int lw3 = (lw + 2) / 3;
-    for (int i = tid; i < kAHash; i += blockDim.x) hset[i] = -1;
-    if (tid == 0) {
-        s_n = 0;
-        s_over = 0;
-        s_fill = 0;
-    }
+    set.clear();
     __syncthreads();
     for (int e = tid; e < 8 * cnt * lw; e += blockDim.x) {
         const int k0 = e / (cnt * lw), r = e - k0 * cnt * lw;
@@ -513,33 +475,15 @@ __global__ __launch_bounds__(1024) void k_adj_tiles(int n, int lw, int hcap, int
         const int64_t row = (int64_t)k0 * n + m;
         if (sl >= ptr[row + 1] - ptr[row]) continue;
         const int q = col[ptr[row] + sl];
-        uint32_t h = ((uint32_t)q * 2654435761u) >> 20;
-        for (int probe = 0; probe < kAHash; ++probe) {
-            const int old = atomicCAS(&hset[h], -1, q);
-            if (old == -1) {
-                atomicAdd(&s_n, 1);
-                break;
-            }
-            if (old == q) break;
-            h = (h + 1) & (kAHash - 1);
-            if (probe == kAHash - 1) atomicOr(&s_over, 1);
-        }
+        set.add(q);
     }
     __syncthreads();
-    const int ni = s_n;
-    const bool fits = !s_over && ni <= cap && cap <= hcap && cap <= 1024;
+    set.count();
+    const int ni = set.members;
+    const bool fits = !set.over && ni <= cap && cap <= hcap && cap <= 1024;
     if (fits) {
-        for (int i = tid; i < kAHash; i += blockDim.x) hsorted[i] = INT_MAX;
+        set.order(ilist + (int64_t)t * hcap);
         __syncthreads();
-        for (int i = tid; i < kAHash; i += blockDim.x) {
-            const int v = hset[i];
-            if (v != -1) hsorted[atomicAdd(&s_fill, 1)] = v;
-        }
-        __syncthreads();
-        int np2 = 1;
-        while (np2 < ni) np2 <<= 1;
-        bitonic_sort_a(hsorted, np2);
-        for (int h = tid; h < ni; h += blockDim.x) ilist[(int64_t)t * hcap + h] = hsorted[h];
         // local columns, one lane per node of the tile (the first four
         // wavefronts, one per group of 64 nodes): the columns come from the
         // compacted heads, slot by slot (contiguous over the lanes; the rows
@@ -581,9 +525,9 @@ __global__ __launch_bounds__(1024) void k_adj_tiles(int n, int lw, int hcap, int
 #pragma unroll
                         for (int k = 0; k < 4; ++k) {
                             if (sl < len[k])
-                                wa[k] |= (uint32_t)lower_bound_a(hsorted, ni, ca[k]) << (10 * sft);
+                                wa[k] |= (uint32_t)set.find(ca[k]) << (10 * sft);
                             if (sl < len[k + 4])
-                                wb[k] |= (uint32_t)lower_bound_a(hsorted, ni, cb[k]) << (10 * sft);
+                                wb[k] |= (uint32_t)set.find(cb[k]) << (10 * sft);
                         }
                     }
                     voff += cs;

@@ -193,6 +193,58 @@ def test_tile_tables_are_consistent(mode):
     plan.close()
 
 
+@pytest.mark.parametrize("mode,no,nh", [(1, 256, 13), (1, 256, 1024), (1, 256, 1025),
+                                        (1, 256, 3072), (0, 1, 12), (0, 512, 1024),
+                                        (0, 513, 700), (0, 2048, 700)])
+def test_tile_tables_of_scattered_stencils(mode, no, nh):
+    """The gather tables where no two owners or members are near one another in
+    the node order, at the sizes around the tables' capacities (512 owners, 1,024
+    members: beyond them the tile is marked for the global path), against numpy's
+    sorted unique sets. Whole numbers: equal."""
+    from paper_2306_01525_amd import Params, Plan
+    K, T = 12, 256
+    n = 3072 * 40 + 13                       # members 40 apart: a word of 32 holds one
+    rng = np.random.default_rng(nh)
+    pool = rng.permutation(np.arange(3072) * 40 + 7)[:nh]
+    opool = rng.permutation(np.arange(2048) * 60 + 11)[:no]
+    nbr = np.empty((n, K), dtype=np.int32)
+    if mode == 0:
+        nbr[:] = pool[0]
+        nbr[opool] = pool[(np.arange(no)[:, None] * K + np.arange(K)) % nh]
+        at = (np.arange(n) % T)[:, None] + T * np.arange(-1, 8)[None, :]
+        owner = opool[at % no]               # a tile's 2,048 candidates go round the pool
+        owner[:, 0] = np.arange(n)
+    else:
+        nbr[:] = pool[((np.arange(n) % T)[:, None] * K + np.arange(K)) % nh]
+        owner = np.repeat(np.arange(n)[:, None], 9, axis=1)
+    owner = owner.astype(np.int32)
+    x = np.arange(n, dtype=np.float64)
+    plan = Plan.from_arrays(x, x, nbr, owner, np.zeros((n, 9, K)),
+                            Params(dx=1.0, K=K, degree=2, tau=0.8, stencil_mode=mode))
+    td, hl, words = plan.export("tdesc"), plan.export("hlist"), plan.export("nbrL")
+    nl = np.stack([(words >> (10 * s_)) & 1023 for s_ in range(3)], axis=-1)
+    nl = nl.reshape(words.shape[0], words.shape[1], -1)[:, :, :K]
+    ol = plan.export("ownerL") if mode == 0 else None
+    plan.close()
+    fit = 0
+    for t in list(range(0, td.shape[0], 97)) + [td.shape[0] - 1]:
+        base, cnt = t * T, min(T, n - t * T)
+        O = np.unique(owner[base:base + cnt, 1:])
+        H = np.unique(nbr[O])
+        assert td[t, 0] == O.size
+        if O.size > 512 or H.size > 1024:
+            assert td[t, 1] == 0
+            continue
+        fit += 1
+        assert td[t, 1] == H.size
+        np.testing.assert_array_equal(hl[t, :H.size], H)
+        np.testing.assert_array_equal(H[nl[t, :O.size]], nbr[O])
+        if mode == 0:
+            np.testing.assert_array_equal(O[ol[:, base:base + cnt].T], owner[base:base + cnt, 1:])
+    say("mode", mode, "owners", no, "members", nh, "tiles with tables", fit)
+    assert fit >= 1     # the last tile holds 13 nodes and always fits
+
+
 def _uncompact(units, hd, lw, n, fill):
     """Row heads compacted per group of 64 nodes ([units][8]: group g from
     unit 64 g lw, slot e a block of the group's nodes with hd > e in node
