@@ -192,45 +192,36 @@ void layout_common(Carve &pl, mlbm_plan &plan, int64_t n_total, int n_clouds = 1
         pl.take<double>(16 + 4 * (size_t)n_clouds + (size_t)blocks_for(n_total, 256) * 4);
 }
 
-// Error words to "none": no singular node, no flags, no reported node.
-hipError_t reset_errors(mlbm_plan *plan, hipStream_t s) {
-    hipError_t e = launch_fill_i32(plan->dev_err, INT_MAX, 3, s);
-    if (e == hipSuccess) e = launch_fill_i32(plan->dev_err + kErrFlags, 0, 1, s);
-    return e;
-}
-
 bool capturing(hipStream_t s) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &st) != hipSuccess) return false;
     return st != hipStreamCaptureStatusNone;
 }
 
-mlbm_status check_singular(mlbm_plan *plan, hipStream_t s) {
-    if (capturing(s)) return MLBM_OK;
-    MLBM_HIP(hipStreamSynchronize(s));
-    int32_t v = 0;
-    MLBM_HIP(hipMemcpy(&v, plan->dev_err, sizeof(v), hipMemcpyDeviceToHost));
-    if (v != INT_MAX)
+mlbm_status check_singular(int32_t first) {
+    if (first != INT_MAX)
         return fail(MLBM_ESINGULAR, "local RBF system is numerically singular at node " +
-                                        std::to_string(v - 1) + " (user index)");
+                                        std::to_string(first - 1) + " (user index)");
     return MLBM_OK;
 }
 
 // Gather tables of the LDS-staged step and of the adjoint. Their kernels
 // record per cloud (stats + kStats * cloud): [0] the largest LDS need of a
 // step tile, [1] step tiles without tables, [2] the largest inverse halo,
-// [3] adjoint tiles without one, [4] the largest halo of a step tile. The tables are enqueued for every cloud
-// first; finish_tables then reads all the records at once (one
-// synchronisation), or, while the stream is being captured, takes the
-// capacity bounds instead.
+// [3] adjoint tiles without one, [4] the largest halo of a step tile. The
+// tables are enqueued for every cloud first; finish_tables then reads all the
+// records and the first singular node (INT_MAX: none) in one copy behind the
+// build, or, while the stream is being captured, takes the capacity bounds
+// instead.
 mlbm_status enqueue_tables(CloudPlan &cp, int32_t *stats, hipStream_t s) {
     if (cp.tdescT) MLBM_HIP(launch_adj_tiles(cp, stats + 2, s));
     if (cp.tdesc) MLBM_HIP(launch_tiles(cp, stats, s));
     return MLBM_OK;
 }
 
-mlbm_status finish_tables(mlbm_plan *plan, hipStream_t s) {
+mlbm_status finish_tables(mlbm_plan *plan, int32_t *singular, hipStream_t s) {
     const size_t nc = plan->c.size();
+    *singular = INT_MAX;
     if (capturing(s)) {
         for (CloudPlan &cp : plan->c) {
             if (cp.tdesc) {
@@ -249,9 +240,13 @@ mlbm_status finish_tables(mlbm_plan *plan, hipStream_t s) {
         }
         return MLBM_OK;
     }
-    std::vector<int32_t> h(kStats * nc);
-    MLBM_HIP(hipStreamSynchronize(s));
-    MLBM_HIP(hipMemcpy(h.data(), plan->stats, sizeof(int32_t) * h.size(), hipMemcpyDeviceToHost));
+    // the error words come right before the records (layout_common)
+    const size_t head = plan->stats - plan->dev_err;
+    std::vector<int32_t> words(head + kStats * nc);
+    MLBM_HIP(hipMemcpyWithStream(words.data(), plan->dev_err, sizeof(int32_t) * words.size(),
+                                 hipMemcpyDeviceToHost, s));
+    *singular = words[kErrSingular];
+    const int32_t *h = words.data() + head;
     for (size_t c = 0; c < nc; ++c) {
         CloudPlan &cp = plan->c[c];
         if (cp.tdesc) {
@@ -416,21 +411,16 @@ void layout_plan(const mlbm_cloud *clouds, const mlbm_params *params, int32_t n_
 mlbm_status build_cloud(mlbm_plan *plan, CloudPlan &cp, const mlbm_cloud &c,
                         const mlbm_params &p, BuildWs &bw, int32_t *stats, hipStream_t s) {
     const int n = c.n;
-    if (c.period_x > 0 && c.period_y > 0)
-        MLBM_HIP(launch_geo_periodic(cp.geo, c.period_x, c.period_y, bw.gx, bw.gy, bw.hb, s));
-    else
-        MLBM_HIP(launch_geo_bbox(cp.geo, c.x, c.y, n, bw.gx, bw.gy, bw.hb, s));
-    MLBM_HIP(launch_keys(cp.geo, c.x, c.y, n, bw.keys, bw.vals, s));
-    MLBM_HIP(sort_pairs(bw.sort_tmp, bw.sort_bytes, bw.keys, bw.skeys, bw.vals, cp.perm, n,
-                        std::max(1, 2 * bw.hb), s));
-    MLBM_HIP(launch_scatter_sorted(cp.geo, c.x, c.y, c.node_type, cp.perm, bw.skeys, n, cp.xs,
-                                   cp.ys, cp.ntype, cp.iperm, bw.cstart, bw.cend, bw.gx * bw.gy, s));
-    // (the solver's workspace is not in use yet: its head takes the search's list)
+    MLBM_HIP(launch_order({n, bw.gx, bw.gy, bw.hb, c.period_x, c.period_y, c.x, c.y, c.node_type,
+                           cp.geo, bw.keys, bw.skeys, bw.vals, bw.cstart, bw.cend, bw.sort_tmp,
+                           bw.rbf_tmp, bw.sort_bytes, bw.rbf_bytes, cp.perm, cp.iperm, cp.xs, cp.ys,
+                           cp.ntype}, s));
     MLBM_HIP(launch_knn(cp.geo, cp.xs, cp.ys, cp.perm, cp.iperm, bw.cstart, bw.cend, n, p.K,
-                        (int32_t *)bw.rbf_tmp, cp.nbr, s));
+                        bw.rbf_tmp, bw.rbf_bytes, cp.nbr, s));
+    // (the shape vectors are not solved yet: their place takes the points' slots)
     if (p.stencil_mode == MLBM_STENCIL_PAPER)
         MLBM_HIP(launch_owner(cp.geo, cp.xs, cp.ys, cp.perm, bw.cstart, bw.cend, n, p.dx, cp.owner,
-                              s));
+                              bw.rbf_tmp, bw.rbf_bytes, (int32_t *)cp.W64, s));
     MLBM_HIP(launch_rbf(cp.geo, cp.xs, cp.ys, cp.perm, cp.nbr, cp.owner, n, p.K, p.degree, p.dx,
                         p.stencil_mode, bw.rbf_tmp, bw.rbf_bytes, cp.W64, plan->dev_err, s));
     if (cp.W32) MLBM_HIP(launch_pack_w32(cp.W64, n, p.K, cp.W32, s));
@@ -609,16 +599,16 @@ mlbm_status build_weights_lanes(const mlbm_cloud *clouds, const mlbm_params *par
         delete plan;
         return r;
     };
-    hipError_t e = reset_errors(plan, s);
-    if (e == hipSuccess) e = launch_fill_i32(plan->stats, 0, (int64_t)kStats * n_clouds, s);
-    if (e != hipSuccess) return cleanup(hip_fail(e, "launch_fill_i32"));
+    hipError_t e = launch_reset(plan->dev_err, plan->stats, kStats * n_clouds, s);
+    if (e != hipSuccess) return cleanup(hip_fail(e, "launch_reset"));
     st = build_clouds(plan, clouds, params, L, s);
     if (st != MLBM_OK) return cleanup(st);
-    st = finish_tables(plan, s);
+    int32_t singular;
+    st = finish_tables(plan, &singular, s);
     if (st != MLBM_OK) return cleanup(st);
     st = build_batch(plan, s);
     if (st != MLBM_OK) return cleanup(st);
-    st = check_singular(plan, s);
+    st = check_singular(singular);
     if (st != MLBM_OK) return cleanup(st);
     *out = plan;
     return MLBM_OK;
@@ -749,7 +739,7 @@ mlbm_status mlbm_import_weights(int32_t n, const double *x, const double *y,
     STEP(launch_force(cp.xs, cp.ys, cp.ntype, n, p.force_kind, p.force_mag, cp.force32,
                       cp.force64, s));
     cp.err = plan->dev_err;
-    STEP(reset_errors(plan, s));
+    STEP(launch_reset(plan->dev_err, plan->stats, kStats, s));
     if (p.with_adjoint) {
         // This path has no workspace argument, so the transposed operator is
         // assembled on the host (rows filled in ascending arriving node, which
@@ -797,12 +787,12 @@ mlbm_status mlbm_import_weights(int32_t n, const double *x, const double *y,
             STEP(hipMemcpyAsync(cp.tr_val, v32.data(), sizeof(float) * nnz, hipMemcpyHostToDevice, s));
         STEP(launch_ell_fill(cp, p.precision, s));
     }
-    STEP(launch_fill_i32(plan->stats, 0, kStats, s));
 #undef STEP
     st = enqueue_tables(cp, plan->stats, s);
     if (st != MLBM_OK) return cleanup(st);
     plan->c.push_back(cp);
-    st = finish_tables(plan, s);
+    int32_t singular;
+    st = finish_tables(plan, &singular, s);
     if (st != MLBM_OK) return cleanup(st);
     *out = plan;
     return MLBM_OK;
@@ -972,7 +962,7 @@ mlbm_status mlbm_device_error_nodes(const mlbm_plan *plan, int32_t *singular_nod
 
 mlbm_status mlbm_device_error_clear(mlbm_plan *plan, hipStream_t s) {
     if (!plan || !plan->dev_err) return fail(MLBM_EINVAL, "null plan");
-    MLBM_HIP(reset_errors(plan, s));
+    MLBM_HIP(launch_reset(plan->dev_err, nullptr, 0, s));
     return MLBM_OK;
 }
 

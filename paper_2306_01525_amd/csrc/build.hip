@@ -67,21 +67,6 @@ __device__ __forceinline__ void cell_of(const Geo &g, double x, double y, int &c
     cy = fy < 0 ? 0 : (fy >= g.gy ? g.gy - 1 : (int)fy);
 }
 
-__global__ void k_geo_periodic(Geo *geo, double Lx, double Ly, int gx, int gy, int hb) {
-    Geo g;
-    g.x0 = 0.0;
-    g.y0 = 0.0;
-    g.cw = Lx / gx;
-    g.ch = Ly / gy;
-    g.Lx = Lx;
-    g.Ly = Ly;
-    g.gx = gx;
-    g.gy = gy;
-    g.hb = hb;
-    g.pad = 0;
-    *geo = g;
-}
-
 // Bounding box of an open cloud (one workgroup).
 __global__ __launch_bounds__(1024) void k_geo_bbox(Geo *geo, const double *x, const double *y,
                                                    int n, int gx, int gy, int hb) {
@@ -127,38 +112,91 @@ __global__ __launch_bounds__(1024) void k_geo_bbox(Geo *geo, const double *x, co
     }
 }
 
-__global__ void k_keys(const Geo *__restrict__ geo, const double *__restrict__ x,
-                       const double *__restrict__ y, int n, uint32_t *keys, int32_t *vals) {
+// First kernel of a cloud's build: the cells and the counters empty, and the
+// geometry of a periodic cloud, whose values the host knows.
+__global__ __launch_bounds__(256) void k_begin(Geo *geo, Geo periodic, int ncells, int32_t *cstart,
+                                               int32_t *cend, int nkeys, int32_t *cnt) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < ncells) cstart[i] = cend[i] = 0;
+    if (i < nkeys) cnt[i] = 0;
+    if (i == 0 && periodic.Lx > 0.0) *geo = periodic;
+}
+
+// Hilbert key of every node's cell. With counters a node also takes the next
+// place in its key (vals[u]), without them vals[u] = u.
+__global__ __launch_bounds__(256) void k_keys(const Geo *__restrict__ geo,
+                                              const double *__restrict__ x,
+                                              const double *__restrict__ y, int n, uint32_t *keys,
+                                              int32_t *vals, int32_t *cnt) {
     int u = blockIdx.x * blockDim.x + threadIdx.x;
     if (u >= n) return;
     Geo g = *geo;
     int cx, cy;
     cell_of(g, x[u], y[u], cx, cy);
-    keys[u] = hilbert_index((uint32_t)cx, (uint32_t)cy, g.hb);
-    vals[u] = u;
+    const uint32_t k = hilbert_index((uint32_t)cx, (uint32_t)cy, g.hb);
+    keys[u] = k;
+    vals[u] = cnt ? atomicAdd(&cnt[k], 1) : u;
 }
 
-__global__ void k_scatter_sorted(const Geo *__restrict__ geo, const double *__restrict__ x,
-                                 const double *__restrict__ y, const uint8_t *__restrict__ nt,
-                                 const int32_t *__restrict__ perm,
-                                 const uint32_t *__restrict__ skeys, int n, double *xs,
-                                 double *ys, uint8_t *ntype, int32_t *iperm, int32_t *cstart,
-                                 int32_t *cend) {
-    int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    Geo g = *geo;
-    int u = perm[p];
-    double px = x[u], py = y[u];
+// Counting sort: the nodes of key k, in no order, at off[k] and up.
+__global__ __launch_bounds__(256) void k_place(int n, const uint32_t *__restrict__ keys,
+                                               const int32_t *__restrict__ vals,
+                                               const int32_t *__restrict__ off,
+                                               int32_t *__restrict__ placed) {
+    const int u = blockIdx.x * blockDim.x + threadIdx.x;
+    if (u < n) placed[off[keys[u]] + vals[u]] = u;
+}
+
+// Nodes in internal order: by key, nodes of one key by user index. COUNTED: the
+// order is found here from the placed nodes and the keys' offsets, a node's rank
+// in its key being the number of smaller user indices there (two nodes a cell on
+// average; the stencil search scans the same cells). Otherwise perm and the
+// sorted keys hold it. Also empties the owner lists' counters and the search's
+// list (redo).
+template <bool COUNTED>
+__global__ __launch_bounds__(256) void k_scatter_sorted(
+    const Geo *__restrict__ geo, const double *__restrict__ x, const double *__restrict__ y,
+    const uint8_t *__restrict__ nt, int32_t *__restrict__ perm, const uint32_t *__restrict__ keys,
+    const int32_t *__restrict__ placed, const int32_t *__restrict__ off, int nkeys, int n, double *xs,
+    double *ys, uint8_t *ntype, int32_t *iperm, int32_t *cstart, int32_t *cend, int32_t *owned,
+    int32_t *redo) {
+    const int t = blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n) return;
+    owned[t] = 0;
+    if (t == 0) redo[0] = 0;
+    const Geo g = *geo;
+    const int u = COUNTED ? placed[t] : perm[t];
+    const double px = x[u], py = y[u];
+    int cx, cy;
+    cell_of(g, px, py, cx, cy);
+    const int c = cy * g.gx + cx;
+    int p = t;
+    if (COUNTED) {
+        const uint32_t k = keys[u];   // by user index
+        const int b = off[k], e = (int)k + 1 < nkeys ? off[k + 1] : n;
+        p = b;
+        for (int q = b; q < e; ++q) p += placed[q] < u ? 1 : 0;
+        perm[p] = u;
+        if (t == b) {
+            cstart[c] = b;
+            cend[c] = e;
+        }
+    } else {
+        const uint32_t k = keys[p];   // sorted
+        if (p == 0 || keys[p - 1] != k) cstart[c] = p;
+        if (p == n - 1 || keys[p + 1] != k) cend[c] = p + 1;
+    }
     xs[p] = px;
     ys[p] = py;
     ntype[p] = nt ? nt[u] : (uint8_t)0;
     iperm[u] = p;
-    int cx, cy;
-    cell_of(g, px, py, cx, cy);
-    int c = cy * g.gx + cx;
-    uint32_t k = skeys[p];
-    if (p == 0 || skeys[p - 1] != k) cstart[c] = p;
-    if (p == n - 1 || skeys[p + 1] != k) cend[c] = p + 1;
+}
+
+// Error words to "none" (no singular node, no flags, no reported node), records to 0.
+__global__ __launch_bounds__(256) void k_reset(int32_t *err, int32_t *stats, int nstats) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < 3) err[i] = i == kErrFlags ? 0 : INT_MAX;
+    if (i < nstats) stats[i] = 0;
 }
 
 __global__ void k_fill_i32(int32_t *p, int32_t v, int64_t n) {
@@ -476,14 +514,17 @@ __global__ __launch_bounds__(256) void k_knn(
 // ties to the lower user index. One thread a departure point: the cells of a
 // ring are loads that wait for one another, so a small cloud needs every
 // wavefront it can get (10,201 nodes: 126 us with one thread a node, 18 now;
-// 262,144 nodes: 176 and 117).
+// 262,144 nodes: 176 and 117). A departure point also takes the next place in its
+// owner's list.
 __global__ __launch_bounds__(256) void k_owner(const Geo *__restrict__ geo,
                                                const double *__restrict__ xs,
                                                const double *__restrict__ ys,
                                                const int32_t *__restrict__ perm,
                                                const int32_t *__restrict__ cstart,
                                                const int32_t *__restrict__ cend, int n,
-                                               double dx, int32_t *__restrict__ owner) {
+                                               double dx, int32_t *__restrict__ owner,
+                                               int32_t *__restrict__ cnt,
+                                               int32_t *__restrict__ slot) {
     // eight directions of 32 nodes a workgroup, which share their cells
     const int64_t nb = ((int64_t)n + 31) / 32, blk = xcd_tile(nb);
     if (blk >= nb) return;
@@ -525,6 +566,7 @@ __global__ __launch_bounds__(256) void k_owner(const Geo *__restrict__ geo,
         if (r > g.gx && r > g.gy) break;
     }
     owner[(int64_t)(k - 1) * n + p] = bq;
+    slot[(int64_t)(k - 1) * n + p] = atomicAdd(&cnt[bq], 1);
 }
 
 // x^e for 0 <= e <= 4, without branches on e, so that a lane-dependent
@@ -1645,25 +1687,24 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
     }
 }
 
-// Owner -> departure-point lists of the paper's stencil rule (CSR): count,
-// then fill (the order inside a list does not affect the solved weights).
-__global__ void k_owned_count(int n, const int32_t *__restrict__ owner, int32_t *__restrict__ cnt) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)8 * n) return;
-    atomicAdd(&cnt[owner[i]], 1);
-}
-
-__global__ void k_owned_fill(int n, const int32_t *__restrict__ owner,
-                             const int32_t *__restrict__ ptr, int32_t *__restrict__ cur,
-                             int32_t *__restrict__ pts) {
+// Owner -> departure-point lists of the paper's stencil rule (CSR): every point
+// to the place it took in its owner's list (the order inside a list does not
+// affect the solved weights). The counters are done with: their first word
+// becomes the empty list of owners to solve again.
+__global__ __launch_bounds__(256) void k_owned_fill(int n, const int32_t *__restrict__ owner,
+                                                    int32_t *__restrict__ ptr,
+                                                    const int32_t *__restrict__ slot,
+                                                    int32_t *__restrict__ pts,
+                                                    int32_t *__restrict__ redo) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= (int64_t)8 * n) return;
     const int k0 = (int)(i / n), p = (int)(i - (int64_t)k0 * n);   // owner is [8][n]
-    const int s = owner[i];
-    pts[ptr[s] + atomicAdd(&cur[s], 1)] = p * 8 + k0;
+    pts[ptr[owner[i]] + slot[i]] = p * 8 + k0;
+    if (i == 0) {
+        ptr[n] = 8 * n;
+        redo[0] = 0;
+    }
 }
-
-__global__ void k_set_last(int32_t *ptr, int n, int32_t v) { ptr[n] = v; }
 
 // FP32 copy of the shape vectors in the streaming layout [K][2][n][4]
 // (directions 1..4 and 5..8 as float4). After rounding, the weights of each
@@ -1770,22 +1811,15 @@ hipError_t launch_links(const uint8_t *ntype, const int32_t *perm, const double 
     return hipGetLastError();
 }
 
-hipError_t launch_geo_periodic(Geo *geo, double Lx, double Ly, int gx, int gy, int hb,
-                               hipStream_t s) {
-    hipLaunchKernelGGL(k_geo_periodic, dim3(1), dim3(1), 0, s, geo, Lx, Ly, gx, gy, hb);
-    return hipGetLastError();
-}
-
 hipError_t launch_geo_bbox(Geo *geo, const double *x, const double *y, int n, int gx, int gy,
                            int hb, hipStream_t s) {
     hipLaunchKernelGGL(k_geo_bbox, dim3(1), dim3(1024), 0, s, geo, x, y, n, gx, gy, hb);
     return hipGetLastError();
 }
 
-hipError_t launch_keys(const Geo *geo, const double *x, const double *y, int n,
-                       uint32_t *keys, int32_t *vals, hipStream_t s) {
-    hipLaunchKernelGGL(k_keys, dim3(blocks_for(n, 256)), dim3(256), 0, s, geo, x, y, n, keys,
-                       vals);
+hipError_t launch_reset(int32_t *err, int32_t *stats, int nstats, hipStream_t s) {
+    hipLaunchKernelGGL(k_reset, dim3(blocks_for(std::max(nstats, 1), 256)), dim3(256), 0, s, err, stats,
+                       nstats);
     return hipGetLastError();
 }
 
@@ -1795,30 +1829,87 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_scatter_sorted(const Geo *geo, const double *x, const double *y,
-                                 const uint8_t *nt, const int32_t *perm,
-                                 const uint32_t *skeys, int n, double *xs, double *ys,
-                                 uint8_t *ntype, int32_t *iperm, int32_t *cstart,
-                                 int32_t *cend, int ncells, hipStream_t s) {
-    hipError_t e = launch_fill_i32(cstart, 0, ncells, s);
+// Workspace of the search and the solve: owner counts [n] (then the list of
+// owners to solve again, n + 1), list offsets [n + 1] (the search's list before
+// that), points [8 n] (the sort's counters before that), scan.
+struct OwnedLists {
+    int32_t *cnt, *ptr, *pts;
+    char *scan;
+    size_t scan_bytes;
+    OwnedLists(void *tmp, size_t bytes, int n) {
+        const size_t a = (((size_t)n + 1) * 4 + 255) & ~size_t(255);
+        char *b = (char *)tmp;
+        cnt = (int32_t *)b;
+        ptr = (int32_t *)(b + a);
+        pts = (int32_t *)(b + 2 * a);
+        const size_t head = 2 * a + (((size_t)8 * n * 4 + 255) & ~size_t(255));
+        scan = b + head;
+        scan_bytes = bytes - head;
+    }
+};
+
+// Internal order of the nodes: Hilbert key of the cell, then user index. A
+// counting sort where the keys are at most four a node (square domains have half
+// a key to one, 1:4 ones four; their counters and offsets then fit the place of
+// the point lists) and the sort's temporary memory holds the scan's; longer
+// domains sort the keys. Both give the same order. A build of a small cloud is
+// bound by its launches (about 5 us each), and the library's sort took five of
+// them at 10,201 nodes and sixteen at 262,144; the counting sort takes three or
+// four, the clearing of counters and lists one more, where it took six. Whole
+// builds, with the lists' counts in k_owner: 10,201 nodes 27 launches to 16, 252
+// to 199 us; 262,144 nodes 1,651 to 1,538 us.
+hipError_t launch_order(const BuildOrder &o, hipStream_t s) {
+    const int n = o.n;
+    const OwnedLists lists(o.rbf_tmp, o.rbf_bytes, n);
+    const int64_t all = (int64_t)1 << (2 * o.hb);
+    const bool counted = o.hb < 15 && all <= (int64_t)4 * n && scan_temp_bytes((int)all) <= o.sort_bytes;
+    const int nkeys = counted ? (int)all : 0, ncells = o.gx * o.gy;
+    int32_t *cnt = counted ? lists.pts : nullptr, *off = lists.pts + nkeys;
+    Geo g{};
+    if (o.Lx > 0 && o.Ly > 0) {
+        g.cw = o.Lx / o.gx;
+        g.ch = o.Ly / o.gy;
+        g.Lx = o.Lx;
+        g.Ly = o.Ly;
+        g.gx = o.gx;
+        g.gy = o.gy;
+        g.hb = o.hb;
+    } else {
+        hipLaunchKernelGGL(k_geo_bbox, dim3(1), dim3(1024), 0, s, o.geo, o.x, o.y, n, o.gx, o.gy, o.hb);
+    }
+    const dim3 grid(blocks_for(n, 256)), block(256);
+    hipLaunchKernelGGL(k_begin, dim3(blocks_for(std::max(ncells, std::max(nkeys, 1)), 256)), block, 0, s,
+                       o.geo, g, ncells, o.cstart, o.cend, nkeys, cnt);
+    hipLaunchKernelGGL(k_keys, grid, block, 0, s, o.geo, o.x, o.y, n, o.keys, o.vals, cnt);
+    hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = launch_fill_i32(cend, 0, ncells, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_scatter_sorted, dim3(blocks_for(n, 256)), dim3(256), 0, s, geo, x, y,
-                       nt, perm, skeys, n, xs, ys, ntype, iperm, cstart, cend);
+    if (counted) {
+        if ((e = exclusive_scan(o.sort_tmp, o.sort_bytes, cnt, off, nkeys, s)) != hipSuccess) return e;
+        hipLaunchKernelGGL(k_place, grid, block, 0, s, n, o.keys, o.vals, off, (int32_t *)o.skeys);
+        hipLaunchKernelGGL(k_scatter_sorted<true>, grid, block, 0, s, o.geo, o.x, o.y, o.nt, o.perm,
+                           o.keys, (const int32_t *)o.skeys, off, nkeys, n, o.xs, o.ys, o.ntype, o.iperm,
+                           o.cstart, o.cend, lists.cnt, lists.ptr);
+    } else {
+        if ((e = sort_pairs(o.sort_tmp, o.sort_bytes, o.keys, o.skeys, o.vals, o.perm, n,
+                            std::max(1, 2 * o.hb), s)) != hipSuccess)
+            return e;
+        hipLaunchKernelGGL(k_scatter_sorted<false>, grid, block, 0, s, o.geo, o.x, o.y, o.nt, o.perm,
+                           o.skeys, nullptr, nullptr, 0, n, o.xs, o.ys, o.ntype, o.iperm, o.cstart,
+                           o.cend, lists.cnt, lists.ptr);
+    }
     return hipGetLastError();
 }
 
 hipError_t launch_knn(const Geo *geo, const double *xs, const double *ys,
                       const int32_t *perm, const int32_t *iperm, const int32_t *cstart,
-                      const int32_t *cend, int n, int K, int32_t *redo, int32_t *nbr,
+                      const int32_t *cend, int n, int K, void *tmp, size_t tmp_bytes, int32_t *nbr,
                       hipStream_t s) {
-    hipError_t e = launch_fill_i32(redo, 0, 1, s);
-    if (e != hipSuccess) return e;
+    int32_t *redo = OwnedLists(tmp, tmp_bytes, n).ptr;   // emptied by launch_order
     const dim3 grid(xcd_grid(blocks_for(n, 256 / kKnnLanes)));
     auto kernel = K <= 16 ? k_knn<32> : K <= 32 ? k_knn<64> : k_knn<96>;   // room for a third more
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, geo, xs, ys, perm, cstart, cend, n, K, redo, nbr);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_knn_redo, dim3(64), dim3(64), 0, s, geo, xs, ys, perm, iperm, cstart, cend, n,
                        K, redo, nbr);
     return hipGetLastError();
@@ -1826,9 +1917,10 @@ hipError_t launch_knn(const Geo *geo, const double *xs, const double *ys,
 
 hipError_t launch_owner(const Geo *geo, const double *xs, const double *ys,
                         const int32_t *perm, const int32_t *cstart, const int32_t *cend, int n,
-                        double dx, int32_t *owner, hipStream_t s) {
+                        double dx, int32_t *owner, void *tmp, size_t tmp_bytes, int32_t *slot,
+                        hipStream_t s) {
     hipLaunchKernelGGL(k_owner, dim3(xcd_grid(blocks_for(n, 32))), dim3(256), 0, s, geo, xs, ys,
-                       perm, cstart, cend, n, dx, owner);
+                       perm, cstart, cend, n, dx, owner, OwnedLists(tmp, tmp_bytes, n).cnt, slot);
     return hipGetLastError();
 }
 
@@ -1844,11 +1936,10 @@ static hipError_t launch_rbf_null(const Geo *geo, const double *xs, const double
         if (N2 > 16) kernel = N2 <= 20 ? k_rbf_null<M, 20> : k_rbf_null<M, 24>;
     if constexpr (M == 6)
         if (N2 > 16) kernel = N2 <= 20 ? k_rbf_null<M, 20> : k_rbf_null<M, 28>;
-    hipError_t e = launch_fill_i32(redo, 0, 1, s);
-    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3(xcd_grid(blocks_for(n, 4))), dim3(64), 0, s, geo, xs, ys, nbr, L,
                        n, K, dx, W64, redo);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_rbf_redo, dim3(256), dim3(64), 0, s, geo, xs, ys, perm, nbr, L, n, K, m, dx,
                        redo, W64, dev_err);
     return hipGetLastError();
@@ -1866,36 +1957,23 @@ hipError_t launch_rbf(const Geo *geo, const double *xs, const double *ys,
                       int n, int K, int m, double dx, int mode, void *tmp, size_t tmp_bytes,
                       double *W64, int32_t *dev_err, hipStream_t s) {
     RhsList L{nullptr, nullptr};
-    hipError_t e;
+    const OwnedLists lists(tmp, tmp_bytes, n);
     if (mode == MLBM_STENCIL_PAPER) {
-        char *b = (char *)tmp;
-        int32_t *cnt = (int32_t *)b;
-        b += (((size_t)n + 1) * 4 + 255) & ~size_t(255);
-        int32_t *ptr = (int32_t *)b;
-        b += (((size_t)n + 1) * 4 + 255) & ~size_t(255);
-        int32_t *pts = (int32_t *)b;
-        b += ((size_t)8 * n * 4 + 255) & ~size_t(255);
-        const size_t scan_bytes = tmp_bytes - (size_t)(b - (char *)tmp);
-        if ((e = launch_fill_i32(cnt, 0, n, s)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_owned_count, dim3(blocks_for((int64_t)8 * n, 256)), dim3(256), 0, s, n,
-                           owner, cnt);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        if ((e = exclusive_scan(b, scan_bytes, cnt, ptr, n, s)) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_set_last, dim3(1), dim3(1), 0, s, ptr, n, 8 * n);
-        if ((e = launch_fill_i32(cnt, 0, n, s)) != hipSuccess) return e;
+        hipError_t e = exclusive_scan(lists.scan, lists.scan_bytes, lists.cnt, lists.ptr, n, s);
+        if (e != hipSuccess) return e;
         hipLaunchKernelGGL(k_owned_fill, dim3(blocks_for((int64_t)8 * n, 256)), dim3(256), 0, s, n,
-                           owner, ptr, cnt, pts);
+                           owner, lists.ptr, (const int32_t *)W64, lists.pts, lists.cnt);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        L.ptr = ptr;
-        L.pts = pts;
+        L.ptr = lists.ptr;
+        L.pts = lists.pts;
     }
     // Stencils of up to 32 nodes take the null-space solver (31 at degree 4,
     // where its registers end): 262,144 nodes, whole build, before -> with it,
     // K 30 degree 4 5.7 -> 2.3 ms, K 25 degree 3 4.9 -> 1.8, K 25 degree 2
     // 3.3 -> 1.9, K 20 degree 3 3.1 -> 1.6, K 15 degree 2 2.0 -> 1.1, K 12
     // degree 2 (own stencils) 1.5 -> 0.7. Its list of owners to solve again
-    // takes the place of the list fill's counters, which are done with.
-    int32_t *redo = (int32_t *)tmp;
+    // takes the place of the owners' counters, which are done with.
+    int32_t *redo = lists.cnt;
     if (K <= (m == 4 ? 31 : 32)) {
         if (m == 2)
             return launch_rbf_null<6>(geo, xs, ys, perm, nbr, L, n, K, m, dx, redo, W64, dev_err, s);

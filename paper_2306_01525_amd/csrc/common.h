@@ -293,27 +293,35 @@ __device__ __forceinline__ int64_t xcd_split_tile(const XcdSplit &r) {
 }
 
 // ---- build stages (build.hip) ----
-hipError_t launch_geo_periodic(Geo *geo, double Lx, double Ly, int gx, int gy, int hb,
-                               hipStream_t s);
-hipError_t launch_geo_bbox(Geo *geo, const double *x, const double *y, int n, int gx,
-                           int gy, int hb, hipStream_t s);
-hipError_t launch_keys(const Geo *geo, const double *x, const double *y, int n,
-                       uint32_t *keys, int32_t *vals, hipStream_t s);
-hipError_t launch_scatter_sorted(const Geo *geo, const double *x, const double *y,
-                                 const uint8_t *nt, const int32_t *perm,
-                                 const uint32_t *skeys, int n, double *xs, double *ys,
-                                 uint8_t *ntype, int32_t *iperm, int32_t *cstart,
-                                 int32_t *cend, int ncells, hipStream_t s);
+// Internal order of a cloud's nodes (Hilbert key of the cell, then user index)
+// and the cells' ranges; empties the counters and the list of the calls below.
+struct BuildOrder {
+    int n, gx, gy, hb;
+    double Lx, Ly;
+    const double *x, *y;
+    const uint8_t *nt;
+    Geo *geo;
+    uint32_t *keys, *skeys;
+    int32_t *vals, *cstart, *cend;
+    void *sort_tmp, *rbf_tmp;
+    size_t sort_bytes, rbf_bytes;
+    int32_t *perm, *iperm;
+    double *xs, *ys;
+    uint8_t *ntype;
+};
+hipError_t launch_order(const BuildOrder &o, hipStream_t s);
 hipError_t launch_knn(const Geo *geo, const double *xs, const double *ys,
                       const int32_t *perm, const int32_t *iperm, const int32_t *cstart,
-                      const int32_t *cend, int n, int K, int32_t *redo, int32_t *nbr,
-                      hipStream_t s);   // redo: room for n + 1
+                      const int32_t *cend, int n, int K, void *tmp, size_t tmp_bytes, int32_t *nbr,
+                      hipStream_t s);   // tmp: of rbf_temp_bytes
 hipError_t launch_owner(const Geo *geo, const double *xs, const double *ys,
                         const int32_t *perm, const int32_t *cstart, const int32_t *cend, int n,
-                        double dx, int32_t *owner, hipStream_t s);
+                        double dx, int32_t *owner, void *tmp, size_t tmp_bytes, int32_t *slot,
+                        hipStream_t s);   // slot [8 n]: each point's place in its owner's list
 // workspace of the paper-mode owner lists: counts [n], offsets [n+1],
 // points [8n], scan temp
 size_t rbf_temp_bytes(int n);
+// W64 holds launch_owner's slots on entry (paper mode)
 hipError_t launch_rbf(const Geo *geo, const double *xs, const double *ys,
                       const int32_t *perm, const int32_t *nbr, const int32_t *owner,
                       int n, int K, int m, double dx, int mode, void *tmp, size_t tmp_bytes,
@@ -325,6 +333,7 @@ hipError_t launch_force(const double *xs, const double *ys, const uint8_t *ntype
 // e_k . n(user(p)) < 0
 hipError_t launch_links(const uint8_t *ntype, const int32_t *perm, const double *nx,
                         const double *ny, int n, uint8_t *links, hipStream_t s);
+hipError_t launch_reset(int32_t *err, int32_t *stats, int nstats, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s);
 
 // ---- tile tables (tiles.hip) ----

@@ -193,6 +193,50 @@ def test_tile_tables_are_consistent(mode):
     plan.close()
 
 
+def _hilbert(x, y, order):
+    x, y, d = x.copy(), y.copy(), np.zeros_like(x)
+    for b in reversed(range(order)):
+        rx, ry = x >> b & 1, y >> b & 1
+        d += (3 * rx ^ ry) << 2 * b
+        flip = (ry == 0) & (rx == 1)
+        x, y = np.where(flip, (1 << order) - 1 - x, x), np.where(flip, (1 << order) - 1 - y, y)
+        x, y = np.where(ry == 0, y, x), np.where(ry == 0, x, y)
+    return d
+
+
+@pytest.mark.parametrize("nx,ny,crowd", [(8, 8, 0), (101, 101, 0), (128, 64, 0), (64, 256, 0),
+                                         (32, 256, 0), (400, 16, 0), (500, 7, 0), (70, 70, 1)])
+def test_internal_order_is_the_stable_order_of_the_cells(nx, ny, crowd):
+    """The build's node order, whether the Hilbert keys are counted (up to four
+    keys a node) or sorted (longer domains): by key, then by user index, as a
+    stable sort on the CPU gives it. `crowd`: half of the nodes in a few cells."""
+    from paper_2306_01525_amd import Params, Plan
+    c, _, _ = tgv_case(nx, 12, 2, 1, seed=3, ny=ny, length=float(nx), length_y=float(ny))
+    x, y = c.x.copy(), c.y.copy()
+    if crowd:
+        rng = np.random.default_rng(8)
+        i = rng.permutation(c.n)[:c.n // 2]
+        x[i], y[i] = 1.0 + 0.05 * x[i], 2.0 + 0.05 * y[i]
+    plan = Plan.build(x, y, c.period, Params(dx=c.h, K=12, degree=2, tau=0.8, stencil_mode=1))
+    perm = plan.export("perm")
+    plan.close()
+    Lx, Ly = c.period
+    cells = max(1.0, c.n / 2.0)
+    g = []
+    for v in (np.sqrt(cells * (Lx / Ly)), np.sqrt(cells / (Lx / Ly))):
+        p2 = 1
+        while p2 * 2 <= v * np.sqrt(2.0):
+            p2 *= 2
+        g.append(p2)
+    order = int(max(g)).bit_length() - 1
+    cx = np.clip(np.floor(x / (Lx / g[0])).astype(np.int64), 0, g[0] - 1)
+    cy = np.clip(np.floor(y / (Ly / g[1])).astype(np.int64), 0, g[1] - 1)
+    key = _hilbert(cx, cy, order)
+    say("%d nodes, %d x %d cells, %.2f keys a node, fullest cell %d" % (
+        c.n, g[0], g[1], 4.0 ** order / c.n, np.unique(key, return_counts=True)[1].max()))
+    np.testing.assert_array_equal(perm, np.argsort(key, kind="stable"))
+
+
 @pytest.mark.parametrize("mode,no,nh", [(1, 256, 13), (1, 256, 1024), (1, 256, 1025),
                                         (1, 256, 3072), (0, 1, 12), (0, 512, 1024),
                                         (0, 513, 700), (0, 2048, 700)])
