@@ -396,7 +396,9 @@ mlbm_status mlbm_build_graph(const mlbm_cloud *clouds, const mlbm_params *params
                              int32_t n_steps, int32_t variant, mlbm_plan **out,
                              hipStream_t stream);
 
-/* Select an FP32 step variant by index (0 = default); drops a created graph. */
+/* Select an FP32 step variant by index; drops a created graph. Results are the
+ * same for all of them; a plan starts with the one that is fastest over most
+ * sizes (info.variant). */
 mlbm_status mlbm_plan_set_variant(mlbm_plan *plan, int32_t variant);
 
 /* ---- graphs ------------------------------------------------------------- */

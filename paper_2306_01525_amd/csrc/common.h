@@ -69,6 +69,14 @@ inline int64_t head_nodes(int n) { return ((int64_t)n + 63) / 64 * 64; }
 constexpr int kTile = 256;      // nodes per workgroup in the step kernels
 constexpr int kHaloCap = 1024;  // largest halo a tile stages (10-bit positions)
 constexpr int kStepVariants = MLBM_STEP_VARIANTS; // FP32 step tuning variants
+// The variant of a plan that has not been tuned: two lanes a node, streamed
+// weights, two index words at a time. Against variant 0 (us a step): 50,176
+// nodes, K 30 18.4 -> 16.7; 65,536, K 20 14.6 -> 13.1; 160,000, K 25 24.7 ->
+// 23.9; 262,144, K 30 45.8 -> 45.0, K 45 92.8 -> 88.8; 518,400, K 20 75.3 ->
+// 71.7; 1,048,576, K 30 219.8 -> 215.7. Own-node stencils gain less (65,536, K 12
+// 9.0 -> 8.3; 262,144, K 30 42.9 -> 42.6) and lose at 1,048,576, K 12 (102.5 ->
+// 103.7).
+constexpr int kStartVariant = 9;
 constexpr int kBuildLanes = 4;   // clouds of one plan built concurrently
 constexpr int kStats = 5;        // build records per cloud (tile tables)
 
@@ -115,7 +123,7 @@ struct CloudPlan {
     unsigned lds_bytes = 0;       // dynamic LDS of the step launch (0: no tables)
     int nh_max = 0;               // largest |H_t| of a tile with tables
     int fallback_tiles = -1;      // tiles stepped with global gathers (-1: unknown)
-    int variant = 0;              // FP32 step tuning variant (mlbm_autotune)
+    int variant = kStartVariant;  // FP32 step tuning variant (mlbm_autotune)
     // transposed streaming (adjoint): per direction k = 1..8, CSR over the
     // source node m of (arriving node i, weight)
     int32_t *tr_ptr = nullptr;  // [8n+1] row offsets, row (k-1)*n + m
