@@ -668,21 +668,16 @@ __device__ __forceinline__ void wide_finish(const WideArgs<double> &a, int p, do
 // ways cost the same, at K 30 the halo is cheaper (FP64 6.0 against 6.3), and
 // with two directions a lane it is at every K (22,500 nodes FP64 6.4 / 8.4).
 template <class T, int MODE, bool FORCE, int WALL, bool REC, int D>
-__global__ __launch_bounds__(256) void k_step_wide(WideArgs<T> a, const T *__restrict__ g,
-                                                   T *__restrict__ go, int64_t nblocks) {
-    extern __shared__ __align__(16) unsigned char smem[];
+__device__ __forceinline__ void wide_group(const WideArgs<T> &a, const T *__restrict__ g,
+                                           T *__restrict__ go, int64_t tile, int first,
+                                           unsigned char *smem) {
     typedef T TD __attribute__((ext_vector_type(D)));
     constexpr int NN = 32 * D;          // nodes of the workgroup
-    constexpr int PER = kTile / NN;     // workgroups per tile
     constexpr int CH = 6, NC = 6;       // weight slots per chunk, chunks held
     constexpr int U = kHaloCap / 256;
     // FP32 rows of weights are two float4 a slot, FP64 rows four double2
     constexpr int RPS = sizeof(T) == 4 ? 2 : 4, EPR = 8 / RPS, LPR = EPR / D;
-    const int64_t b = xcd_tile(nblocks);
-    if (b >= nblocks) return;
     const int n = a.n, K = a.K, Kw = (K + 2) / 3;
-    const int64_t tile = b / PER;
-    const int first = (int)(b - tile * PER) * NN;   // first node of the workgroup in its tile
     if (tile * kTile + first >= n) return;          // uniform
     const int tid = threadIdx.x, lane = tid & 63;
     const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -853,6 +848,52 @@ __global__ __launch_bounds__(256) void k_step_wide(WideArgs<T> a, const T *__res
 #pragma unroll
     for (int d = 0; d < 8; ++d) f[d + 1] = gl[d * NN + fn];
     wide_finish<FORCE, WALL, REC>(a, fp, f, go, node, ax, ay, part ? part * D + 1 : 0, part * D + D + 1);
+}
+
+template <class T, int MODE, bool FORCE, int WALL, bool REC, int D>
+__global__ __launch_bounds__(256) void k_step_wide(WideArgs<T> a, const T *__restrict__ g,
+                                                   T *__restrict__ go, int64_t nblocks) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int PER = kTile / (32 * D);   // workgroups per tile
+    const int64_t b = xcd_tile(nblocks);
+    if (b >= nblocks) return;
+    wide_group<T, MODE, FORCE, WALL, REC, D>(a, g, go, b / PER, (int)(b % PER) * 32 * D, smem);
+}
+
+// The same over all tiles of a batched plan, as k_step32_batch.
+template <int MODE, int D>
+__global__ __launch_bounds__(256) void k_step_wide_batch(const Step32Args *__restrict__ descs,
+                                                         const int32_t *__restrict__ tile2cloud,
+                                                         const float *__restrict__ g,
+                                                         float *__restrict__ go, int64_t nblocks,
+                                                         int nhcap) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    constexpr int PER = kTile / (32 * D);
+    const int64_t b = xcd_tile(nblocks);
+    if (b >= nblocks) return;
+    const int64_t t = b / PER;
+    const Step32Args &s = descs[tile2cloud[t]];
+    WideArgs<float> a{};
+    a.n = s.n;
+    a.K = s.K;
+    a.ocap = s.ocap;
+    a.hcap = s.hcap;
+    a.W = reinterpret_cast<const float *>(s.W);
+    a.nbr = s.nbr;
+    a.owner = s.owner;
+    a.rtau = s.rtau;
+    a.rho0 = s.rho0;
+    a.rho_w = s.rho_w;
+    a.tdesc = s.tdesc;
+    a.ownerL = s.ownerL;
+    a.nbrL = s.nbrL;
+    a.hlist = s.hlist;
+    a.err = s.err;
+    a.perm = s.perm;
+    a.uoff = s.uoff;
+    a.nhcap = nhcap;
+    wide_group<float, MODE, false, 0, false, D>(a, g + s.soff, go + s.soff, t - s.tile_begin,
+                                                (int)(b % PER) * 32 * D, smem);
 }
 
 // ------------------------------------------------------------------------
@@ -1116,22 +1157,6 @@ void launch32_batch(const mlbm_plan &plan, const void *gin, void *gout, hipStrea
                        (const float *)gin, (float *)gout, plan.xcd);
 }
 
-template <int MODE>
-void launch32_batch_v(const mlbm_plan &plan, const void *gin, void *gout, hipStream_t s) {
-    switch (plan.c[0].variant) {
-        case 1: launch32_batch<MODE, 1, true>(plan, gin, gout, s); break;
-        case 2: launch32_batch<MODE, 2, false>(plan, gin, gout, s); break;
-        case 3: launch32_batch<MODE, 2, true>(plan, gin, gout, s); break;
-        case 4: launch32_batch<MODE, 3, false>(plan, gin, gout, s); break;
-        case 5: launch32_batch<MODE, 3, true>(plan, gin, gout, s); break;
-        case 6: launch32s_batch<MODE, false>(plan, gin, gout, s); break;
-        case 7: launch32s_batch<MODE, true>(plan, gin, gout, s); break;
-        case 8: launch32s_batch<MODE, false, 2>(plan, gin, gout, s); break;
-        case 9: launch32s_batch<MODE, true, 2>(plan, gin, gout, s); break;
-        default: launch32_batch<MODE, 1, false>(plan, gin, gout, s); break;
-    }
-}
-
 template <int MODE, bool FORCE, int WALL, bool REC>
 void launch32_tuned(const CloudPlan &cp, const void *gin, void *gout, void *frec,
                     int64_t nblocks, hipStream_t s) {
@@ -1151,6 +1176,12 @@ void launch32_tuned(const CloudPlan &cp, const void *gin, void *gout, void *frec
         case 9: launch32s<MODE, FORCE, WALL, REC, true, 2>(cp, gin, gout, frec, nblocks, s); break;
         default: launch32<MODE, FORCE, WALL, REC, 1, false>(cp, gin, gout, frec, nblocks, s); break;
     }
+}
+
+// Halo nodes that a launch's LDS holds (64 KiB at most: a tile past that gathers
+// from global memory).
+template <class T> int wide_halo(int nh_max) {
+    return std::min(nh_max, (int)(65536 / sizeof(T) - 2) / 8);
 }
 
 template <class T> WideArgs<T> wide_args(const CloudPlan &cp, void *frec) {
@@ -1180,9 +1211,13 @@ template <class T> WideArgs<T> wide_args(const CloudPlan &cp, void *frec) {
     a.err = cp.err;
     a.perm = cp.perm;
     a.uoff = (int)cp.off;
-    // (64 KiB of LDS at most: a tile past that gathers from global memory)
-    a.nhcap = std::min(cp.nh_max, (int)(65536 / sizeof(T) - 2) / 8);
+    a.nhcap = wide_halo<T>(cp.nh_max);
     return a;
+}
+
+// the halo's populations and a zero, then the sums of the workgroup's nodes in their place
+template <class T> unsigned wide_lds(int nhcap, int nodes) {
+    return (unsigned)(8 * std::max(nhcap, nodes) + 2) * sizeof(T);
 }
 
 template <class T, int MODE, bool FORCE, int WALL, bool REC>
@@ -1191,8 +1226,7 @@ void launch_wide(const CloudPlan &cp, int dirs, const void *gin, void *gout, voi
     const int nodes = 32 * dirs;   // of a workgroup
     const int64_t nb = ((int64_t)cp.n + nodes - 1) / nodes;
     const WideArgs<T> a = wide_args<T>(cp, frec);
-    // the halo's populations and a zero, then the sums of the workgroup's nodes in their place
-    const unsigned lds = (unsigned)(8 * std::max(a.nhcap, nodes) + 2) * sizeof(T);
+    const unsigned lds = wide_lds<T>(a.nhcap, nodes);
     auto kernel = dirs == 1 ? k_step_wide<T, MODE, FORCE, WALL, REC, 1>
                             : k_step_wide<T, MODE, FORCE, WALL, REC, 2>;
     hipLaunchKernelGGL(kernel, dim3(xcd_grid(nb)), dim3(256), lds, s, a, (const T *)gin, (T *)gout,
@@ -1214,6 +1248,42 @@ void launch_wide(const CloudPlan &cp, int dirs, const void *gin, void *gout, voi
 inline int wide_dirs(int n, int precision) {
     if (n <= 8192) return 1;
     return n <= (precision == MLBM_FP64 ? 102400 : 49152) ? 2 : 0;
+}
+
+template <int MODE, int D>
+void launch_wide_batch(const mlbm_plan &plan, const void *gin, void *gout, hipStream_t s) {
+    const int64_t nb = plan.total_tiles * (kTile / (32 * D));
+    int nh = 0;
+    for (const CloudPlan &cp : plan.c) nh = std::max(nh, cp.nh_max);
+    nh = wide_halo<float>(nh);
+    hipLaunchKernelGGL((k_step_wide_batch<MODE, D>), dim3(xcd_grid(nb)), dim3(256),
+                       wide_lds<float>(nh, 32 * D), s, plan.descs, plan.tile2cloud,
+                       (const float *)gin, (float *)gout, nb, nh);
+}
+
+// Small batches take the small-cloud kernel by the rule of a single cloud of as
+// many tiles, whatever the variant. K 20 to 30, us a step, best tile kernel and
+// this: 2 clouds of 3,232 nodes together 9.5 and 5.1, 8 of 15,247 9.7 and 6.6, 4
+// of 38,054 16.7 and 12.9; 8 of 76,924 nodes stay with the tile kernels (18.5).
+template <int MODE>
+void launch32_batch_v(const mlbm_plan &plan, const void *gin, void *gout, hipStream_t s) {
+    if (const int dirs = wide_dirs((int)std::min<int64_t>(plan.total_tiles * kTile, INT32_MAX), MLBM_FP32_DEV)) {
+        if (dirs == 1) launch_wide_batch<MODE, 1>(plan, gin, gout, s);
+        else launch_wide_batch<MODE, 2>(plan, gin, gout, s);
+        return;
+    }
+    switch (plan.c[0].variant) {
+        case 1: launch32_batch<MODE, 1, true>(plan, gin, gout, s); break;
+        case 2: launch32_batch<MODE, 2, false>(plan, gin, gout, s); break;
+        case 3: launch32_batch<MODE, 2, true>(plan, gin, gout, s); break;
+        case 4: launch32_batch<MODE, 3, false>(plan, gin, gout, s); break;
+        case 5: launch32_batch<MODE, 3, true>(plan, gin, gout, s); break;
+        case 6: launch32s_batch<MODE, false>(plan, gin, gout, s); break;
+        case 7: launch32s_batch<MODE, true>(plan, gin, gout, s); break;
+        case 8: launch32s_batch<MODE, false, 2>(plan, gin, gout, s); break;
+        case 9: launch32s_batch<MODE, true, 2>(plan, gin, gout, s); break;
+        default: launch32_batch<MODE, 1, false>(plan, gin, gout, s); break;
+    }
 }
 
 template <int MODE, bool FORCE, int WALL, bool REC>

@@ -228,3 +228,40 @@ def test_random_batches_equal_single_plans(batch):
         sp.close()
     assert bp.device_error() == 0
     bp.close()
+
+
+@pytest.mark.parametrize("sides,tile_kernels", [
+    ((9, 16, 17, 20), 0),               # 7 tiles: 32 nodes a workgroup
+    ((64, 61, 20), 0),                  # 33 tiles, one more than those take: 64 nodes
+    ((128, 128, 128), 0),               # 192 tiles, the most that it takes
+    ((130, 130, 130), 1),               # 201 tiles, beyond the small-cloud kernel
+])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_batches_on_both_sides_of_the_small_cloud_kernel(sides, tile_kernels, mode):
+    """Batches of the small-cloud kernel's two workgroup sizes and of the tile
+    kernels (every variant): bitwise the single-cloud plans' states."""
+    from paper_2306_01525_amd import Params, Plan
+    sets = [(20, 3), (30, 4), (12, 2), (25, 2)]
+    clouds, params, u = [], [], []
+    for i, side in enumerate(sides):
+        c = jittered_lattice(side, seed=40 + i)
+        K, m = sets[i]
+        clouds.append((c.x, c.y, c.period, None))
+        params.append(Params(dx=c.h, K=K, degree=m, tau=0.6 + 0.1 * i, stencil_mode=mode))
+        u.append(tgv_initial_velocity(c.x, c.y, c.period[0], 0.01))
+    bp = Plan.build_batch(clouds, params)
+    tiles = sum((s * s + 255) // 256 for s in sides)
+    say("mode %d: %d clouds, %d nodes, %d tiles" % (mode, len(sides), bp.n, tiles))
+    assert (tiles * 256 > 49152) == bool(tile_kernels)
+    start = bp.init(np.concatenate([a for a, _ in u]), np.concatenate([b for _, b in u]))
+    want = []
+    for i, ((x, y, period, _), p) in enumerate(zip(clouds, params)):
+        sp = Plan.build(x, y, period, p)
+        want.append(sp.step(sp.init(*u[i]), sp.new_state(), 3))
+        sp.close()
+    for v in range(10) if tile_kernels else (0, 9):
+        bp.set_variant(v)
+        g = bp.step(start.clone(), bp.new_state(), 3)
+        for i in range(len(sides)):
+            assert torch.equal(want[i], bp.cloud_view(g, i)), (v, i)
+    bp.close()
