@@ -26,10 +26,11 @@ __device__ __forceinline__ int stencil_owner(const int32_t *owner, int mode, int
 // LDS hash table per tile of arriving nodes, so that a tile adds to a row, or
 // claims a run of it, with a single atomic. Keys that find no slot within
 // kTrProbe probes (an unusually wide tile) fall back to one atomic per entry;
-// k_tr_sort orders every row afterwards.
+// k_tr_finish orders every row afterwards.
 constexpr int kTrHash = 4096;    // counts: keys of four directions
 constexpr int kTrHashF = 1024;   // fill: keys of one direction
 constexpr int kTrProbe = 32;
+constexpr int kTrCs = 4;         // threads a node in the counts
 constexpr uint32_t kTrEmpty = 0xFFFFFFFFu;
 
 template <int HS = kTrHash>
@@ -49,29 +50,28 @@ __device__ __forceinline__ int tr_slot(uint32_t *hkey, uint32_t key, bool insert
     return -1;
 }
 
-// Source node m of entry (i, direction 4 h + kk + 1, slot j).
-__device__ __forceinline__ int tr_source(const int32_t *nbr, const int32_t *owner, int mode,
-                                         int n, int h, int kk, int j, int i) {
-    const int s = stencil_owner(owner, mode, 4 * h + kk + 1, n, i);
-    return nbr[(int64_t)j * n + s];
-}
-
-// Pass over the workgroup's entries: per-key counts in hcnt; entries without
-// a slot add to cnt_direct[row] directly (when it is given).
-__device__ __forceinline__ void tr_count_tile(int n, int K, int mode, int h, int i,
+// Counts of one thread's entries, stencil slots j0, j0 + step, ... of node i, per
+// key in hcnt; entries without a slot add to cnt_direct[row] directly.
+__device__ __forceinline__ void tr_count_node(int n, int K, int mode, int h, int i, int j0, int step,
                                               const int32_t *nbr, const int32_t *owner,
                                               uint32_t *hkey, int32_t *hcnt,
                                               int32_t *cnt_direct) {
     if (i >= n) return;
-    for (int j = 0; j < K; ++j) {
+    int s[4];
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) s[kk] = stencil_owner(owner, mode, 4 * h + kk + 1, n, i);
+#pragma unroll 2
+    for (int j = j0; j < K; j += step) {
+        int m[4];
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk) m[kk] = nbr[(int64_t)j * n + s[kk]];
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) {
-            const int m = tr_source(nbr, owner, mode, n, h, kk, j, i);
-            const int sl = tr_slot(hkey, (uint32_t)(kk * n + m), true);
+            const int sl = tr_slot(hkey, (uint32_t)(kk * n + m[kk]), true);
             if (sl >= 0)
                 atomicAdd(&hcnt[sl], 1);
-            else if (cnt_direct)
-                atomicAdd(&cnt_direct[(int64_t)(4 * h + kk) * n + m], 1);
+            else
+                atomicAdd(&cnt_direct[(int64_t)(4 * h + kk) * n + m[kk]], 1);
         }
     }
 }
@@ -89,8 +89,11 @@ __device__ __forceinline__ int64_t tr_key_row(uint32_t key, int n, int h) {
 }
 
 // Counts: a workgroup per tile of 256 arriving nodes and half of the
-// directions (1-4 or 5-8), keys (k - 1 - 4 h) n + m.
-__global__ __launch_bounds__(256) void k_tr_count(int n, int K, int mode,
+// directions (1-4 or 5-8), keys (k - 1 - 4 h) n + m. Four threads a node, on
+// alternate stencil slots: the entries of a thread wait for memory and for the
+// hash table one after another (K 30: 10,201 nodes, one thread a node, 78 us, now
+// 23; 262,144 nodes 312 and 216).
+__global__ __launch_bounds__(kTrCs * 256) void k_tr_count(int n, int K, int mode,
                                                   const int32_t *__restrict__ nbr,
                                                   const int32_t *__restrict__ owner,
                                                   int32_t *__restrict__ cnt) {
@@ -98,10 +101,10 @@ __global__ __launch_bounds__(256) void k_tr_count(int n, int K, int mode,
     __shared__ int32_t hcnt[kTrHash];
     const int64_t nt = ((int64_t)n + 255) / 256, t = xcd_tile(nt);
     if (t >= nt) return;   // uniform
-    const int h = blockIdx.y, i = (int)(t * 256) + (int)threadIdx.x;
+    const int h = blockIdx.y, i = (int)(t * 256) + (int)(threadIdx.x & 255);
     tr_hash_clear(hkey, hcnt);
     __syncthreads();
-    tr_count_tile(n, K, mode, h, i, nbr, owner, hkey, hcnt, cnt);
+    tr_count_node(n, K, mode, h, i, threadIdx.x >> 8, kTrCs, nbr, owner, hkey, hcnt, cnt);
     __syncthreads();
     for (int t = threadIdx.x; t < kTrHash; t += blockDim.x)
         if (hkey[t] != kTrEmpty) atomicAdd(&cnt[tr_key_row(hkey[t], n, h)], hcnt[t]);
@@ -214,76 +217,6 @@ __global__ __launch_bounds__(kTrJs * TT) void k_tr_fill(int n, int K, int mode,
     }
 }
 
-// Sort each CSR row by arriving node. An arriving node appears at most once
-// in a row, so the rank of an entry (how many entries of the row have a
-// smaller column) is its sorted position. A wavefront takes two rows: when
-// both have at most 32 entries, each half of the wavefront ranks one;
-// otherwise the whole wavefront ranks one row after the other, and a row
-// longer than a wavefront (not met with K <= 48 on clouds of even spacing)
-// takes an insertion sort by one lane.
-template <class T>
-__device__ __forceinline__ void tr_sort_row_wave(int lane, int b, int len, int32_t *col, T *val) {
-    if (len <= 64) {
-        int c = INT_MAX;
-        T v = 0;
-        if (lane < len) {
-            c = col[b + lane];
-            v = val[b + lane];
-        }
-        int rank = 0;
-        for (int j = 0; j < len; ++j) rank += __shfl(c, j, 64) < c;   // len: uniform
-        if (lane < len) {
-            col[b + rank] = c;
-            val[b + rank] = v;
-        }
-        return;
-    }
-    if (lane != 0) return;
-    for (int a = b + 1; a < b + len; ++a) {
-        const int c = col[a];
-        const T v = val[a];
-        int q = a - 1;
-        while (q >= b && col[q] > c) {
-            col[q + 1] = col[q];
-            val[q + 1] = val[q];
-            --q;
-        }
-        col[q + 1] = c;
-        val[q + 1] = v;
-    }
-}
-
-template <class T>
-__global__ __launch_bounds__(256) void k_tr_sort(int64_t rows, const int32_t *__restrict__ ptr,
-                                                 int32_t *__restrict__ col, T *__restrict__ val) {
-    const int lane = threadIdx.x & 63;
-    const int64_t r0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * 2;
-    if (r0 >= rows) return;   // uniform across the wavefront
-    const int half = lane >> 5, hl = lane & 31;
-    const int64_t r = r0 + half;
-    const int b = r < rows ? ptr[r] : 0;
-    const int len = r < rows ? ptr[r + 1] - b : 0;
-    const int len0 = __builtin_amdgcn_readlane(len, 0), len1 = __builtin_amdgcn_readlane(len, 32);
-    const int lmax = max(len0, len1);
-    if (lmax <= 32) {
-        int c = INT_MAX;
-        T v = 0;
-        if (hl < len) {
-            c = col[b + hl];
-            v = val[b + hl];
-        }
-        int rank = 0;
-        for (int j = 0; j < lmax; ++j) rank += __shfl(c, j, 32) < c;   // pads hold INT_MAX
-        if (hl < len) {
-            col[b + rank] = c;
-            val[b + rank] = v;
-        }
-        return;
-    }
-    tr_sort_row_wave(lane, __builtin_amdgcn_readlane(b, 0), len0, col, val);
-    if (r0 + 1 < rows) tr_sort_row_wave(lane, __builtin_amdgcn_readlane(b, 32), len1, col, val);
-}
-
 __global__ void k_set_i32(int32_t *p, int32_t v) { *p = v; }
 
 // Row heads of the transposed operator, compacted per group of 64 nodes (one
@@ -311,91 +244,146 @@ __device__ __forceinline__ int64_t unit_entry(int64_t u0, int c, int r, int k) {
     return u0 * 8 + (int64_t)((k >> 2) * c + r) * 4 + (k & 3);
 }
 
-// Compacted copy of the first lw entries of every sorted CSR row, one
-// wavefront per group of 64 nodes (lanes past the last node take part in the
-// ballots with hd = 0). Slot by slot, each lane of a node with hd > e builds
-// its unit: the eight rows' entry e, padded with (m, 0) past a row's end, and
-// stores it as two 16-byte column vectors and two weight vectors. Consecutive
-// active lanes hold consecutive units, so the stores are coalesced. A lane
-// reads kEllChunk consecutive entries of a row back to back, so that the
-// lines they share are used while they are still in the cache (one slot at a
-// time, with every wavefront of a CU walking its own rows, they were not).
 constexpr int kEllMaxLw = kMaxK + 4;
-constexpr int kEllChunk = 8;
-template <class T> struct Vec4;
-template <> struct Vec4<float> { typedef float4 type; };
-template <> struct Vec4<double> { typedef double __attribute__((ext_vector_type(4))) type; };
+constexpr int kFinRows = 16;    // nodes of a workgroup of k_tr_finish
+constexpr int kFinLen = 64;     // row entries ranked in LDS; longer rows take one lane
+constexpr int kFinPitch = 68;   // their stride (16-byte aligned, rows on other banks)
 
+// Last pass over the transposed operator: sorts each CSR row by arriving node and
+// writes the compacted heads. A workgroup takes 16 nodes of a group and half of
+// the directions, one direction a wavefront. Sixteen lanes hold a row; an arriving
+// node appears at most once in it, so an entry's place is the count of smaller
+// columns, taken from the row in LDS four columns a read. The sorted heads stay
+// in LDS, from where all lanes gather the units, padded with (m, 0) past a row's
+// end, as two 16-byte vectors each; consecutive lanes hold consecutive units.
+// Four rows a wavefront wait for their entries, then for the row in LDS, in turn.
+// Sort (by lane exchanges) and heads (each lane walking its own rows in memory) as
+// two passes, and now, us, degree 4, K 30: 10,201 nodes FP32 24 + 82, 23; 90,000
+// FP64 193 + 432, 292; 262,144 FP32 528 + 592, 581 (1.6 GB, 2.8 TB/s).
 template <class T>
-__global__ __launch_bounds__(256) void k_ell_fill(int n, int lw, const int32_t *__restrict__ ptr,
-                                                  const int32_t *__restrict__ col,
-                                                  const T *__restrict__ val,
-                                                  int32_t *__restrict__ ecol, T *__restrict__ eval) {
-    typedef typename Vec4<T>::type V4;
-    const int lane = threadIdx.x & 63;
-    const int64_t g = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    const int64_t m0 = g * 64;
-    if (m0 >= n) return;   // uniform across the wavefront
-    const int m = (int)(m0 + lane);
-    int b[8], len[8], hd = 0;
+__global__ __launch_bounds__(256) void k_tr_finish(int n, int lw, const int32_t *__restrict__ ptr,
+                                                   int32_t *col, T *val, int32_t *__restrict__ ecol,
+                                                   T *__restrict__ eval) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ uint64_t s_mask[kEllMaxLw];   // nodes of the group with a unit in slot e
+    __shared__ int s_off[kEllMaxLw];         // units of earlier slots
+    __shared__ int s_hd[64];                 // head lengths of the group
+    __shared__ int s_row[4][kFinRows + 1];   // row bounds
+    typedef T T4 __attribute__((ext_vector_type(4)));
+    constexpr int NR = kFinRows, PARTS = 64 / NR, NJ = kFinLen / 16;
+    const int S = lw | 1;
+    const int64_t parts = ((int64_t)n + 63) / 64 * PARTS, part = xcd_tile(parts);
+    if (part >= parts) return;   // uniform
+    const int64_t g = part / PARTS;
+    const int m0 = (int)(g * 64), r0 = m0 + (int)(part % PARTS) * NR, h = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int32_t *unsorted = reinterpret_cast<int32_t *>(smem);               // [4][4][kFinPitch]
+    T *hval = reinterpret_cast<T *>(unsorted + 16 * kFinPitch);          // [4][NR][S]
+    int32_t *hcol = reinterpret_cast<int32_t *>(hval + 4 * NR * S);      // [4][NR][S]
+    if (wv == 0) {
+        int hd = 0;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        b[k] = len[k] = 0;
-        if (m < n) {
-            const int64_t row = (int64_t)k * n + m;
-            b[k] = ptr[row];
-            len[k] = ptr[row + 1] - b[k];
-            hd = max(hd, min(len[k], lw));
+        for (int k = 0; k < 8; ++k)
+            if (m0 + lane < n) {
+                const int64_t row = (int64_t)k * n + m0 + lane;
+                hd = max(hd, min(ptr[row + 1] - ptr[row], lw));
+            }
+        s_hd[lane] = hd;
+        int off = 0;
+        for (int e = 0; e < lw; ++e) {
+            const uint64_t mask = __ballot(e < hd);
+            if (lane == 0) {
+                s_mask[e] = mask;
+                s_off[e] = off;
+            }
+            off += __popcll(mask);
         }
     }
-    const int64_t g0 = g * 64 * lw;
-    int64_t off = 0;
-    for (int e0 = 0; e0 < lw; e0 += kEllChunk) {
-        if (__ballot(e0 < hd) == 0) break;   // hd is fixed: no later slot has a unit
-        int rk[kEllChunk], ck[kEllChunk];
+    const int64_t krow = (int64_t)(4 * h + wv) * n;
+    if (lane <= NR) s_row[wv][lane] = ptr[krow + min(r0 + lane, n)];
+    wave_lds_sync();
+    int32_t *uc = unsorted + wv * 4 * kFinPitch, *hc = hcol + wv * NR * S;
+    T *hv = hval + wv * NR * S;
+    const int sub = lane >> 4, p16 = lane & 15;
+    for (int r4 = 0; r4 < NR; r4 += 4) {
+        const int r = r4 + sub, b = s_row[wv][r], all = s_row[wv][r + 1] - b;
+        const int len = all <= kFinLen ? all : 0;
+        int longest = max(len, __shfl_xor(len, 16));
+        longest = max(longest, __shfl_xor(longest, 32));
+        longest = __builtin_amdgcn_readfirstlane(longest);
+        int32_t c[NJ];
+        T v[NJ];
 #pragma unroll
-        for (int t = 0; t < kEllChunk; ++t) {
-            const uint64_t mask = __ballot(e0 + t < hd);
-            rk[t] = lanes_below(mask);
-            ck[t] = __popcll(mask);
+        for (int j = 0; j < NJ; ++j)
+            if (16 * j < longest) {
+                const bool in = 16 * j + p16 < len;
+                c[j] = in ? col[b + 16 * j + p16] : INT_MAX;
+                v[j] = in ? val[b + 16 * j + p16] : (T)0;
+            }
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+            if (16 * j < longest) uc[sub * kFinPitch + 16 * j + p16] = c[j];
+        wave_lds_sync();
+        int rank[NJ] = {};
+        const int4 *row = reinterpret_cast<const int4 *>(uc + sub * kFinPitch);
+        for (int t = 0; 4 * t < longest; ++t) {   // (filled with INT_MAX to a multiple of 16)
+            const int4 x = row[t];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                if (16 * j < longest)
+                    rank[j] += (x.x < c[j] ? 1 : 0) + (x.y < c[j] ? 1 : 0) + (x.z < c[j] ? 1 : 0) +
+                               (x.w < c[j] ? 1 : 0);
         }
 #pragma unroll
-        for (int hh = 0; hh < 2; ++hh) {
-            // the chunk's entries of the half's four rows, read row by row
-            int cv[4][kEllChunk];
-            T wv[4][kEllChunk];
-#pragma unroll
-            for (int kk = 0; kk < 4; ++kk) {
-                const int k = 4 * hh + kk;
-#pragma unroll
-                for (int t = 0; t < kEllChunk; ++t) {
-                    cv[kk][t] = m;
-                    wv[kk][t] = (T)0;
-                    if (e0 + t < len[k]) {
-                        cv[kk][t] = col[b[k] + e0 + t];
-                        wv[kk][t] = val[b[k] + e0 + t];
-                    }
+        for (int j = 0; j < NJ; ++j)
+            if (16 * j + p16 < len) {
+                col[b + rank[j]] = c[j];
+                val[b + rank[j]] = v[j];
+                if (rank[j] < lw) {
+                    hc[r * S + rank[j]] = c[j];
+                    hv[r * S + rank[j]] = v[j];
                 }
             }
-            int64_t u = off;
-#pragma unroll
-            for (int t = 0; t < kEllChunk; ++t) {
-                if (e0 + t < hd) {
-                    const int64_t at = unit_entry(g0 + u, ck[t], rk[t], 4 * hh);
-                    *reinterpret_cast<int4 *>(ecol + at) =
-                        make_int4(cv[0][t], cv[1][t], cv[2][t], cv[3][t]);
-                    V4 vv;
-                    vv[0] = wv[0][t];
-                    vv[1] = wv[1][t];
-                    vv[2] = wv[2][t];
-                    vv[3] = wv[3][t];
-                    *reinterpret_cast<V4 *>(eval + at) = vv;
+        // a row longer than that (not met with K <= 48 on clouds of even
+        // spacing): an insertion sort by one lane
+        if (p16 == 0 && all > kFinLen) {
+            for (int a = b + 1; a < b + all; ++a) {
+                const int ca = col[a];
+                const T va = val[a];
+                int q = a - 1;
+                while (q >= b && col[q] > ca) {
+                    col[q + 1] = col[q];
+                    val[q + 1] = val[q];
+                    --q;
                 }
-                u += ck[t];
+                col[q + 1] = ca;
+                val[q + 1] = va;
+            }
+            for (int e = 0; e < lw; ++e) {
+                hc[r * S + e] = col[b + e];
+                hv[r * S + e] = val[b + e];
             }
         }
+        wave_lds_sync();   // the next rows take the place of these
+    }
+    __syncthreads();
+    const int l = tid % NR, m = r0 + l, bit = m - m0;
+    const int hd = s_hd[bit];
+    for (int e = tid / NR; e < hd; e += 256 / NR) {
+        const uint64_t mask = s_mask[e];
+        const int64_t at = unit_entry(g * 64 * lw + s_off[e], __popcll(mask),
+                                      __popcll(mask & ((uint64_t(1) << bit) - 1)), 4 * h);
+        int cc[4];
+        T4 w;
 #pragma unroll
-        for (int t = 0; t < kEllChunk; ++t) off += ck[t];
+        for (int k = 0; k < 4; ++k) {
+            const bool in = e < s_row[k][l + 1] - s_row[k][l];
+            cc[k] = in ? hcol[(k * NR + l) * S + e] : m;
+            w[k] = in ? hval[(k * NR + l) * S + e] : (T)0;
+        }
+        *reinterpret_cast<int4 *>(ecol + at) = make_int4(cc[0], cc[1], cc[2], cc[3]);
+        *reinterpret_cast<T4 *>(eval + at) = w;
     }
 }
 
@@ -449,11 +437,12 @@ __device__ __forceinline__ void moments_of(const T *f, int n, int p, int dev, do
 
 // Inverse halo of a tile of source nodes: every arriving node that the head
 // (first lw entries) of the transposed rows of the tile's nodes reads, sorted
-// (IndexSet), capped at cap. The slot-major
-// columns of those rows are rewritten as positions in that set, three 10-bit
-// fields per word: word w of row k of node m (compacted like the heads, over
-// triples of slots) holds slots 3w, 3w+1, 3w+2; fields past the end of the
-// row are 0.
+// (IndexSet), capped at cap. The slot-major columns of those rows are rewritten
+// as positions in that set, three 10-bit fields per word: word w of row k of node
+// m (compacted like the heads, over triples of slots) holds slots 3w, 3w+1, 3w+2;
+// fields past the end of the row are 0. Bound by its chains of waits: with one
+// entry at a time a thread and the columns left to a quarter of the wavefronts
+// 10,201 nodes (K 30) took 103 us and 262,144 320, now 55 and 268.
 __global__ __launch_bounds__(1024) void k_adj_tiles(int n, int lw, int hcap, int cap,
                                                     const int32_t *__restrict__ ptr,
                                                     const int32_t *__restrict__ col,
@@ -468,14 +457,32 @@ __global__ __launch_bounds__(1024) void k_adj_tiles(int n, int lw, int hcap, int
     const int lw3 = (lw + 2) / 3;
     set.clear();
     __syncthreads();
-    for (int e = tid; e < 8 * cnt * lw; e += blockDim.x) {
-        const int k0 = e / (cnt * lw), r = e - k0 * cnt * lw;
-        const int l = r / lw, sl = r - l * lw;
-        const int m = base + l;
-        const int64_t row = (int64_t)k0 * n + m;
-        if (sl >= ptr[row + 1] - ptr[row]) continue;
-        const int q = col[ptr[row] + sl];
-        set.add(q);
+    // sixteen lanes a row, kRows rows of theirs in flight
+    constexpr int kRows = 4, kTeams = 1024 / 16;
+    const int p16 = tid & 15;
+    for (int w0 = tid >> 4; w0 < 8 * kTile; w0 += kRows * kTeams) {
+        int b[kRows], len[kRows];
+#pragma unroll
+        for (int i = 0; i < kRows; ++i) {
+            const int w = w0 + i * kTeams, l = w & (kTile - 1);   // row w / kTile of node l
+            b[i] = len[i] = 0;
+            if (l < cnt) {
+                const int64_t row = (int64_t)(w / kTile) * n + base + l;
+                b[i] = ptr[row];
+                len[i] = min(ptr[row + 1] - b[i], lw);
+            }
+        }
+        int q[kRows][kEllMaxLw / 16 + 1];
+#pragma unroll
+        for (int i = 0; i < kRows; ++i)
+#pragma unroll
+            for (int j = 0; j < kEllMaxLw / 16 + 1; ++j)
+                if (16 * j + p16 < len[i]) q[i][j] = col[b[i] + 16 * j + p16];
+#pragma unroll
+        for (int i = 0; i < kRows; ++i)
+#pragma unroll
+            for (int j = 0; j < kEllMaxLw / 16 + 1; ++j)
+                if (16 * j + p16 < len[i]) set.add(q[i][j]);
     }
     __syncthreads();
     set.count();
@@ -484,61 +491,62 @@ __global__ __launch_bounds__(1024) void k_adj_tiles(int n, int lw, int hcap, int
     if (fits) {
         set.order(ilist + (int64_t)t * hcap);
         __syncthreads();
-        // local columns, one lane per node of the tile (the first four
-        // wavefronts, one per group of 64 nodes): the columns come from the
-        // compacted heads, slot by slot (contiguous over the lanes; the rows
-        // themselves would be read with a stride across the lanes, triple
-        // after triple), and each lane stores its unit's two halves
-        if (tid < kTile) {
-            typedef int32_t I4 __attribute__((ext_vector_type(4)));
-            typedef uint32_t U4 __attribute__((ext_vector_type(4)));
-            const int m = base + tid;
-            int len[8], hd = 0;
+        // local columns: the columns come from the compacted heads, slot by slot
+        // (contiguous over the lanes; the rows themselves would be read with a
+        // stride across the lanes, triple after triple). Four wavefronts a group
+        // of 64 nodes, one lane a node, each on every fourth triple; the ballots
+        // of the others only move its offsets.
+        typedef int32_t I4 __attribute__((ext_vector_type(4)));
+        typedef uint32_t U4 __attribute__((ext_vector_type(4)));
+        const int wv = tid >> 6, turn = wv >> 2;
+        const int m = base + (wv & 3) * 64 + (tid & 63);
+        int len[8], hd = 0;
 #pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                len[k] = 0;
-                if (m < n) {
-                    const int64_t row = (int64_t)k * n + m;
-                    len[k] = ptr[row + 1] - ptr[row];
-                    hd = max(hd, min(len[k], lw));
-                }
+        for (int k = 0; k < 8; ++k) {
+            len[k] = 0;
+            if (m < n) {
+                const int64_t row = (int64_t)k * n + m;
+                len[k] = ptr[row + 1] - ptr[row];
+                hd = max(hd, min(len[k], lw));
             }
-            const int64_t g0 = (int64_t)(m >> 6) * 64 * lw3;   // words of the group
-            const int64_t gv = (int64_t)(m >> 6) * 64 * lw;    // heads of the group
-            int64_t off = 0, voff = 0;
-            for (int w = 0; w < lw3; ++w) {
-                const bool on = 3 * w < hd;
-                const uint64_t mask = __ballot(on);
-                if (mask == 0) break;
+        }
+        const int64_t g0 = (int64_t)(m >> 6) * 64 * lw3;   // words of the group
+        const int64_t gv = (int64_t)(m >> 6) * 64 * lw;    // heads of the group
+        int64_t off = 0, voff = 0;
+        for (int w = 0; w < lw3; ++w) {
+            const bool on = 3 * w < hd;
+            const uint64_t mask = __ballot(on);
+            if (mask == 0) break;
+            I4 ca[3], cb[3];
+#pragma unroll
+            for (int sft = 0; sft < 3; ++sft) {
+                const bool ons = 3 * w + sft < hd;
+                const uint64_t ms = __ballot(ons);
+                const int cs = __popcll(ms);
+                if (ons && (w & 3) == turn) {
+                    const int32_t *u = ecol + unit_entry(gv + voff, cs, lanes_below(ms), 0);
+                    ca[sft] = *reinterpret_cast<const I4 *>(u);
+                    cb[sft] = *reinterpret_cast<const I4 *>(u + 4 * cs);
+                }
+                voff += cs;
+            }
+            if (on && (w & 3) == turn) {
                 U4 wa = (U4)0, wb = (U4)0;
 #pragma unroll
                 for (int sft = 0; sft < 3; ++sft) {
                     const int sl = 3 * w + sft;
-                    const bool ons = sl < hd;
-                    const uint64_t ms = __ballot(ons);
-                    const int cs = __popcll(ms);
-                    if (ons) {
-                        const int rs = lanes_below(ms);
-                        const int32_t *u = ecol + unit_entry(gv + voff, cs, rs, 0);
-                        const I4 ca = *reinterpret_cast<const I4 *>(u);
-                        const I4 cb = *reinterpret_cast<const I4 *>(u + 4 * cs);
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            if (sl < len[k])
-                                wa[k] |= (uint32_t)set.find(ca[k]) << (10 * sft);
-                            if (sl < len[k + 4])
-                                wb[k] |= (uint32_t)set.find(cb[k]) << (10 * sft);
-                        }
+                    for (int k = 0; k < 4; ++k) {
+                        if (sl < min(len[k], lw)) wa[k] |= (uint32_t)set.find(ca[sft][k]) << (10 * sft);
+                        if (sl < min(len[k + 4], lw))
+                            wb[k] |= (uint32_t)set.find(cb[sft][k]) << (10 * sft);
                     }
-                    voff += cs;
                 }
-                if (on) {
-                    const int r = lanes_below(mask), c = __popcll(mask);
-                    *reinterpret_cast<U4 *>(elocal + unit_entry(g0 + off, c, r, 0)) = wa;
-                    *reinterpret_cast<U4 *>(elocal + unit_entry(g0 + off, c, r, 4)) = wb;
-                }
-                off += __popcll(mask);
+                const int r = lanes_below(mask), c = __popcll(mask);
+                *reinterpret_cast<U4 *>(elocal + unit_entry(g0 + off, c, r, 0)) = wa;
+                *reinterpret_cast<U4 *>(elocal + unit_entry(g0 + off, c, r, 4)) = wb;
             }
+            off += __popcll(mask);
         }
     }
     if (tid == 0) {
@@ -856,7 +864,7 @@ hipError_t launch_transpose(const CloudPlan &cp, int precision, void *tmp, size_
     // tiles of 256 arriving nodes (neighbouring tiles on one XCD, whose L2
     // then merges the runs they write into shared rows) x half of the directions
     const dim3 egrid(xcd_grid(blocks_for(n, 256)), 2);
-    hipLaunchKernelGGL(k_tr_count, egrid, dim3(256), 0, s, n, K, mode, cp.nbr, cp.owner, cnt);
+    hipLaunchKernelGGL(k_tr_count, egrid, dim3(kTrCs * 256), 0, s, n, K, mode, cp.nbr, cp.owner, cnt);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = exclusive_scan(scan_tmp, scan_bytes, cnt, cp.tr_ptr, (int)rows, s)) != hipSuccess)
         return e;
@@ -883,9 +891,6 @@ hipError_t launch_transpose(const CloudPlan &cp, int precision, void *tmp, size_
             hipLaunchKernelGGL((k_tr_fill<double, 64>), fgrid, dim3(kTrJs * 64), lds, s, n, K, mode,
                                cp.nbr, cp.owner, (const float *)nullptr, cp.W64, cp.tr_ptr, cnt,
                                cp.tr_col, (double *)cp.tr_val);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_tr_sort<double>, dim3(blocks_for(rows, 8)), dim3(256), 0, s, rows,
-                           cp.tr_ptr, cp.tr_col, (double *)cp.tr_val);
     } else {
         if (wide)
             hipLaunchKernelGGL((k_tr_fill<float, 128>), fgrid, dim3(kTrJs * 128), lds, s, n, K, mode,
@@ -895,25 +900,22 @@ hipError_t launch_transpose(const CloudPlan &cp, int precision, void *tmp, size_
             hipLaunchKernelGGL((k_tr_fill<float, 64>), fgrid, dim3(kTrJs * 64), lds, s, n, K, mode,
                                cp.nbr, cp.owner, cp.W32, (const double *)nullptr, cp.tr_ptr, cnt,
                                cp.tr_col, (float *)cp.tr_val);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-        hipLaunchKernelGGL(k_tr_sort<float>, dim3(blocks_for(rows, 8)), dim3(256), 0, s, rows,
-                           cp.tr_ptr, cp.tr_col, (float *)cp.tr_val);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    return launch_ell_fill(cp, precision, s);
+    return launch_tr_finish(cp, precision, s);
 }
 
-hipError_t launch_ell_fill(const CloudPlan &cp, int precision, hipStream_t s) {
+hipError_t launch_tr_finish(const CloudPlan &cp, int precision, hipStream_t s) {
     if (cp.tr_lw > kEllMaxLw) return hipErrorInvalidValue;
-    const dim3 grid(blocks_for(cp.n, 256)), block(256);
+    const size_t esz = precision == MLBM_FP64 ? sizeof(double) : sizeof(float);
+    const unsigned lds = (unsigned)(16 * kFinPitch * 4 + 4 * kFinRows * (cp.tr_lw | 1) * (4 + esz));
+    const dim3 grid(xcd_grid(head_nodes(cp.n) / kFinRows), 2), block(256);
     if (precision == MLBM_FP64)
-        hipLaunchKernelGGL(k_ell_fill<double>, grid, block, 0, s, cp.n,
-                           cp.tr_lw, cp.tr_ptr, cp.tr_col, (const double *)cp.tr_val, cp.ell_col,
-                           (double *)cp.ell_val);
+        hipLaunchKernelGGL(k_tr_finish<double>, grid, block, lds, s, cp.n, cp.tr_lw, cp.tr_ptr,
+                           cp.tr_col, (double *)cp.tr_val, cp.ell_col, (double *)cp.ell_val);
     else
-        hipLaunchKernelGGL(k_ell_fill<float>, grid, block, 0, s, cp.n,
-                           cp.tr_lw, cp.tr_ptr, cp.tr_col, (const float *)cp.tr_val, cp.ell_col,
-                           (float *)cp.ell_val);
+        hipLaunchKernelGGL(k_tr_finish<float>, grid, block, lds, s, cp.n, cp.tr_lw, cp.tr_ptr,
+                           cp.tr_col, (float *)cp.tr_val, cp.ell_col, (float *)cp.ell_val);
     return hipGetLastError();
 }
 

@@ -29,15 +29,6 @@ __device__ __forceinline__ double dist2(double ax, double ay, double bx, double 
     return dx * dx + dy * dy;
 }
 
-// Orders the LDS accesses of one wavefront: LDS operations of a wavefront
-// complete in issue order, so only the compiler has to be kept from moving
-// accesses across this point.
-__device__ __forceinline__ void wave_lds_sync() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // Index of cell (x, y) along the Hilbert curve of a 2^order x 2^order grid
 // (the classic quadrant-rotation construction).
 __device__ uint32_t hilbert_index(uint32_t x, uint32_t y, int order) {

@@ -285,6 +285,14 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t nblocks) {
 
 inline unsigned xcd_grid(int64_t nblocks) { return (unsigned)(((nblocks + 7) / 8) * 8); }
 
+// Orders the LDS accesses of one wavefront: LDS operations of a wavefront
+// complete in issue order, so only the compiler has to be kept from moving
+// accesses across this point.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 // This workgroup's tile under an XcdSplit, or -1 past the end of its XCD's range.
 __device__ __forceinline__ int64_t xcd_split_tile(const XcdSplit &r) {
@@ -395,7 +403,7 @@ hipError_t launch_l2_final(const double *part, int64_t nparts, double *out, hipS
 size_t transpose_temp_bytes(int n, int K);
 hipError_t launch_transpose(const CloudPlan &cp, int precision, void *tmp, size_t tmp_bytes,
                             hipStream_t s);
-hipError_t launch_ell_fill(const CloudPlan &cp, int precision, hipStream_t s);
+hipError_t launch_tr_finish(const CloudPlan &cp, int precision, hipStream_t s);
 // stats[0] <- largest inverse halo, stats[1] <- tiles without one
 hipError_t launch_adj_tiles(const CloudPlan &cp, int32_t *stats, hipStream_t s);
 hipError_t launch_loss_seed(const CloudPlan &cp, int precision, const void *fT,

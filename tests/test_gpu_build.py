@@ -554,3 +554,52 @@ def test_interpolation_at_ragged_sizes(nx, ny, K, mode):
         terms = W[:, k] * f[nbr[own[:, k]]]
         assert (np.abs(got[k - 1] - terms.sum(1)) <= 2 * K * 2.0 ** -53 * np.abs(terms).sum(1)).all()
     plan.close()
+
+
+@pytest.mark.parametrize("n,frac,width,K,m,precision", [(2000, 0.97, 0.02, 12, 2, 1),
+                                                        (2000, 0.9, 0.05, 20, 3, 1),
+                                                        (1500, 0.9, 0.05, 30, 4, 0)])
+def test_transposed_rows_of_uneven_clouds(n, frac, width, K, m, precision):
+    """Row lengths from none to several hundred (a dense strip whose edge nodes own
+    many departure points), around the 16, 32, 48 and 64 entries that the last
+    pass ranks at a time and beyond, where one lane sorts: row lengths and heads
+    equal the transpose of the forward stencils, sorted by arriving node, and a
+    reversed step equals the one on rows that the host put in order. All exact."""
+    from paper_2306_01525_amd import Params, Plan
+    x, y, period, h = dense_strip(n, frac, width)
+    p = Params(dx=h, K=K, degree=m, tau=0.8, stencil_mode=0, precision=precision, with_adjoint=1)
+    plan = Plan.build(x, y, period, p)
+    perm = plan.export("perm")
+    iperm = np.empty_like(perm)
+    iperm[perm] = np.arange(n)
+    nbr = iperm[plan.export("nbr")[perm]]
+    own = iperm[plan.export("owner")[perm]]
+    ptr, ecol = plan.export("tr_ptr"), plan.export("ell_col")
+    # the rows' weights and tails: a reversed step, bit for bit that of an import
+    # of the same weights, whose rows the host puts in order
+    back = Plan.from_arrays(x[perm], y[perm], nbr, own, plan.export("W")[perm], p)
+    f = plan.init_f(0.02 * np.sin(x) * np.cos(y), -0.02 * np.cos(x) * np.sin(y))
+    lam = torch.linspace(-1.0, 1.0, f.numel(), device="cuda").reshape(f.shape).to(f.dtype)
+    out = []
+    for q in (plan, back):
+        dtau = torch.zeros(1, dtype=torch.float64, device="cuda")
+        out.append((q.step_adjoint(f, lam, torch.empty_like(f), dtau), dtau))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+    back.close()
+    plan.close()
+    lens, lw = np.diff(ptr).reshape(8, n), K + 4
+    say("n %d K %d: rows of up to %d entries, %d above 64, %d empty" % (
+        n, K, lens.max(), (lens > 64).sum(), (lens == 0).sum()))
+    assert lens.max() > 64 and lens.min() == 0
+    hd = np.minimum(lens, lw).max(axis=0)
+    head = _uncompact(ecol, hd, lw, n, -1)
+    for k in range(1, 9):
+        src, arr = nbr[own[:, k]].ravel(), np.repeat(np.arange(n), K)
+        np.testing.assert_array_equal(lens[k - 1], np.bincount(src, minlength=n))
+        order = np.lexsort((arr, src))
+        src, arr = src[order], arr[order]
+        slot = np.arange(src.size) - (np.cumsum(lens[k - 1]) - lens[k - 1])[src]
+        want = np.full((lw, n), -1)
+        want[:] = np.where(np.arange(lw)[:, None] < hd, np.arange(n), -1)   # padding
+        want[slot[slot < lw], src[slot < lw]] = arr[slot < lw]
+        np.testing.assert_array_equal(head[k - 1], want)
