@@ -454,7 +454,8 @@ def run_lbm(steps: int, warmup: int, l2_steps: int, ml_l2: float, ml_ms: float):
     on the regular 512 x 512 lattice of the same Taylor-Green flow (equal
     node count to the MLBM cloud): L2 against the analytic decay after the same
     steps, and the step time (HIP graph of the steps, as for the MLBM); then a
-    2048 x 2048 lattice for the bandwidth figure (72 B per node-update)."""
+    2048 x 2048 lattice for the bandwidth figure: 72 B per node and step, which
+    exceeds the peak where one pass over memory takes several steps."""
     import numpy as np
     import torch
     from paper_2306_01525_amd import targets

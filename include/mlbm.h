@@ -98,7 +98,7 @@ typedef struct {
                                not available through mlbm_import_weights       */
     double rho_wall;
     int32_t with_adjoint;   /* 1: also build the transposed streaming operator
-                               used by mlbm_step_adjoint (8K entries per node;
+                               used by the reversed steps (8K entries per node;
                                8 K n above 2^31 - 1 is MLBM_EUNSUPPORTED)          */
     int32_t fp32_weights_only;  /* 0: the plan keeps the FP64 shape vectors beside
                                the FP32 ones. 1 (MLBM_FP32_DEV only, else
