@@ -256,10 +256,11 @@ constexpr int kFinPitch = 68;   // their stride (16-byte aligned, rows on other 
 // columns, taken from the row in LDS four columns a read. The sorted heads stay
 // in LDS, from where all lanes gather the units, padded with (m, 0) past a row's
 // end, as two 16-byte vectors each; consecutive lanes hold consecutive units.
-// Four rows a wavefront wait for their entries, then for the row in LDS, in turn.
+// Four rows a wavefront are ranked while the next four are on their way (without
+// that 581 us for the 493 below).
 // Sort (by lane exchanges) and heads (each lane walking its own rows in memory) as
-// two passes, and now, us, degree 4, K 30: 10,201 nodes FP32 24 + 82, 23; 90,000
-// FP64 193 + 432, 292; 262,144 FP32 528 + 592, 581 (1.6 GB, 2.8 TB/s).
+// two passes, and now, us, degree 4, K 30: 10,201 nodes FP32 24 + 82, 22; 90,000
+// FP64 193 + 432, 243; 262,144 FP32 528 + 592, 493 (1.6 GB, 3.2 TB/s).
 template <class T>
 __global__ __launch_bounds__(256) void k_tr_finish(int n, int lw, const int32_t *__restrict__ ptr,
                                                    int32_t *col, T *val, int32_t *__restrict__ ecol,
@@ -306,21 +307,27 @@ __global__ __launch_bounds__(256) void k_tr_finish(int n, int lw, const int32_t 
     int32_t *uc = unsorted + wv * 4 * kFinPitch, *hc = hcol + wv * NR * S;
     T *hv = hval + wv * NR * S;
     const int sub = lane >> 4, p16 = lane & 15;
+    // entries of four rows: this lane's, and the longest row of the wavefront's
+    auto fetch = [&](int r, int32_t (&c)[NJ], T (&v)[NJ], int &longest) {
+        const int b = s_row[wv][r], all = s_row[wv][r + 1] - b, len = all <= kFinLen ? all : 0;
+        longest = max(len, __shfl_xor(len, 16));
+        longest = __builtin_amdgcn_readfirstlane(max(longest, __shfl_xor(longest, 32)));
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const bool in = 16 * j + p16 < len;
+            c[j] = in ? col[b + 16 * j + p16] : INT_MAX;
+            v[j] = in ? val[b + 16 * j + p16] : (T)0;
+        }
+    };
+    int32_t c[NJ], cn[NJ] = {};
+    T v[NJ], vn[NJ] = {};
+    int longest, ln = 0;
+    fetch(sub, c, v, longest);
+#pragma unroll
     for (int r4 = 0; r4 < NR; r4 += 4) {
         const int r = r4 + sub, b = s_row[wv][r], all = s_row[wv][r + 1] - b;
         const int len = all <= kFinLen ? all : 0;
-        int longest = max(len, __shfl_xor(len, 16));
-        longest = max(longest, __shfl_xor(longest, 32));
-        longest = __builtin_amdgcn_readfirstlane(longest);
-        int32_t c[NJ];
-        T v[NJ];
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-            if (16 * j < longest) {
-                const bool in = 16 * j + p16 < len;
-                c[j] = in ? col[b + 16 * j + p16] : INT_MAX;
-                v[j] = in ? val[b + 16 * j + p16] : (T)0;
-            }
+        if (r4 + 4 < NR) fetch(r + 4, cn, vn, ln);   // in flight under this turn
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
             if (16 * j < longest) uc[sub * kFinPitch + 16 * j + p16] = c[j];
@@ -366,6 +373,12 @@ __global__ __launch_bounds__(256) void k_tr_finish(int n, int lw, const int32_t 
             }
         }
         wave_lds_sync();   // the next rows take the place of these
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            c[j] = cn[j];
+            v[j] = vn[j];
+        }
+        longest = ln;
     }
     __syncthreads();
     const int l = tid % NR, m = r0 + l, bit = m - m0;
