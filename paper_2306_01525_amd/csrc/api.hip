@@ -996,6 +996,10 @@ hipError_t step_once(const mlbm_plan *plan, const void *gin, void *gout, void *f
 mlbm_status mlbm_init(const mlbm_plan *plan, const double *rho, const double *ux,
                       const double *uy, void *g, hipStream_t s) {
     if (!single(plan) || !g) return fail(MLBM_EINVAL, "null plan or state");
+    if (plan->batched) {
+        MLBM_HIP(launch_init_batch(*plan, rho, ux, uy, g, s));
+        return MLBM_OK;
+    }
     for (const CloudPlan &cp : plan->c)
         MLBM_HIP(launch_init(cp, plan->precision, node_at(rho, cp), node_at(ux, cp),
                              node_at(uy, cp), state_at(plan, g, cp), true, s));
@@ -1005,6 +1009,10 @@ mlbm_status mlbm_init(const mlbm_plan *plan, const double *rho, const double *ux
 mlbm_status mlbm_init_f(const mlbm_plan *plan, const double *rho, const double *ux,
                         const double *uy, void *f, hipStream_t s) {
     if (!single(plan) || !f) return fail(MLBM_EINVAL, "null plan or state");
+    if (plan->batched) {
+        MLBM_HIP(launch_init_batch(*plan, rho, ux, uy, f, s));
+        return MLBM_OK;
+    }
     for (const CloudPlan &cp : plan->c)
         MLBM_HIP(launch_init(cp, plan->precision, node_at(rho, cp), node_at(ux, cp),
                              node_at(uy, cp), state_at(plan, f, cp), false, s));
@@ -1050,6 +1058,10 @@ mlbm_status mlbm_step_record(const mlbm_plan *plan, void *g_a, void *g_b, int32_
 mlbm_status mlbm_moments(const mlbm_plan *plan, const void *g, double *rho, double *ux,
                          double *uy, hipStream_t s) {
     if (!single(plan) || !g) return fail(MLBM_EINVAL, "null plan or state");
+    if (plan->batched) {
+        MLBM_HIP(launch_moments_batch(*plan, g, rho, ux, uy, s));
+        return MLBM_OK;
+    }
     for (const CloudPlan &cp : plan->c)
         MLBM_HIP(launch_moments(cp, plan->precision, state_at(plan, g, cp), out_at(rho, cp),
                                 out_at(ux, cp), out_at(uy, cp), true, s));

@@ -200,6 +200,7 @@ struct Step32Args {
     const uint32_t *nbrL;
     const int32_t *hlist;
     int64_t soff, tile_begin;
+    double rho0_64;          // rho0 as given, for the initial state and the moments
     int32_t *err;            // device error words (may be null)
     const int32_t *perm;     // internal -> user index of this cloud
     int uoff;                // offset of this cloud's nodes in the plan's user order
@@ -374,6 +375,10 @@ hipError_t launch_step(const CloudPlan &cp, int precision, const void *gin, void
 Step32Args step32_args(const CloudPlan &cp, void *frec);
 hipError_t launch_step_batch(const mlbm_plan &plan, const void *gin, void *gout,
                              hipStream_t s);
+hipError_t launch_init_batch(const mlbm_plan &plan, const double *rho, const double *ux,
+                             const double *uy, void *g, hipStream_t s);
+hipError_t launch_moments_batch(const mlbm_plan &plan, const void *g, double *rho, double *ux,
+                                double *uy, hipStream_t s);
 hipError_t launch_set_desc(Step32Args *dst, const Step32Args &v, hipStream_t s);
 hipError_t launch_moments(const CloudPlan &cp, int precision, const void *g, double *rho,
                           double *ux, double *uy, bool post_collision, hipStream_t s);

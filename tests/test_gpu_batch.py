@@ -265,3 +265,34 @@ def test_batches_on_both_sides_of_the_small_cloud_kernel(sides, tile_kernels, mo
         for i in range(len(sides)):
             assert torch.equal(want[i], bp.cloud_view(g, i)), (v, i)
     bp.close()
+
+
+@pytest.mark.parametrize("sides", [(9, 16), (16, 33, 40, 20)])
+@pytest.mark.parametrize("rho0", [1.0, 1.1])
+def test_batched_initial_state_and_moments_equal_single_plans(sides, rho0):
+    """One launch over all tiles (whole, ragged and one-tile clouds; a density that
+    FP32 does not hold exactly) against one launch a cloud: bit for bit."""
+    from paper_2306_01525_amd import Params, Plan
+    clouds, params, u = [], [], []
+    for i, side in enumerate(sides):
+        c = jittered_lattice(side, seed=60 + i)
+        clouds.append((c.x, c.y, c.period, None))
+        params.append(Params(dx=c.h, K=20, degree=3, tau=0.8, stencil_mode=0, rho0=rho0))
+        u.append(tgv_initial_velocity(c.x, c.y, c.period[0], 0.01))
+    bp = Plan.build_batch(clouds, params)
+    rho = [rho0 + 0.01 * a / np.abs(a).max() for a, _ in u]
+    for given in (rho, None):
+        r = None if given is None else np.concatenate(given)
+        ux, uy = np.concatenate([a for a, _ in u]), np.concatenate([b for _, b in u])
+        g, f = bp.init(ux, uy, rho=r), bp.init_f(ux, uy, rho=r)
+        m = bp.moments(g)
+        for i, ((x, y, period, _), p) in enumerate(zip(clouds, params)):
+            sp = Plan.build(x, y, period, p)
+            ri = None if given is None else given[i]
+            gs = sp.init(*u[i], rho=ri)
+            assert torch.equal(gs, bp.cloud_view(g, i)), i
+            assert torch.equal(sp.init_f(*u[i], rho=ri), bp.cloud_view(f, i)), i
+            sl = slice(bp.offsets[i], bp.offsets[i] + bp.sizes[i])
+            assert all(torch.equal(a, b[sl]) for a, b in zip(sp.moments(gs), m)), i
+            sp.close()
+    bp.close()
