@@ -252,8 +252,11 @@ constexpr int kFinPitch = 68;   // their stride (16-byte aligned, rows on other 
 // Last pass over the transposed operator: sorts each CSR row by arriving node and
 // writes the compacted heads. A workgroup takes 16 nodes of a group and half of
 // the directions, one direction a wavefront. Sixteen lanes hold a row; an arriving
-// node appears at most once in it, so an entry's place is the count of smaller
-// columns, taken from the row in LDS four columns a read. The sorted heads stay
+// node appears at most once in it (the stencils that the search finds repeat no
+// member), so an entry's place is the count of smaller columns, taken from the row
+// in LDS four columns a read. SORTED rows come in order, and may hold an arriving
+// node more than once (imported stencils may repeat a member): their entries keep
+// their places. The sorted heads stay
 // in LDS, from where all lanes gather the units, padded with (m, 0) past a row's
 // end, as two 16-byte vectors each; consecutive lanes hold consecutive units.
 // Four rows a wavefront are ranked while the next four are on their way (without
@@ -261,7 +264,7 @@ constexpr int kFinPitch = 68;   // their stride (16-byte aligned, rows on other 
 // Sort (by lane exchanges) and heads (each lane walking its own rows in memory) as
 // two passes, and now, us, degree 4, K 30: 10,201 nodes FP32 24 + 82, 22; 90,000
 // FP64 193 + 432, 243; 262,144 FP32 528 + 592, 493 (1.6 GB, 3.2 TB/s).
-template <class T>
+template <class T, bool SORTED>
 __global__ __launch_bounds__(256) void k_tr_finish(int n, int lw, const int32_t *__restrict__ ptr,
                                                    int32_t *col, T *val, int32_t *__restrict__ ecol,
                                                    T *__restrict__ eval) {
@@ -328,25 +331,32 @@ __global__ __launch_bounds__(256) void k_tr_finish(int n, int lw, const int32_t 
         const int r = r4 + sub, b = s_row[wv][r], all = s_row[wv][r + 1] - b;
         const int len = all <= kFinLen ? all : 0;
         if (r4 + 4 < NR) fetch(r + 4, cn, vn, ln);   // in flight under this turn
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-            if (16 * j < longest) uc[sub * kFinPitch + 16 * j + p16] = c[j];
-        wave_lds_sync();
         int rank[NJ] = {};
-        const int4 *row = reinterpret_cast<const int4 *>(uc + sub * kFinPitch);
-        for (int t = 0; 4 * t < longest; ++t) {   // (filled with INT_MAX to a multiple of 16)
-            const int4 x = row[t];
+        if constexpr (SORTED) {
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) rank[j] = 16 * j + p16;
+        } else {
 #pragma unroll
             for (int j = 0; j < NJ; ++j)
-                if (16 * j < longest)
-                    rank[j] += (x.x < c[j] ? 1 : 0) + (x.y < c[j] ? 1 : 0) + (x.z < c[j] ? 1 : 0) +
-                               (x.w < c[j] ? 1 : 0);
+                if (16 * j < longest) uc[sub * kFinPitch + 16 * j + p16] = c[j];
+            wave_lds_sync();
+            const int4 *row = reinterpret_cast<const int4 *>(uc + sub * kFinPitch);
+            for (int t = 0; 4 * t < longest; ++t) {   // (filled with INT_MAX to a multiple of 16)
+                const int4 x = row[t];
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+                    if (16 * j < longest)
+                        rank[j] += (x.x < c[j] ? 1 : 0) + (x.y < c[j] ? 1 : 0) +
+                                   (x.z < c[j] ? 1 : 0) + (x.w < c[j] ? 1 : 0);
+            }
         }
 #pragma unroll
         for (int j = 0; j < NJ; ++j)
             if (16 * j + p16 < len) {
-                col[b + rank[j]] = c[j];
-                val[b + rank[j]] = v[j];
+                if (!SORTED) {
+                    col[b + rank[j]] = c[j];
+                    val[b + rank[j]] = v[j];
+                }
                 if (rank[j] < lw) {
                     hc[r * S + rank[j]] = c[j];
                     hv[r * S + rank[j]] = v[j];
@@ -355,7 +365,7 @@ __global__ __launch_bounds__(256) void k_tr_finish(int n, int lw, const int32_t 
         // a row longer than that (not met with K <= 48 on clouds of even
         // spacing): an insertion sort by one lane
         if (p16 == 0 && all > kFinLen) {
-            for (int a = b + 1; a < b + all; ++a) {
+            for (int a = b + 1; !SORTED && a < b + all; ++a) {
                 const int ca = col[a];
                 const T va = val[a];
                 int q = a - 1;
@@ -915,20 +925,22 @@ hipError_t launch_transpose(const CloudPlan &cp, int precision, void *tmp, size_
                                cp.tr_col, (float *)cp.tr_val);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    return launch_tr_finish(cp, precision, s);
+    return launch_tr_finish(cp, precision, false, s);
 }
 
-hipError_t launch_tr_finish(const CloudPlan &cp, int precision, hipStream_t s) {
+hipError_t launch_tr_finish(const CloudPlan &cp, int precision, bool sorted, hipStream_t s) {
     if (cp.tr_lw > kEllMaxLw) return hipErrorInvalidValue;
     const size_t esz = precision == MLBM_FP64 ? sizeof(double) : sizeof(float);
     const unsigned lds = (unsigned)(16 * kFinPitch * 4 + 4 * kFinRows * (cp.tr_lw | 1) * (4 + esz));
     const dim3 grid(xcd_grid(head_nodes(cp.n) / kFinRows), 2), block(256);
+    auto k64 = sorted ? k_tr_finish<double, true> : k_tr_finish<double, false>;
+    auto k32 = sorted ? k_tr_finish<float, true> : k_tr_finish<float, false>;
     if (precision == MLBM_FP64)
-        hipLaunchKernelGGL(k_tr_finish<double>, grid, block, lds, s, cp.n, cp.tr_lw, cp.tr_ptr,
-                           cp.tr_col, (double *)cp.tr_val, cp.ell_col, (double *)cp.ell_val);
+        hipLaunchKernelGGL(k64, grid, block, lds, s, cp.n, cp.tr_lw, cp.tr_ptr, cp.tr_col,
+                           (double *)cp.tr_val, cp.ell_col, (double *)cp.ell_val);
     else
-        hipLaunchKernelGGL(k_tr_finish<float>, grid, block, lds, s, cp.n, cp.tr_lw, cp.tr_ptr,
-                           cp.tr_col, (float *)cp.tr_val, cp.ell_col, (float *)cp.ell_val);
+        hipLaunchKernelGGL(k32, grid, block, lds, s, cp.n, cp.tr_lw, cp.tr_ptr, cp.tr_col,
+                           (float *)cp.tr_val, cp.ell_col, (float *)cp.ell_val);
     return hipGetLastError();
 }
 

@@ -785,7 +785,7 @@ mlbm_status mlbm_import_weights(int32_t n, const double *x, const double *y,
             STEP(hipMemcpyAsync(cp.tr_val, v64.data(), sizeof(double) * nnz, hipMemcpyHostToDevice, s));
         else
             STEP(hipMemcpyAsync(cp.tr_val, v32.data(), sizeof(float) * nnz, hipMemcpyHostToDevice, s));
-        STEP(launch_tr_finish(cp, p.precision, s));
+        STEP(launch_tr_finish(cp, p.precision, true, s));
     }
 #undef STEP
     st = enqueue_tables(cp, plan->stats, s);

@@ -408,7 +408,8 @@ hipError_t launch_l2_final(const double *part, int64_t nparts, double *out, hipS
 size_t transpose_temp_bytes(int n, int K);
 hipError_t launch_transpose(const CloudPlan &cp, int precision, void *tmp, size_t tmp_bytes,
                             hipStream_t s);
-hipError_t launch_tr_finish(const CloudPlan &cp, int precision, hipStream_t s);
+// sorted: the rows are in order (and may repeat an arriving node)
+hipError_t launch_tr_finish(const CloudPlan &cp, int precision, bool sorted, hipStream_t s);
 // stats[0] <- largest inverse halo, stats[1] <- tiles without one
 hipError_t launch_adj_tiles(const CloudPlan &cp, int32_t *stats, hipStream_t s);
 hipError_t launch_loss_seed(const CloudPlan &cp, int precision, const void *fT,

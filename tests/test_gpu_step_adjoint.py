@@ -270,3 +270,47 @@ def test_several_reversed_steps_equal_single_ones_and_oracle(case, precision):
     if precision == 1:
         assert abs(float(total) - gt_o) <= tol * abs(gt_o)
     plan.close()
+
+
+@pytest.mark.parametrize("order", ["lattice", "scattered"])
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("precision", [1, 0])
+def test_imported_stencils_may_repeat_a_member(precision, mode, order):
+    """Members repeated in every stencil, the weight split between the places: a
+    transposed row then holds an arriving node several times. In lattice order the
+    tiles have inverse halos; with the nodes numbered at random a tile's 256 nodes
+    are read from all over the cloud, more than an inverse halo holds, and rows are
+    gathered from global memory. Gradient against the oracle's on the same stencils
+    within the bounds of the imported-weights test."""
+    from paper_2306_01525_amd import Params, Plan
+    c, u0x, u0y, tx, ty, K, m, _ = _setup(n_side=48, seed=29)
+    nbr, own, W = oracle.build_plan(c, 1.0, K, m, mode)
+    nbr = np.concatenate([nbr, nbr[:, [0, 5, 5]]], axis=1)
+    W = np.concatenate([W, W[:, :, [0, 5, 5]]], axis=2)
+    W[:, :, 0] *= 0.25
+    W[:, :, K] *= 0.75
+    W[:, :, 5] *= 0.5
+    W[:, :, K + 1:] *= 0.25
+    if order == "scattered":
+        at = np.random.Generator(np.random.PCG64(8)).permutation(c.n)   # new index of a node
+        old = np.argsort(at)
+        nbr, own, W = at[nbr[old]], at[own[old]], W[old]
+        u0x, u0y, tx, ty = u0x[old], u0y[old], tx[old], ty[old]
+        c.x, c.y = c.x[old], c.y[old]
+    tau, steps = 0.7, 3
+    _, gx_o, gy_o, gt_o = oracle.adjoint(nbr, own, W, tau, steps, 1.0, u0x, u0y, tx, ty)
+    plan = Plan.from_arrays(c.x, c.y, nbr, own, W,
+                            Params(dx=1.0, K=K + 3, degree=m, tau=tau, stencil_mode=mode,
+                                   precision=precision, with_adjoint=1))
+    halos = plan.export("tdescT")
+    say("%s mode %d prec %d: inverse halos of %d to %d nodes" % (order, mode, precision,
+                                                              halos.min(), halos.max()))
+    assert (halos == 0).all() if order == "scattered" else (halos > 0).all()
+    J, gx, gy, gt = _gpu_grad(plan, u0x, u0y, tx, ty, steps, 2)
+    eg = rel_l2(np.concatenate([gx, gy]), np.concatenate([gx_o, gy_o]))
+    say("  grad u0 rel %.2e, dtau %.6e vs %.6e" % (eg, gt, gt_o))
+    assert eg < (1e-10 if precision == 1 else 2e-6)
+    if precision == 1:
+        assert abs(gt - gt_o) <= 1e-10 * abs(gt_o)
+    assert plan.device_error() == 0
+    plan.close()
