@@ -605,11 +605,15 @@ mlbm_status build_weights_lanes(const mlbm_cloud *clouds, const mlbm_params *par
     if (st != MLBM_OK) return cleanup(st);
     int32_t singular;
     st = finish_tables(plan, &singular, s);
+    if (st == MLBM_OK) st = check_singular(singular);
     if (st != MLBM_OK) return cleanup(st);
     st = build_batch(plan, s);
     if (st != MLBM_OK) return cleanup(st);
-    st = check_singular(singular);
-    if (st != MLBM_OK) return cleanup(st);
+    // a batched plan's descriptors follow the records that finish_tables waits for
+    if (plan->batched && !capturing(s)) {
+        e = hipStreamSynchronize(s);
+        if (e != hipSuccess) return cleanup(hip_fail(e, "hipStreamSynchronize"));
+    }
     *out = plan;
     return MLBM_OK;
 }

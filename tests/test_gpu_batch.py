@@ -296,3 +296,43 @@ def test_batched_initial_state_and_moments_equal_single_plans(sides, rho0):
             assert all(torch.equal(a, b[sl]) for a, b in zip(sp.moments(gs), m)), i
             sp.close()
     bp.close()
+
+
+def test_batched_build_has_finished_when_the_call_returns():
+    """The C entry point alone, without the binding's own wait: once
+    mlbm_build_weights returns, the stream has nothing left to do, and the plan can
+    be initialised and stepped on another stream at once. 48 clouds, whose
+    descriptors are 96 launches behind the tables."""
+    import ctypes
+    from paper_2306_01525_amd import Params, Plan, _lib
+    c, ux, uy = tgv_case(16, 12, 2, 1, seed=4)
+    nc = 48
+    clouds = [(c.x, c.y, c.period, None)] * nc
+    params = [Params(dx=c.h, K=12, degree=2, tau=0.8, stencil_mode=1) for _ in range(nc)]
+    L = _lib.load()
+    carr, keep = Plan._clouds(clouds, "cuda")
+    parr = (_lib.Params * nc)(*[p.to_c() for p in params])
+    pb, wb = ctypes.c_size_t(), ctypes.c_size_t()
+    assert L.mlbm_weights_query(carr, parr, nc, ctypes.byref(pb), ctypes.byref(wb)) == 0
+    buf = torch.empty(pb.value, dtype=torch.uint8, device="cuda")
+    ws = torch.empty(wb.value, dtype=torch.uint8, device="cuda")
+    u, v = (torch.tensor(np.tile(a, nc), device="cuda") for a in (ux, uy))
+    a, b = (torch.empty(9 * nc * c.n, dtype=torch.float32, device="cuda") for _ in range(2))
+    one, other = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    h, rb = ctypes.c_void_p(), ctypes.c_int32()
+    st = L.mlbm_build_weights(carr, parr, nc, buf.data_ptr(), pb.value, ws.data_ptr(), wb.value,
+                              ctypes.byref(h), one.cuda_stream)
+    done = one.query()
+    assert st == 0 and done
+    assert L.mlbm_init(h, None, u.data_ptr(), v.data_ptr(), a.data_ptr(), other.cuda_stream) == 0
+    assert L.mlbm_step(h, a.data_ptr(), b.data_ptr(), 2, ctypes.byref(rb), other.cuda_stream) == 0
+    other.synchronize()
+    sp = Plan.build(c.x, c.y, c.period, params[0])
+    g = sp.step(sp.init(ux, uy), sp.new_state(), 2)
+    assert rb.value == 0
+    for k in range(nc):
+        assert torch.equal(a[9 * k * c.n: 9 * (k + 1) * c.n].view(9, c.n), g), k
+    torch.cuda.synchronize()
+    L.mlbm_plan_destroy(h)
+    sp.close()
