@@ -346,8 +346,8 @@ mlbm_status mlbm_step_adjoint(const mlbm_plan *plan, const void *f_n, const void
  * with lamf_b, *result_in_b (host) = 1 when the adjoint before the first is in
  * lamf_b. Instead of a sum per step, dJ/dtau is kept in partial sums: parts
  * (device FP64 [mlbm_adjoint_parts], caller-owned) is overwritten by the first
- * reversed step when `first` is not 0 and added to otherwise, so several calls
- * can share it; mlbm_adjoint_tau then adds their sum into dJ_dtau (device FP64
+ * reversed step when `first` is not 0 (cleared if the call has none) and added
+ * to otherwise, so several calls can share it; mlbm_adjoint_tau then adds their sum into dJ_dtau (device FP64
  * [1]). The sums do not depend on how the steps are cut into calls.
  * mlbm_adjoint_parts returns 0 for a plan without the adjoint. */
 int64_t mlbm_adjoint_parts(const mlbm_plan *plan);

@@ -1217,8 +1217,11 @@ mlbm_status mlbm_steps_adjoint(const mlbm_plan *plan, const void *f_rec, int32_t
     const CloudPlan *cp = single(plan);
     mlbm_status st = check_adjoint(cp, plan);
     if (st != MLBM_OK) return st;
-    if (!f_rec || !lamf_a || !lamf_b || !parts || n_steps < 0) return fail(MLBM_EINVAL, "null argument");
+    if (!f_rec || !lamf_a || !lamf_b || !parts) return fail(MLBM_EINVAL, "null argument");
     if (lamf_a == lamf_b) return fail(MLBM_EINVAL, "adjoint buffers must differ");
+    if (n_steps < 0) return fail(MLBM_EINVAL, "negative step count");
+    if (first && n_steps == 0)   // no step overwrites the sums: they are zero
+        MLBM_HIP(launch_fill_i32((int32_t *)parts, 0, 2 * adjoint_parts(cp->n), s));
     const size_t sb = (size_t)kQ * plan->n_total * state_elem_bytes(plan->precision);
     void *cur = lamf_a, *nxt = lamf_b;
     for (int32_t t = n_steps - 1; t >= 0; --t) {

@@ -314,3 +314,33 @@ def test_imported_stencils_may_repeat_a_member(precision, mode, order):
         assert abs(gt - gt_o) <= 1e-10 * abs(gt_o)
     assert plan.device_error() == 0
     plan.close()
+
+
+def test_an_empty_first_call_of_reversed_steps_clears_the_sums():
+    """steps_adjoint of no steps leaves the adjoint in place and its parts zero,
+    whatever their memory held; a later call adds to them, bit for bit what one
+    call gives. A negative count is refused by name."""
+    import ctypes
+    from paper_2306_01525_amd import MLBMError, Params, Plan, _lib
+    c, u0x, u0y, tx, ty, K, m, mode = _setup(n_side=17, seed=3)
+    plan = Plan.build(c.x, c.y, c.period, Params(dx=1.0, K=K, degree=m, tau=0.8, precision=1,
+                                                 with_adjoint=1))
+    f = plan.init_f(u0x, u0y)
+    rec = torch.stack([f, 1.01 * f])
+    lam = torch.linspace(-1.0, 1.0, f.numel(), dtype=f.dtype, device="cuda").reshape(f.shape)
+    ref, _, whole = plan.steps_adjoint(rec, 2, lam.clone(), torch.empty_like(f))
+    parts = torch.full_like(whole, float("nan"))
+    a, b = lam.clone(), torch.empty_like(f)
+    rb = ctypes.c_int32(7)
+    st = torch.cuda.current_stream().cuda_stream
+    call = _lib.load().mlbm_steps_adjoint
+    assert call(plan._h, rec.data_ptr(), 0, a.data_ptr(), b.data_ptr(), parts.data_ptr(), 1,
+                ctypes.byref(rb), st) == 0
+    assert rb.value == 0 and torch.equal(a, lam) and (parts == 0).all()
+    got, _, parts = plan.steps_adjoint(rec, 2, a, b, parts)
+    assert torch.equal(got, ref) and torch.equal(parts, whole)
+    empty = plan.steps_adjoint(rec, 0, a, b)[2]
+    assert float(plan.adjoint_tau(empty, torch.ones(1, dtype=torch.float64, device="cuda"))) == 1.0
+    with pytest.raises(MLBMError, match="negative"):
+        plan.steps_adjoint(rec, -1, a, b)
+    plan.close()
