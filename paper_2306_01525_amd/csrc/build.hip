@@ -1252,10 +1252,19 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(3))) void k_
 // 5.0e-16 of an interpolated field. Blocks of eight multiply-adds instead of
 // four (fewer wait states) measured the same.
 //
-// A system with a pivot near the singularity threshold is left to k_rbf_redo,
-// whose general elimination decides whether it is singular: `redo` gets its
-// owner. The line, 1e6 eps (8 K + M), is at least 1e3 times that threshold
-// (1e3 eps |Phi|, with distances of at most 2 stencil radii).
+// A system that may be singular by the rule of the general elimination (a pivot
+// of at most 1e3 eps |Phi|) is left to k_rbf_redo, which decides by that rule:
+// `redo` gets its owner. Nodes nearly on one curve of the polynomials' degree
+// leave a small pivot u in P; the elimination of Phi then meets a pivot near u^2
+// (its inverse holds R / u^2), so the line for u lies at 1e-4, where u^2 is a
+// hundred times the largest threshold. Nodes close together leave a small pivot
+// in S, which is of the size of Phi's: its line is 1e6 eps (8 K + M), at least
+// 1e3 times the threshold (distances are at most 2 stencil radii). Over 40,000
+// systems of pairs, clusters, strips and curves of all sizes, 12,641 of them
+// refused, the refused ones had u below 5e-7 or a pivot of S below 2e-4 of its
+// line. Jittered lattices have u above 2e-2 from K = M + 3 on and above 2e-4 at
+// K = M.
+constexpr double kSetPivot = 1e-4;
 
 // acc[i] += (NEG ? -1 : 1) src(lane L0 + i) m for i < C <= 4, the lane taken within each
 // group of sixteen. The wait states that a DPP read of a fresh result needs
@@ -1469,7 +1478,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
         sy[h] *= irad;
         monomials<M>(sx[h], sy[h], P[h]);
     }
-    const double line = 1e6 * DBL_EPSILON * (8 * K + M);
+    const double line = 1e6 * DBL_EPSILON * (8 * K + M);   // for the pivots of S
     bool bad = false;
     auto store_row = [&](int at, int h) {
         double *o = rows + at * RS;
@@ -1510,7 +1519,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
 #pragma unroll
         for (int c = 0; c < M; ++c)
             if (c >= t) U[c] = rows[t * RS + c];
-        if (!(fabs(U[t]) > line)) bad = true;
+        if (!(fabs(U[t]) > kSetPivot)) bad = true;
         const double pi = recip(U[t]);
         if (ll == t) uinv = pi;
 #pragma unroll

@@ -603,3 +603,31 @@ def test_transposed_rows_of_uneven_clouds(n, frac, width, K, m, precision):
         want[:] = np.where(np.arange(lw)[:, None] < hd, np.arange(n), -1)   # padding
         want[slot[slot < lw], src[slot < lw]] = arr[slot < lw]
         np.testing.assert_array_equal(head[k - 1], want)
+
+
+@pytest.mark.parametrize("K,m,width,seed", [(9, 2, 3.16e-4, 7), (12, 2, 3e-4, 9),
+                                            (14, 3, 5.6e-3, 8), (17, 4, 3.4e-2, 9)])
+def test_strips_too_thin_for_the_polynomials_are_refused(K, m, width, seed):
+    """Nodes of an open strip so thin that some systems' smallest pivot, in the
+    elimination of the whole system, lies below the singularity threshold (0.02 to
+    0.2 of it), while the polynomials' own pivots are only near its square root:
+    refused by the oracle and by the build. Four times as wide, both accept it."""
+    from types import SimpleNamespace
+    from paper_2306_01525_amd import MLBMError, Params, Plan
+    n = 80
+    for scale in (1, 4):
+        r = np.random.default_rng(seed)
+        x = np.linspace(0, 1, n) + r.uniform(-0.3, 0.3, n) / n
+        y = scale * width * r.uniform(-1, 1, n) * K / n
+        c = SimpleNamespace(x=x, y=y, period=(0.0, 0.0), n=n)
+        p = Params(dx=0.01, K=K, degree=m, tau=0.8, stencil_mode=1, precision=1)
+        say("K %d degree %d width %.1e" % (K, m, scale * width))
+        if scale == 1:
+            with pytest.raises(np.linalg.LinAlgError):
+                oracle.build_plan(c, 0.01, K, m, 1)
+            with pytest.raises(MLBMError) as ei:
+                Plan.build(x, y, c.period, p)
+            assert ei.value.status == -2
+        else:
+            oracle.build_plan(c, 0.01, K, m, 1)
+            Plan.build(x, y, c.period, p).close()
