@@ -1831,20 +1831,22 @@ hipError_t launch_fill_i32(int32_t *p, int32_t v, int64_t n, hipStream_t s) {
 
 // Workspace of the search and the solve: owner counts [n] (then the list of
 // owners to solve again, n + 1), list offsets [n + 1] (the search's list before
-// that), points [8 n] (the sort's counters before that), scan.
+// that), points [8 n] (the sort's counters before that), scan. Counts and
+// offsets share what n and n + 1 words take when each starts a 256-byte line:
+// a fixed workspace that held a build without the lists still holds it.
 struct OwnedLists {
     int32_t *cnt, *ptr, *pts;
     char *scan;
     size_t scan_bytes;
+    static size_t lines(size_t bytes) { return (bytes + 255) & ~size_t(255); }
+    static size_t head(int n) { return lines((size_t)n * 4) + lines(((size_t)n + 1) * 4); }
+    static size_t points(int n) { return lines((size_t)8 * n * 4); }
     OwnedLists(void *tmp, size_t bytes, int n) {
-        const size_t a = (((size_t)n + 1) * 4 + 255) & ~size_t(255);
-        char *b = (char *)tmp;
-        cnt = (int32_t *)b;
-        ptr = (int32_t *)(b + a);
-        pts = (int32_t *)(b + 2 * a);
-        const size_t head = 2 * a + (((size_t)8 * n * 4 + 255) & ~size_t(255));
-        scan = b + head;
-        scan_bytes = bytes - head;
+        cnt = (int32_t *)tmp;
+        ptr = cnt + (((size_t)n + 1 + 3) & ~size_t(3));
+        pts = (int32_t *)((char *)tmp + head(n));
+        scan = (char *)pts + points(n);
+        scan_bytes = bytes - (size_t)(scan - (char *)tmp);
     }
 };
 
@@ -1946,10 +1948,7 @@ static hipError_t launch_rbf_null(const Geo *geo, const double *xs, const double
 }
 
 size_t rbf_temp_bytes(int n) {
-    const size_t a = (((size_t)n + 1) * 4 + 255) & ~size_t(255);
-    const size_t b = (((size_t)n + 1) * 4 + 255) & ~size_t(255);
-    const size_t c = ((size_t)8 * n * 4 + 255) & ~size_t(255);
-    return a + b + c + scan_temp_bytes(n) + 256;
+    return OwnedLists::head(n) + OwnedLists::points(n) + scan_temp_bytes(n) + 256;
 }
 
 hipError_t launch_rbf(const Geo *geo, const double *xs, const double *ys,

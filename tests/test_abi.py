@@ -82,6 +82,19 @@ def test_fp32_weights_only_moves_the_fp64_shape_vectors_to_the_workspace():
     assert _lib.load().mlbm_import_query(n, ctypes.byref(p), ctypes.byref(size)) == -5
 
 
+def test_workspace_of_a_build_that_fills_the_static_array():
+    """16,448 nodes, K 31, degree 2, FP32 weights only, on a 1:2 domain: the build's
+    workspace is the 32 MiB of mlbm_build_weights_static to the byte."""
+    from paper_2306_01525_amd import _lib
+    p = _lib.Params(dx=0.001, K=31, degree=2, tau=0.8, rho0=1.0, rho_wall=1.0,
+                    fp32_weights_only=1)
+    cl = _lib.Cloud(16448, None, None, None, 1.0, 0.5, None, None)
+    pb, wb = ctypes.c_size_t(), ctypes.c_size_t()
+    assert _lib.load().mlbm_weights_query(ctypes.byref(cl), ctypes.byref(p), 1,
+                                          ctypes.byref(pb), ctypes.byref(wb)) == 0
+    assert wb.value <= 32 << 20
+
+
 PLAN_CALLS = {   # entry point -> its arguments after the plan (pointers null)
     "mlbm_plan_get_info": [None],
     "mlbm_plan_export": [0, 0, None, 0],
