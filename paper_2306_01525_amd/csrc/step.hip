@@ -1292,19 +1292,32 @@ void launch_wide(const CloudPlan &cp, int dirs, const void *gin, void *gout, voi
 
 // Directions a lane takes in the small-cloud step, 0 for the tile kernels.
 // One (32 nodes a workgroup) as long as that gives every CU at most one
-// workgroup; two (64 nodes) until the halos that each workgroup stages for
-// itself cost more than the tile kernels' unfilled chip. us per step at K 30 on
-// 8,100 / 12,100 / 44,100 / 57,600 / 102,400 / 144,400 nodes (K 15 at 102,400):
-//   FP32 tile kernel 8.9 / 8.9 / 16.1 / 16.8 / 12.5 / 25.7
-//   FP32 one         5.5 / 6.4 / 13.1 / 16.2 / 17.8 / 32.4
-//   FP32 two         6.8 / 6.9 / 13.1 / 16.3 / 16.8 / 31.3
-//   FP64 tile kernel 37.6 / 38.3 / 40.8 / 41.9 / 29.4 / 58.3
-//   FP64 one         6.2 / 8.2 / 20.8 / 25.1 / 27.2 / 69.6
-//   FP64 two         7.1 / 7.5 / 20.1 / 24.2 / 25.8 / 61.9
-// At K 12 to 15 FP32 breaks even near 50,000 nodes and FP64 near 110,000.
-inline int wide_dirs(int n, int precision) {
-    if (n <= 8192) return 1;
-    return n <= (precision == MLBM_FP64 ? 102400 : 49152) ? 2 : 0;
+// workgroup, in FP32 up to three; two (64 nodes) until the halos that each
+// workgroup stages for itself cost more than the tile kernels' unfilled chip. us
+// per step, of the FP32 tile kernels the fastest variant, paper stencils:
+//   FP32 K 30 at 8,464 / 17,956 / 24,649 / 40,000 / 48,841 nodes
+//     one 5.8 / 7.0 / 8.2 / 12.0 / 14.4, two 6.4 / 8.6 / 8.9 / 12.6 / 14.1, tile 8.7 / 10.3 / 13.2 / 16.0 / 16.6
+//   FP32 K 15 at 17,956 / 24,649 / 33,124 / 48,841
+//     one 5.8 / 6.4 / 8.0 / 10.0, two 6.5 / 6.6 / 7.8 / 8.3, tile 6.3 / 6.5 / 8.9 / 9.0
+//   FP64 K 30 at 8,100 / 12,100 / 44,100 / 102,400 / 144,400
+//     one 6.2 / 8.2 / 20.8 / 27.2 / 69.6, two 7.1 / 7.5 / 20.1 / 25.8 / 61.9, tile 38 / 38 / 41 / 29 / 58
+// Staging the halo does not shrink with K, so short stencils return to the tile
+// kernels earlier (two, tile): FP32 K 10 at 24,649 nodes 5.6, 5.6 and at 40,000
+// 6.7, 6.3; K 12 at 40,000 6.9, 7.0 and at 48,841 6.9, 6.7. FP64 K 6 at 65,536
+// nodes 10.2, 13.1 and at 78,400 (own stencils) 14.4, 13.2; own K 10 and 12 at
+// 90,000 18.9, 18.9 and 20.3, 21.5, at 102,400 21.9, 19.6 and 23.1, 22.1; K 48 at
+// 102,400 78.0, 76.3.
+// Batches of K below 18 return at 32,768 nodes, counted in whole tiles: K 12 at
+// 30,752 5.7, 6.2 and at 40,000 6.7, 6.4; K 15 at 30,752 6.4, 6.6 and at 45,000
+// 7.8, 6.9; K 18 at 45,000 8.4, 9.9.
+inline int wide_dirs(int64_t n, int K, int precision, bool batch = false) {
+    if (precision == MLBM_FP64) {
+        if (n <= 8192) return 1;
+        return n <= (K <= 8 ? 65536 : K <= 12 ? 90112 : K <= 44 ? 102400 : 94208) ? 2 : 0;
+    }
+    if (n <= 24576) return 1;
+    const int most = batch && K < 18 ? 32768 : K <= 12 ? 40960 : 49152;
+    return K > 10 && n <= most ? 2 : 0;
 }
 
 template <int MODE, int D>
@@ -1318,13 +1331,15 @@ void launch_wide_batch(const mlbm_plan &plan, const void *gin, void *gout, hipSt
                        (const float *)gin, (float *)gout, nb, nh);
 }
 
-// Small batches take the small-cloud kernel by the rule of a single cloud of as
-// many tiles, whatever the variant. K 20 to 30, us a step, best tile kernel and
-// this: 2 clouds of 3,232 nodes together 9.5 and 5.1, 8 of 15,247 9.7 and 6.6, 4
-// of 38,054 16.7 and 12.9; 8 of 76,924 nodes stay with the tile kernels (18.5).
+// Small batches take the small-cloud kernel by their tiles and shortest stencils,
+// whatever the variant. K 20 to 30, us a step, best tile kernel and this: 2 clouds
+// of 3,232 nodes together 9.5 and 5.1, 8 of 15,247 9.7 and 6.6, 4 of 38,054 16.7
+// and 12.9; 8 of 76,924 nodes stay with the tile kernels (18.5).
 template <int MODE>
 void launch32_batch_v(const mlbm_plan &plan, const void *gin, void *gout, hipStream_t s) {
-    if (const int dirs = wide_dirs((int)std::min<int64_t>(plan.total_tiles * kTile, INT32_MAX), MLBM_FP32_DEV)) {
+    int K = kMaxK;
+    for (const CloudPlan &cp : plan.c) K = std::min(K, cp.K);
+    if (const int dirs = wide_dirs(plan.total_tiles * kTile, K, MLBM_FP32_DEV, true)) {
         if (dirs == 1) launch_wide_batch<MODE, 1>(plan, gin, gout, s);
         else launch_wide_batch<MODE, 2>(plan, gin, gout, s);
         return;
@@ -1348,7 +1363,7 @@ hipError_t step_variant(const CloudPlan &cp, int precision, const void *gin, voi
                         void *frec, hipStream_t s) {
     const int n = cp.n;
     const int64_t nblocks = (n + kTile - 1) / kTile;
-    if (const int dirs = wide_dirs(n, precision)) {
+    if (const int dirs = wide_dirs(n, cp.K, precision)) {
         if (precision == MLBM_FP64)
             launch_wide<double, MODE, FORCE, WALL, REC>(cp, dirs, gin, gout, frec, s);
         else

@@ -359,3 +359,42 @@ def test_bounce_back_on_whole_tiles_matches_oracle(prec):
         f = oracle.run(f, nbr, own, W, tau, steps - (1 if ref else 0), ax, ay, links=links)
         ref[steps] = oracle.moments(f)
     _compare(ref, got, (lambda s: TOL_FP64) if prec else tol_fp32, "bounce/f%d" % (64 if prec else 32))
+
+
+# either side of the lines that depend on K: FP32 24,576 nodes (one direction a
+# lane, then two, or whole tiles up to K 10), 40,960 up to K 12; FP64 65,536 up to
+# K 8, 90,112 up to K 12, 94,208 from K 45
+LINE_CASES = [
+    (156, 157, 10, 2, 1, 0), (157, 157, 10, 2, 1, 0), (156, 157, 13, 2, 0, 0),
+    (157, 157, 13, 2, 0, 0), (202, 202, 12, 2, 0, 0), (203, 202, 12, 2, 0, 0),
+    (256, 256, 8, 2, 1, 1), (257, 256, 8, 2, 1, 1), (300, 300, 12, 2, 0, 1),
+    (301, 300, 12, 2, 0, 1), (307, 306, 45, 2, 1, 1), (307, 307, 45, 2, 1, 1),
+]
+
+
+@pytest.mark.parametrize("nx,ny,K,m,mode,prec", LINE_CASES,
+                         ids=["%dx%d-K%d-%d-f%d" % (a, b, k, o, 64 if p else 32)
+                              for a, b, k, _, o, p in LINE_CASES])
+def test_step_kernels_on_either_side_of_the_lines_in_k(nx, ny, K, m, mode, prec):
+    """As the test of the edges of their sizes."""
+    test_step_kernels_at_the_edges_of_their_sizes(nx, ny, K, m, mode, prec)
+
+
+@pytest.mark.parametrize("nclouds,side", [(8, 64), (4, 91)])
+def test_batched_step_on_either_side_of_its_line(nclouds, side):
+    """32,768 nodes in whole tiles and a little more, K 15: the small-cloud kernel and
+    the tile kernels, every cloud bitwise as its single-cloud plan."""
+    from paper_2306_01525_amd import Plan
+    clouds, params, u = [], [], []
+    for k in range(nclouds):
+        c, ux, uy = tgv_case(side, 15, 2, 0, seed=k, jitter=0.2)
+        clouds.append((c.x, c.y, c.period, None))
+        params.append(_params(c.h, 15, 2, 0, 0, 0.8))
+        u.append((ux, uy))
+    bp = Plan.build_batch(clouds, params)
+    g = bp.step(bp.init(*(np.concatenate(a) for a in zip(*u))), bp.new_state(), 3)
+    for k in (0, nclouds - 1):
+        sp = Plan.build(*clouds[k][:3], params[k])
+        assert torch.equal(sp.step(sp.init(*u[k]), sp.new_state(), 3), bp.cloud_view(g, k)), k
+        sp.close()
+    bp.close()
