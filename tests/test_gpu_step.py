@@ -398,3 +398,32 @@ def test_batched_step_on_either_side_of_its_line(nclouds, side):
         assert torch.equal(sp.step(sp.init(*u[k]), sp.new_state(), 3), bp.cloud_view(g, k)), k
         sp.close()
     bp.close()
+
+
+@pytest.mark.parametrize("wall", [1, 2])
+def test_tile_kernel_variants_agree_with_walls_and_force(wall):
+    """The FP32 tile kernels with force and equilibrium or bounce-back walls, plain
+    and recording, above the sizes of the small-cloud step, whose plans all run one
+    kernel: bitwise the same states from every variant."""
+    from paper_2306_01525_amd import Plan
+    c = annulus_case(0.0107)
+    assert c.n > 49152
+    r = np.hypot(c.x, c.y)
+    s = np.where(r < 1.5, -1.0, 1.0)
+    plan = Plan.build(c.x, c.y, c.period,
+                      _params(0.01, 20, 3, 0, 0, 0.7, force_kind=1, force_mag=1e-5, wall_kind=wall,
+                              rho_wall=1.0), node_type=c.node_type,
+                      normals=(s * c.x / r, s * c.y / r) if wall == 2 else None)
+    ux, uy = -1e-3 * (r - 1) * (2 - r) * c.y / r, 1e-3 * (r - 1) * (2 - r) * c.x / r
+    ref = None
+    for v in range(10):
+        plan.set_variant(v)
+        g = plan.step(plan.init(ux, uy), plan.new_state(), 3)
+        rec = torch.empty((3, 9, plan.n), dtype=g.dtype, device=g.device)
+        assert torch.equal(plan.step_record(plan.init(ux, uy), plan.new_state(), 3, rec), g), v
+        if ref is None:
+            ref = (g.clone(), rec)
+        assert torch.equal(g, ref[0]) and torch.equal(rec, ref[1]), v
+    say("wall", wall, "n", c.n, "largest |g|", float(g.abs().max()))
+    assert plan.device_error() == 0
+    plan.close()
