@@ -600,18 +600,14 @@ __global__ __launch_bounds__(1024) void k_adj_tiles(int n, int lw, int hcap, int
 // tau partial, h = 1 stores lambda_5..8.
 //
 // GR groups make a workgroup: four (a whole tile) where the tiles fill the
-// chip, one where they do not (adj_groups), each with the halo of its tile. The
-// small form (GR = 1) also takes a chunk of four triples at a time, asking for
-// the first one's weights before it waits for the halo, where the large one
-// goes triple by triple and lets its many wavefronts overlap. A step of
-// mlbm_steps_adjoint, GR = 4 -> 1 (us, FP32 / FP64, degree 4 and K = 30 where
-// not said): 1,600 nodes (K = 20) 10.2 -> 10.0 / 11.7 -> 10.7, 6,400 (K = 25)
-// 13.9 -> 12.1 / 23.7 -> 14.7, 14,400 17.7 -> 13.0 / 28.1 -> 16.1, 40,000
-// 19.1 -> 17.4 / 30.5 -> 27.3, 90,000 29.0 -> 28.3 / 55.7 -> 57.7, 262,144
-// 66 -> 82 / 132 -> 164: the small form stages four halos where the large one
-// stages one. What is left of a small step is its chain of dependent trips (row
-// bounds, units, halo, moments); loads of the moments and of the row bounds'
-// ends moved ahead of the walk measured 9.6 in FP32 and 16.4 in FP64 at 1,600.
+// chip, two or one where they do not (adj_groups), each with the halo of its tile.
+// FP32 pairs and FP64 single groups take a chunk of C = 4 triples at a time, asking
+// for the first one's weights before they wait for the halo; the others go triple
+// by triple and let their many wavefronts overlap (FP64 pairs with chunks of four
+// measured 5 to 10 % slower, FP32 ones without 5 to 25 %). FP32 pairs and whole
+// tiles fetch UN = 4 halo nodes a lane at a time, which costs registers that FP64
+// pays for. What is left of a small step is its chain of dependent trips (row
+// bounds, units, halo, moments).
 // A large step is bound by the traffic of the heads: 262,144 nodes FP32 read
 // about 0.42 GB in 66 us, 6.3 TB/s.
 template <class T, int GR>
@@ -623,6 +619,8 @@ __global__ __launch_bounds__(128 * GR) void k_adj_step(
     const uint32_t *__restrict__ elocal, int hcap, double rtau, double rho0, int dev,
     double *__restrict__ part, int add, int32_t *err) {
     constexpr int NTH = 128 * GR, PER = kTile / 64 / GR;   // workgroups per tile
+    constexpr int C = GR < 4 && (GR == 1 || sizeof(T) == 4) ? 4 : 1;
+    constexpr int UN = GR == 4 || sizeof(T) == 4 ? 4 : 1;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ T s_x[GR][2][4][64];   // row sums exchanged between the halves
     __shared__ T s_m[GR][4][64];      // moments of f^n, from half 0 to half 1
@@ -668,7 +666,6 @@ __global__ __launch_bounds__(128 * GR) void k_adj_step(
     const int64_t gv = grp * 64 * lw, gw = grp * 64 * lw3;
     int64_t voff = 0, woff = 0;
     // the words and weights of triples w .. w + C - 1, this lane's or zero
-    constexpr int C = GR == 1 ? 4 : 1;
     U4 wd[C];
     T4 v[C][3];
     auto triples = [&](int w) {
@@ -693,14 +690,14 @@ __global__ __launch_bounds__(128 * GR) void k_adj_step(
             }
         }
     };
-    if (GR == 1 && ni > 0) {
+    if (C > 1 && ni > 0) {
         __syncthreads();
         hmax = max(hmax, s_hd[gq][1 - hv][lane]);
         triples(0);
     }
     if (ni > 0) {
         const int32_t *il = ilist + (int64_t)t * hcap;
-#pragma unroll 4
+#pragma unroll UN
         for (int h = tid; h < ni; h += NTH) {
             int q = il[h];
             if ((unsigned)q >= (unsigned)n) {   // a bad table must not fault
@@ -720,7 +717,7 @@ __global__ __launch_bounds__(128 * GR) void k_adj_step(
     if (ni > 0) {
         const T *Lh = L + 4 * hv * ni;
         for (int w = 0; w < ntrip; w += C) {
-            if (GR > 1 || w > 0) triples(w);
+            if (C == 1 || w > 0) triples(w);
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 if (w + c >= ntrip) break;
@@ -961,18 +958,33 @@ hipError_t launch_loss_seed(const CloudPlan &cp, int precision, const void *fT,
     return hipGetLastError();
 }
 
-// Groups per workgroup of the reversed step. The small form is the faster one up
-// to 40,000 nodes in both precisions and the slower one in FP64 at 90,000
-// (figures at k_adj_step); 192 tiles are still less than one a CU.
-static int adj_groups(int n) { return n <= 49152 ? 1 : kTile / 64; }
+// Groups per workgroup of the reversed step. us a step of mlbm_steps_adjoint, one /
+// two / four groups (the form of the precision; FP32 takes no single groups):
+//   nodes    FP32 K 6     K 12         K 30         FP64 K 6            K 12                K 30
+//   1,600    7.4 / 7.1    8.7 / 8.4    10.5 / 12.0  8.1 / 7.4 / 8.1     9.6 / 8.9 / 9.9     12 / 14 / 17
+//   16,384   8.0 / 9.0    9.4 / 10.7   12.9 / 16.8  9.3 / 10.0 / 11.8   11.3 / 12.4 / 15.3  16 / 19 / 27
+//   32,761   8.5 / 9.4    10.1 / 11.2  14.6 / 17.4  11.6 / 10.5 / 12.4  15.0 / 13.1 / 16.4  22 / 21 / 29
+//   40,000   9.7 / 9.5    12.1 / 11.5  16.9 / 17.8  13.1 / 12.5 / 12.5  17.5 / 16.7 / 16.7  27 / 29 / 29
+//   48,841   9.9 / 9.7    12.7 / 11.8  17.8 / 18.6  13.6 / 12.9 / 12.8  18.1 / 17.1 / 17.1  29 / 31 / 31
+//   65,536   10.6 / 10.2  14.0 / 12.6  20.7 / 21.0  16.0 / 13.8 / 13.7  22 / 19 / 18        48 / 33 / 33
+// FP64 K 48 at 40,000 nodes 50 / 42 / 42.
+static int adj_groups(const CloudPlan &cp, int precision) {
+    const int n = cp.n, K = cp.K;
+    if (precision != MLBM_FP64) return n <= (K < 24 ? 36864 : 49152) ? 2 : 4;
+    if (n <= 20480) return 1;
+    if (n <= 36864) return 2;
+    return n <= 49152 && K >= 18 && K <= 40 ? 1 : 4;
+}
 
-int64_t adjoint_parts(int n) { return blocks_for(n, 64 * adj_groups(n)); }
+int64_t adjoint_parts(const CloudPlan &cp, int precision) {
+    return blocks_for(cp.n, 64 * adj_groups(cp, precision));
+}
 
 template <class T, int GR>
 static void launch_adj(const CloudPlan &cp, int dev, const void *fn, const void *lam_next,
                        void *lam_n, double *part, bool add, hipStream_t s) {
     const unsigned lds = cp.adj_ni ? (unsigned)(8 * cp.adj_ni * sizeof(T)) : 0;
-    hipLaunchKernelGGL((k_adj_step<T, GR>), dim3(xcd_grid(adjoint_parts(cp.n))), dim3(128 * GR), lds,
+    hipLaunchKernelGGL((k_adj_step<T, GR>), dim3(xcd_grid(blocks_for(cp.n, 64 * GR))), dim3(128 * GR), lds,
                        s, cp.n, (const T *)fn, (const T *)lam_next, (T *)lam_n, cp.tr_ptr, cp.tr_col,
                        (const T *)cp.tr_val, cp.tr_lw, cp.ell_col, (const T *)cp.ell_val,
                        cp.adj_ni ? cp.tdescT : nullptr, cp.ilist, cp.elocal, cp.hcap,
@@ -982,19 +994,21 @@ static void launch_adj(const CloudPlan &cp, int dev, const void *fn, const void 
 hipError_t launch_step_adjoint(const CloudPlan &cp, int precision, const void *fn,
                                const void *lam_next, void *lam_n, double *part, bool add,
                                hipStream_t s) {
-    const bool whole = adj_groups(cp.n) == kTile / 64;
+    const int groups = adj_groups(cp, precision);
     if (precision == MLBM_FP64)
-        whole ? launch_adj<double, kTile / 64>(cp, 0, fn, lam_next, lam_n, part, add, s)
-              : launch_adj<double, 1>(cp, 0, fn, lam_next, lam_n, part, add, s);
+        groups == 1 ? launch_adj<double, 1>(cp, 0, fn, lam_next, lam_n, part, add, s)
+        : groups == 2 ? launch_adj<double, 2>(cp, 0, fn, lam_next, lam_n, part, add, s)
+                      : launch_adj<double, 4>(cp, 0, fn, lam_next, lam_n, part, add, s);
     else
-        whole ? launch_adj<float, kTile / 64>(cp, 1, fn, lam_next, lam_n, part, add, s)
-              : launch_adj<float, 1>(cp, 1, fn, lam_next, lam_n, part, add, s);
+        groups == 2 ? launch_adj<float, 2>(cp, 1, fn, lam_next, lam_n, part, add, s)
+                    : launch_adj<float, 4>(cp, 1, fn, lam_next, lam_n, part, add, s);
     return hipGetLastError();
 }
 
-hipError_t launch_adjoint_tau(const CloudPlan &cp, const double *part, double *dtau,
+hipError_t launch_adjoint_tau(const CloudPlan &cp, int precision, const double *part, double *dtau,
                               hipStream_t s) {
-    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(256), 0, s, adjoint_parts(cp.n), part, dtau, 1);
+    hipLaunchKernelGGL(k_sum_final, dim3(1), dim3(256), 0, s,
+                       adjoint_parts(cp, precision), part, dtau, 1);
     return hipGetLastError();
 }
 

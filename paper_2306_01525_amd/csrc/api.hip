@@ -1202,13 +1202,13 @@ mlbm_status mlbm_step_adjoint(const mlbm_plan *plan, const void *f_n, const void
     if (st != MLBM_OK) return st;
     if (lamf_next == lamf_n) return fail(MLBM_EINVAL, "adjoint buffers must differ");
     MLBM_HIP(launch_step_adjoint(*cp, plan->precision, f_n, lamf_next, lamf_n, plan->scratch64, false, s));
-    MLBM_HIP(launch_adjoint_tau(*cp, plan->scratch64, dJ_dtau, s));
+    MLBM_HIP(launch_adjoint_tau(*cp, plan->precision, plan->scratch64, dJ_dtau, s));
     return MLBM_OK;
 }
 
 int64_t mlbm_adjoint_parts(const mlbm_plan *plan) {
     const CloudPlan *cp = single(plan);
-    return cp && check_adjoint(cp, plan) == MLBM_OK ? adjoint_parts(cp->n) : 0;
+    return cp && check_adjoint(cp, plan) == MLBM_OK ? adjoint_parts(*cp, plan->precision) : 0;
 }
 
 mlbm_status mlbm_steps_adjoint(const mlbm_plan *plan, const void *f_rec, int32_t n_steps,
@@ -1221,7 +1221,7 @@ mlbm_status mlbm_steps_adjoint(const mlbm_plan *plan, const void *f_rec, int32_t
     if (lamf_a == lamf_b) return fail(MLBM_EINVAL, "adjoint buffers must differ");
     if (n_steps < 0) return fail(MLBM_EINVAL, "negative step count");
     if (first && n_steps == 0)   // no step overwrites the sums: they are zero
-        MLBM_HIP(launch_fill_i32((int32_t *)parts, 0, 2 * adjoint_parts(cp->n), s));
+        MLBM_HIP(launch_fill_i32((int32_t *)parts, 0, 2 * adjoint_parts(*cp, plan->precision), s));
     const size_t sb = (size_t)kQ * plan->n_total * state_elem_bytes(plan->precision);
     void *cur = lamf_a, *nxt = lamf_b;
     for (int32_t t = n_steps - 1; t >= 0; --t) {
@@ -1239,7 +1239,7 @@ mlbm_status mlbm_adjoint_tau(const mlbm_plan *plan, const double *parts, double 
     mlbm_status st = check_adjoint(cp, plan);
     if (st != MLBM_OK) return st;
     if (!parts || !dJ_dtau) return fail(MLBM_EINVAL, "null argument");
-    MLBM_HIP(launch_adjoint_tau(*cp, parts, dJ_dtau, s));
+    MLBM_HIP(launch_adjoint_tau(*cp, plan->precision, parts, dJ_dtau, s));
     return MLBM_OK;
 }
 

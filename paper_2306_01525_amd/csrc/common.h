@@ -415,12 +415,12 @@ hipError_t launch_adj_tiles(const CloudPlan &cp, int32_t *stats, hipStream_t s);
 hipError_t launch_loss_seed(const CloudPlan &cp, int precision, const void *fT,
                             const double *uxt, const double *uyt, void *lam, double *J,
                             double *part, hipStream_t s);
-// part: adjoint_parts(n) partial sums of dJ/dtau, overwritten or added to
-int64_t adjoint_parts(int n);
+// part: adjoint_parts partial sums of dJ/dtau, overwritten or added to
+int64_t adjoint_parts(const CloudPlan &cp, int precision);
 hipError_t launch_step_adjoint(const CloudPlan &cp, int precision, const void *fn,
                                const void *lam_next, void *lam_n, double *part, bool add,
                                hipStream_t s);
-hipError_t launch_adjoint_tau(const CloudPlan &cp, const double *part, double *dtau,
+hipError_t launch_adjoint_tau(const CloudPlan &cp, int precision, const double *part, double *dtau,
                               hipStream_t s);   // dtau += sum of the parts
 hipError_t launch_init_adjoint(const CloudPlan &cp, int precision, const double *u0x,
                                const double *u0y, const void *lam0, double *gx, double *gy,

@@ -344,3 +344,19 @@ def test_an_empty_first_call_of_reversed_steps_clears_the_sums():
     with pytest.raises(MLBMError, match="negative"):
         plan.steps_adjoint(rec, -1, a, b)
     plan.close()
+
+
+# either side of the lines between the reversed step's workgroups of one, two and
+# four groups of 64 nodes: FP64 20,480 and 36,864 nodes, or 49,152 for K 18 to 40;
+# FP32 36,864, or 49,152 from K 24
+GROUP_CASES = [(64, 64, 12, 2, 1), (143, 143, 12, 2, 0), (144, 143, 12, 2, 0), (192, 192, 12, 2, 1),
+               (193, 192, 12, 2, 1), (193, 192, 24, 3, 0), (222, 222, 24, 3, 0),
+               (193, 192, 41, 2, 1)]
+
+
+@pytest.mark.parametrize("case", GROUP_CASES, ids=["%dx%d-K%d-mode%d" % (
+    c[0], c[1], c[2], c[4]) for c in GROUP_CASES])
+@pytest.mark.parametrize("precision", [1, 0])
+def test_reversed_steps_on_either_side_of_the_lines(case, precision):
+    """As the test of several reversed steps."""
+    test_several_reversed_steps_equal_single_ones_and_oracle(case, precision)
