@@ -249,6 +249,57 @@ constexpr int kFinRows = 16;    // nodes of a workgroup of k_tr_finish
 constexpr int kFinLen = 64;     // row entries ranked in LDS; longer rows take one lane
 constexpr int kFinPitch = 68;   // their stride (16-byte aligned, rows on other banks)
 
+// Sorts a row by column (no two equal), one wavefront, in place: blocks of 64
+// entries are ranked and merged into the sorted part before them, whose entries
+// move up by the count of smaller columns in the block, from the end, 64 at a time
+// (an entry moves by at most 64 places, so what a turn overwrites has been read).
+// blk: 64 words of LDS. Clouds of a few dense clusters, whose edge nodes own most of
+// the departure points, have rows of hundreds to thousands of entries: 20,000 nodes
+// in eight clusters, rows of up to 2,305, the whole pass 1.9 ms; 1,250 with an
+// insertion sort by one lane a row, which k_tr_finish takes sixteen of in turn.
+template <class T>
+__device__ void sort_long_row(int lane, int len, int32_t *col, T *val, int32_t *blk) {
+    for (int done = 0; done < len; done += 64) {
+        const bool in = lane < len - done;
+        const int32_t c = in ? col[done + lane] : INT_MAX;
+        const T v = in ? val[done + lane] : (T)0;
+        int rank = 0, lo = 0;
+        for (int j = 0; j < 64; ++j) rank += __builtin_amdgcn_readlane(c, j) < c ? 1 : 0;
+        if (!in) rank = lane;   // the pads, behind all others
+        blk[rank] = c;
+        wave_lds_sync();
+        if (in) {   // smaller entries of the sorted part
+            int hi = done;
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (col[mid] < c) lo = mid + 1;
+                else hi = mid;
+            }
+        }
+        for (int t = done - 64; t >= 0; t -= 64) {   // (done is a multiple of 64)
+            const int32_t e = col[t + lane];
+            const T ev = val[t + lane];
+            int up = 0, end = 64;
+            while (up < end) {
+                const int mid = (up + end) >> 1;
+                if (blk[mid] < e) up = mid + 1;
+                else end = mid;
+            }
+            if (up > 0) {
+                col[t + lane + up] = e;
+                val[t + lane + up] = ev;
+            }
+            if (__ballot(up > 0) == 0) break;   // nothing below moves either
+        }
+        if (in) {
+            col[lo + rank] = c;
+            val[lo + rank] = v;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");   // read by other lanes next
+        wave_lds_sync();
+    }
+}
+
 // Last pass over the transposed operator: sorts each CSR row by arriving node and
 // writes the compacted heads. A workgroup takes 16 nodes of a group and half of
 // the directions, one direction a wavefront. Sixteen lanes hold a row; an arriving
@@ -362,26 +413,6 @@ __global__ __launch_bounds__(256) void k_tr_finish(int n, int lw, const int32_t 
                     hv[r * S + rank[j]] = v[j];
                 }
             }
-        // a row longer than that (not met with K <= 48 on clouds of even
-        // spacing): an insertion sort by one lane
-        if (p16 == 0 && all > kFinLen) {
-            for (int a = b + 1; !SORTED && a < b + all; ++a) {
-                const int ca = col[a];
-                const T va = val[a];
-                int q = a - 1;
-                while (q >= b && col[q] > ca) {
-                    col[q + 1] = col[q];
-                    val[q + 1] = val[q];
-                    --q;
-                }
-                col[q + 1] = ca;
-                val[q + 1] = va;
-            }
-            for (int e = 0; e < lw; ++e) {
-                hc[r * S + e] = col[b + e];
-                hv[r * S + e] = val[b + e];
-            }
-        }
         wave_lds_sync();   // the next rows take the place of these
 #pragma unroll
         for (int j = 0; j < NJ; ++j) {
@@ -389,6 +420,19 @@ __global__ __launch_bounds__(256) void k_tr_finish(int n, int lw, const int32_t 
             v[j] = vn[j];
         }
         longest = ln;
+    }
+    // rows longer than that (not met with K <= 48 on clouds of even spacing)
+    const int mine = s_row[wv][p16 + 1] - s_row[wv][p16];
+    if (__ballot(mine > kFinLen) != 0) {
+        for (int r = 0; r < NR; ++r) {
+            const int b = s_row[wv][r], all = s_row[wv][r + 1] - b;
+            if (all <= kFinLen) continue;   // uniform
+            if (!SORTED) sort_long_row(lane, all, col + b, val + b, uc);
+            for (int e = lane; e < lw; e += 64) {
+                hc[r * S + e] = col[b + e];
+                hv[r * S + e] = val[b + e];
+            }
+        }
     }
     __syncthreads();
     const int l = tid % NR, m = r0 + l, bit = m - m0;

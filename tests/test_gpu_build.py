@@ -631,3 +631,39 @@ def test_strips_too_thin_for_the_polynomials_are_refused(K, m, width, seed):
         else:
             oracle.build_plan(c, 0.01, K, m, 1)
             Plan.build(x, y, c.period, p).close()
+
+
+@pytest.mark.parametrize("n,K,m,precision", [(2500, 12, 2, 1), (2500, 20, 3, 0), (9000, 12, 2, 0)])
+def test_transposed_rows_of_clustered_clouds(n, K, m, precision):
+    """Four dense clusters in a sparse cloud: departure points leave a cluster for the
+    nodes at its edge, whose rows hold hundreds to thousands of entries, several
+    blocks of 64. Row lengths against the stencils, and a reversed step, bit for
+    bit, that of an import of the same weights, whose rows the host puts in order
+    and nothing reorders."""
+    from paper_2306_01525_amd import Params, Plan
+    r = np.random.default_rng(3)
+    at, which = r.uniform(0.2, 0.8, (4, 2)), r.integers(0, 4, n)
+    q = at[which] + 0.002 * r.standard_normal((n, 2))
+    q[:n // 10] = r.uniform(0, 1, (n // 10, 2))
+    x, y, period, h = q[:, 0] % 1, q[:, 1] % 1, (1.0, 1.0), n ** -0.5
+    p = Params(dx=h, K=K, degree=m, tau=0.8, stencil_mode=0, precision=precision, with_adjoint=1)
+    plan = Plan.build(x, y, period, p)
+    perm = plan.export("perm")
+    iperm = np.empty_like(perm)
+    iperm[perm] = np.arange(n)
+    nbr, own = iperm[plan.export("nbr")[perm]], iperm[plan.export("owner")[perm]]
+    lens = np.diff(plan.export("tr_ptr")).reshape(8, n)
+    for k in range(1, 9):
+        np.testing.assert_array_equal(lens[k - 1], np.bincount(nbr[own[:, k]].ravel(), minlength=n))
+    say("n %d K %d: rows of up to %d entries, %d above 64, %d above 256" % (
+        n, K, lens.max(), (lens > 64).sum(), (lens > 256).sum()))
+    assert lens.max() > 256
+    back = Plan.from_arrays(x[perm], y[perm], nbr, own, plan.export("W")[perm], p)
+    f = plan.init_f(0.02 * np.sin(x) * np.cos(y), -0.02 * np.cos(x) * np.sin(y))
+    lam = torch.linspace(-1.0, 1.0, f.numel(), device="cuda").reshape(f.shape).to(f.dtype)
+    out = []
+    for one in (plan, back):
+        dtau = torch.zeros(1, dtype=torch.float64, device="cuda")
+        out.append((one.step_adjoint(f, lam, torch.empty_like(f), dtau), dtau))
+        one.close()
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
