@@ -415,7 +415,7 @@ mlbm_status build_cloud(mlbm_plan *plan, CloudPlan &cp, const mlbm_cloud &c,
                            cp.geo, bw.keys, bw.skeys, bw.vals, bw.cstart, bw.cend, bw.sort_tmp,
                            bw.rbf_tmp, bw.sort_bytes, bw.rbf_bytes, cp.perm, cp.iperm, cp.xs, cp.ys,
                            cp.ntype}, s));
-    MLBM_HIP(launch_knn(cp.geo, cp.xs, cp.ys, cp.perm, cp.iperm, bw.cstart, bw.cend, n, p.K,
+    MLBM_HIP(launch_knn(cp.geo, cp.xs, cp.ys, cp.perm, bw.cstart, bw.cend, n, p.K,
                         bw.rbf_tmp, bw.rbf_bytes, cp.nbr, s));
     // (the shape vectors are not solved yet: their place takes the points' slots)
     if (p.stencil_mode == MLBM_STENCIL_PAPER)

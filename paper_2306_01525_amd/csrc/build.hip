@@ -265,105 +265,44 @@ __device__ __forceinline__ void for_ring(const Geo &g, const int32_t *__restrict
     }
 }
 
-// Stencil of node p: p itself, then the K-1 closest other nodes by
-// (squared distance, user index). Rings of cells are scanned outwards until
-// every unscanned node is provably farther than the current (K-1)-th. One
-// lane a node; it serves the nodes that k_knn leaves.
-template <int KMAX>
-__device__ __forceinline__ void knn_by_rings(const Geo &g, const double *__restrict__ xs,
-                                             const double *__restrict__ ys,
-                                             const int32_t *__restrict__ perm,
-                                             const int32_t *__restrict__ iperm,
-                                             const int32_t *__restrict__ cstart,
-                                             const int32_t *__restrict__ cend, int n, int K, int p,
-                                             int32_t *__restrict__ nbr) {
-    const int live = K - 1, first = KMAX - live;
-    double bd[KMAX];
-    int bu[KMAX];
-#pragma unroll
-    for (int q = 0; q < KMAX; ++q) {
-        bd[q] = q < first ? -1.0 : DBL_MAX;
-        bu[q] = q < first ? -1 : INT_MAX;
-    }
-    const double px = xs[p], py = ys[p];
-    int cx, cy;
-    cell_of(g, px, py, cx, cy);
-    const double cmin = fmin(g.cw, g.ch);
-    for (int r = 0;; ++r) {
-        bool wraps = (g.Lx > 0.0 && 2 * r + 1 > g.gx) || (g.Ly > 0.0 && 2 * r + 1 > g.gy);
-        if (wraps) {  // tiny periodic grid: rings would revisit cells, scan all nodes
-#pragma unroll
-            for (int q = 0; q < KMAX; ++q) {   // static indices keep the list in registers
-                bd[q] = q < first ? bd[q] : DBL_MAX;
-                bu[q] = q < first ? bu[q] : INT_MAX;
-            }
-            for (int q = 0; q < n; ++q)
-                if (q != p) topk_insert<KMAX>(bd, bu, dist2(px, py, xs[q], ys[q], g.Lx, g.Ly), perm[q]);
-            break;
-        }
-        // (the ring is walked here rather than through for_ring, whose
-        // closure would take the list's address)
-        const int count = r == 0 ? 1 : 8 * r;
-        for (int t = 0; t < count; ++t) {
-            const int c = ring_cell(g, cx, cy, r, t);
-            if (c < 0) continue;
-            const int e = cend[c];
-            for (int q = cstart[c]; q < e; ++q)
-                if (q != p) topk_insert<KMAX>(bd, bu, dist2(px, py, xs[q], ys[q], g.Lx, g.Ly), perm[q]);
-        }
-        double reach = r * cmin;
-        if (bd[KMAX - 1] < reach * reach) break;
-        if (r > g.gx && r > g.gy) break;
-    }
-    nbr[p] = p;
-#pragma unroll
-    for (int q = 0; q < KMAX; ++q)
-        if (q >= first) nbr[(int64_t)(q - first + 1) * n + p] = iperm[bu[q]];
-}
+// LDS of the group of lanes that looks for one node's stencil.
+struct KnnList {
+    double *d;       // [CAP] squared distances of the listed nodes
+    int *q;          // [CAP] the nodes
+    int *cnt;
+    unsigned *occ;   // [2]
+};
 
-
-__global__ __launch_bounds__(64) void k_knn_redo(
-    const Geo *__restrict__ geo, const double *__restrict__ xs, const double *__restrict__ ys,
-    const int32_t *__restrict__ perm, const int32_t *__restrict__ iperm,
-    const int32_t *__restrict__ cstart, const int32_t *__restrict__ cend, int n, int K,
-    const int32_t *__restrict__ redo, int32_t *__restrict__ nbr) {
-    const int count = min(redo[0], n);
-    for (int i = blockIdx.x * 64 + threadIdx.x; i < count; i += gridDim.x * 64)
-        knn_by_rings<kMaxK>(*geo, xs, ys, perm, iperm, cstart, cend, n, K, redo[1 + i], nbr);
-}
-
-// The same stencils, eight lanes a node. The nodes within a radius that
-// should hold a few more than K - 1 (from the count of the 5 x 5 cells around)
-// are listed in LDS; a list that comes out short, or longer than CAP, is taken
-// again with another radius. The place of an entry in the stencil is then the
-// number of entries before it, counted by comparing it with all of them: five
-// entries a lane and one LDS read for every entry of the list. (Inserting each
-// candidate into a sorted list in registers costs every lane of a wavefront a
-// pass over the list whenever one lane takes it, and one lane a node leaves a
-// small cloud's few wavefronts waiting for cells and nodes in turn: 909 us
-// against 209 on 262,144 nodes, K 30, and 182 against 20 on 10,201, K 25.)
-// Equal distances are decided by the user index in a second pass, which only
-// lists that have them (lattices) take. Lists that no radius brings into [K - 1, CAP] (more than
-// CAP nodes at one distance) go to k_knn_redo.
-constexpr int kKnnLanes = 8;
-template <int CAP>
-__global__ __launch_bounds__(256) void k_knn(
-    const Geo *__restrict__ geo, const double *__restrict__ xs, const double *__restrict__ ys,
-    const int32_t *__restrict__ perm, const int32_t *__restrict__ cstart,
-    const int32_t *__restrict__ cend, int n, int K, int32_t *__restrict__ redo,
-    int32_t *__restrict__ nbr) {
-    constexpr int G = kKnnLanes, QB = 256 / G, E = CAP / G;
-    __shared__ double s_d[QB][CAP + 1];   // (odd strides: the groups read distinct banks)
-    __shared__ int s_q[QB][CAP + 1];
-    __shared__ int s_cnt[QB];
-    __shared__ unsigned s_occ[QB][2];
-    const int64_t nb = ((int64_t)n + QB - 1) / QB, blk = xcd_tile(nb);
-    if (blk >= nb) return;
-    const Geo g = *geo;
-    const int grp = threadIdx.x / G, gl = threadIdx.x % G;
-    const int64_t pt = blk * QB + grp;
-    const bool live = pt < n;
-    const int p = live ? (int)pt : n - 1;
+// Stencil of node p: p itself, then the K - 1 closest other nodes by (squared
+// distance, user index), by G lanes of a wavefront (all of its lanes take part;
+// groups of lanes have nodes of their own, and live tells whether there is one).
+// The nodes within a radius that should hold a few more than K - 1 (from the count
+// of the 5 x 5 cells around) are listed in LDS; a list that comes out short, or
+// longer than CAP, is taken again with another radius. The place of an entry in
+// the stencil is then the number of entries before it, counted by comparing it with
+// all of them: CAP / G entries a lane and one LDS read for every entry of the list.
+// Equal distances are decided by the user index in a second pass, which only lists
+// that have them (lattices) take.
+// A whole wavefront (G = 64) shares crowded cells among its lanes, takes the third
+// and later radii from the counts of 32 shells between radii known to hold too few
+// and too many (a node outside a dense part of an uneven cloud meets hundreds of
+// nodes within a thousandth of the radius), and where no radius brings the list
+// into [K - 1, CAP] (more than CAP nodes at one distance) finds the nodes one after
+// another. Eight lanes give up, and return false with nothing written, after four
+// radii, at a crowded cell, or at a block of cells too large for them.
+constexpr int kCrowded = 64;        // nodes of a cell
+constexpr int kManyCells = 1024;    // cells of a block; also nodes where a block would wrap
+template <int CAP, int G>
+__device__ __forceinline__ bool knn_by_radius(const Geo &g, const double *__restrict__ xs,
+                                              const double *__restrict__ ys,
+                                              const int32_t *__restrict__ perm,
+                                              const int32_t *__restrict__ cstart,
+                                              const int32_t *__restrict__ cend, int n, int K, int p,
+                                              bool live, const KnnList &l,
+                                              int32_t *__restrict__ nbr) {
+    constexpr bool WAVE = G == 64;
+    constexpr int E = (CAP + G - 1) / G, TRIES = WAVE ? 16 : 4;
+    const int gl = threadIdx.x % G;
     const double px = xs[p], py = ys[p];
     const bool perx = g.Lx > 0.0, pery = g.Ly > 0.0;
     int cx, cy;
@@ -380,7 +319,7 @@ __global__ __launch_bounds__(256) void k_knn(
         int sum = 0, cells = 0;
         if (g.gx >= 5 && g.gy >= 5) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) {
+            for (int t = 0; t < (24 + G) / G; ++t) {
                 const int i = gl + t * G;
                 const int c = i < 25 ? cell(cx + i % 5 - 2, cy + i / 5 - 2) : -1;
                 if (c >= 0) {
@@ -397,70 +336,154 @@ __global__ __launch_bounds__(256) void k_knn(
         const double per_cell = cells ? (double)sum / cells : (double)n / ((double)g.gx * g.gy);
         lim2 = (1.15 * need + 5.0) / (3.14159265 * per_cell) * g.cw * g.ch;
     }
-    int cnt = 0;
-    bool ok = false;
-    double lo2 = 0.0, hi2 = DBL_MAX;   // squared radii known to hold too few, too many
-    for (int tries = 0; tries < 16 && !ok; ++tries) {
-        if (gl == 0) s_cnt[grp] = 0;
-        wave_lds_sync();
-        auto take = [&](int q) {
-            const double d = dist2(px, py, xs[q], ys[q], g.Lx, g.Ly);
-            if (d < lim2 && q != p) {
-                const int at = atomicAdd(&s_cnt[grp], 1);
-                if (at < CAP) {
-                    s_d[grp][at] = d;
-                    s_q[grp][at] = q;
-                }
-            }
-        };
-        // every node closer than the radius lies at most rx, ry cells away
-        // (the margin covers the rounding of a node's cell)
+    // take(q) for every node closer than the radius, and for some beyond it; false if
+    // this is not for eight lanes
+    auto each_near = [&](auto &&take) {
+        // they lie at most rx, ry cells away (the margin covers the rounding of a
+        // node's cell)
         const double lim = sqrt(lim2) * (1.0 + 1e-9);
         const double fx = floor(lim / g.cw) + 1.0, fy = floor(lim / g.ch) + 1.0;
         if ((perx && 2.0 * fx + 1.0 > g.gx) || (pery && 2.0 * fy + 1.0 > g.gy)) {
+            if (!WAVE && n > kManyCells) return false;
             for (int q = gl; q < n; q += G) take(q);   // a block would meet cells twice
-        } else {
-            // (an open grid: the block ends at its edge)
-            const int rx = (int)fmin(fx, (double)g.gx), ry = (int)fmin(fy, (double)g.gy);
-            const int x0 = perx ? cx - rx : max(cx - rx, 0);
-            const int x1 = perx ? cx + rx : min(cx + rx, g.gx - 1);
-            const int y0 = pery ? cy - ry : max(cy - ry, 0);
-            const int y1 = pery ? cy + ry : min(cy + ry, g.gy - 1);
-            const int w = x1 - x0 + 1, count = w * (y1 - y0 + 1);
-            int ix = gl % w, iy = gl / w;
-            const int sx = G % w, sy = G / w;
-            for (int t = gl; t < count; t += G) {
+            return true;
+        }
+        // (an open grid: the block ends at its edge)
+        const int rx = (int)fmin(fx, (double)g.gx), ry = (int)fmin(fy, (double)g.gy);
+        const int x0 = perx ? cx - rx : max(cx - rx, 0);
+        const int x1 = perx ? cx + rx : min(cx + rx, g.gx - 1);
+        const int y0 = pery ? cy - ry : max(cy - ry, 0);
+        const int y1 = pery ? cy + ry : min(cy + ry, g.gy - 1);
+        const int w = x1 - x0 + 1, count = w * (y1 - y0 + 1);
+        if (!WAVE && count > kManyCells) return false;
+        int ix = gl % w, iy = gl / w;
+        const int sx = G % w, sy = G / w;
+        bool crowded = false;
+        for (int t = gl; (WAVE ? t - gl : t) < count; t += G) {
+            int b = 0, e = 0;
+            if (!WAVE || t < count) {
                 const int c = cell(x0 + ix, y0 + iy);
-                const int e = cend[c];
-                for (int q = cstart[c]; q < e; ++q) take(q);
-                ix += sx;
-                iy += sy;
-                if (ix >= w) {
-                    ix -= w;
-                    ++iy;
+                b = cstart[c];
+                e = cend[c];
+            }
+            const bool shared = WAVE && e - b > 8;
+            if (!WAVE && e - b > kCrowded) {
+                crowded = true;
+                e = b;
+            }
+            if (!shared)
+                for (int q = b; q < e; ++q) take(q);
+            if (WAVE) {
+                for (uint64_t m = __ballot(shared); m != 0; m &= m - 1) {
+                    const int from = __builtin_ctzll(m);
+                    const int be = __builtin_amdgcn_readlane(e, from);
+                    for (int q = __builtin_amdgcn_readlane(b, from) + gl; q < be; q += G) take(q);
                 }
             }
+            ix += sx;
+            iy += sy;
+            if (ix >= w) {
+                ix -= w;
+                ++iy;
+            }
         }
+        return !crowded;
+    };
+    constexpr int BINS = 32;   // (in the list's place)
+    int cnt = 0, below = 0;
+    bool ok = false;
+    double lo2 = 0.0, hi2 = DBL_MAX;   // squared radii known to hold too few (below), too many
+    for (int tries = 0; tries < TRIES && !ok; ++tries) {
+        if (WAVE && tries >= 2 && hi2 < DBL_MAX) {
+            for (int b = gl; b < BINS; b += G) l.q[b] = 0;
+            wave_lds_sync();
+            const double width = (hi2 - lo2) / BINS;
+            lim2 = hi2;
+            each_near([&](int q) {
+                const double d = dist2(px, py, xs[q], ys[q], g.Lx, g.Ly);
+                if (d >= lo2 && d < hi2 && q != p)
+                    atomicAdd(&l.q[(int)fmin((d - lo2) / width, BINS - 1.0)], 1);
+            });
+            wave_lds_sync();
+            int b = 0;
+            while (b < BINS - 1 && below + l.q[b] < need) below += l.q[b++];
+            const bool few = below + l.q[b] <= CAP;
+            wave_lds_sync();
+            if (b < BINS - 1) hi2 = lo2 + (b + 1) * width;
+            lo2 += b * width;
+            if (!few) continue;
+            lim2 = hi2;
+        }
+        if (gl == 0) *l.cnt = 0;
         wave_lds_sync();
-        cnt = s_cnt[grp];
+        constexpr int kGiveUp = 1 << 30;   // (above any count of nodes)
+        if (!each_near([&](int q) {
+                const double d = dist2(px, py, xs[q], ys[q], g.Lx, g.Ly);
+                if (d < lim2 && q != p) {
+                    const int at = atomicAdd(l.cnt, 1);
+                    if (at < CAP) {
+                        l.d[at] = d;
+                        l.q[at] = q;
+                    }
+                }
+            }))
+            atomicOr(reinterpret_cast<unsigned *>(l.cnt), (unsigned)kGiveUp);
         wave_lds_sync();
+        cnt = *l.cnt;
+        wave_lds_sync();
+        if (cnt >= kGiveUp) break;
         ok = cnt >= need && cnt <= CAP;
         if (!ok) {
-            (cnt < need ? lo2 : hi2) = lim2;
+            if (cnt < need) {
+                lo2 = lim2;
+                below = cnt;
+            } else {
+                hi2 = lim2;
+            }
             const double f = (1.15 * need + 5.0) / (cnt > 0 ? cnt : 1);
             lim2 *= cnt < need ? fmin(fmax(f, 1.1), 4.0) : fmin(fmax(f, 0.25), 0.95);
             if (!(lim2 > lo2 && lim2 < hi2)) lim2 = sqrt(lo2) * sqrt(hi2);
         }
     }
-    if (!ok) {
-        if (live && gl == 0) redo[1 + atomicAdd(&redo[0], 1)] = p;
-        cnt = 0;   // (the lanes stay: the steps below work across the wavefront)
+    if (WAVE && !ok) {   // each next node: the closest one behind the last
+        if (live && gl == 0) nbr[p] = p;
+        double ld = -1.0;
+        int lu = -1;
+        lim2 = hi2;
+        for (int k = 1; k < K; ++k) {
+            double bd = DBL_MAX;
+            int bu = INT_MAX, bq = p;   // (p: there is none, coordinates are not finite)
+            each_near([&](int q) {
+                const double d = dist2(px, py, xs[q], ys[q], g.Lx, g.Ly);
+                if (!(d <= bd) || d < ld || q == p) return;
+                const int u = perm[q];
+                if ((d == ld && u <= lu) || (d == bd && u > bu)) return;
+                bd = d;
+                bu = u;
+                bq = q;
+            });
+#pragma unroll
+            for (int off = 1; off < 64; off <<= 1) {
+                const double od = __shfl_xor(bd, off);
+                const int ou = __shfl_xor(bu, off), oq = __shfl_xor(bq, off);
+                if (od < bd || (od == bd && ou < bu)) {
+                    bd = od;
+                    bu = ou;
+                    bq = oq;
+                }
+            }
+            ld = bd;
+            lu = bu;
+            if (live && gl == 0) nbr[(int64_t)k * n + p] = bq;
+        }
+        return true;
     }
+    if (!ok) cnt = 0;   // (the lanes stay: the steps below work across the wavefront)
     double d[E];
     int rank[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) {
-        d[e] = e * G + gl < cnt ? s_d[grp][e * G + gl] : -1.0;
+        d[e] = e * G + gl < cnt ? l.d[e * G + gl] : -1.0;
         rank[e] = 0;
     }
     int top = cnt;   // the wavefront's longest list
@@ -469,36 +492,91 @@ __global__ __launch_bounds__(256) void k_knn(
     top = __builtin_amdgcn_readfirstlane(top);
 #pragma unroll 4
     for (int j = 0; j < cnt; ++j) {
-        const double dj = s_d[grp][j];
+        const double dj = l.d[j];
 #pragma unroll
         for (int e = 0; e < E; ++e)
             if (e * G < top) rank[e] += dj < d[e];
     }
     // two entries at one place: equal distances
-    if (gl < 2) s_occ[grp][gl] = 0u;
+    if (gl < 2) l.occ[gl] = 0u;
     wave_lds_sync();
     bool tie = false;
 #pragma unroll
     for (int e = 0; e < E; ++e)
         if (e * G + gl < cnt && rank[e] < need) {
             const unsigned bit = 1u << (rank[e] & 31);
-            if (atomicOr(&s_occ[grp][rank[e] >> 5], bit) & bit) tie = true;
+            if (atomicOr(&l.occ[rank[e] >> 5], bit) & bit) tie = true;
         }
     if (__any(tie)) {
 #pragma unroll
         for (int e = 0; e < E; ++e)
             if (e * G + gl < cnt) {
-                const int u = perm[s_q[grp][e * G + gl]];
+                const int u = perm[l.q[e * G + gl]];
                 for (int j = 0; j < cnt; ++j)
-                    if (s_d[grp][j] == d[e] && perm[s_q[grp][j]] < u) ++rank[e];
+                    if (l.d[j] == d[e] && perm[l.q[j]] < u) ++rank[e];
             }
     }
-    if (!live || !ok) return;
+    if (!live || !ok) return ok;
     if (gl == 0) nbr[p] = p;
 #pragma unroll
     for (int e = 0; e < E; ++e)
         if (e * G + gl < cnt && rank[e] < need)
-            nbr[(int64_t)(rank[e] + 1) * n + p] = s_q[grp][e * G + gl];
+            nbr[(int64_t)(rank[e] + 1) * n + p] = l.q[e * G + gl];
+    return ok;
+}
+
+// Stencils of all nodes, eight lanes a node; k_knn_redo serves those that give up
+// (none on lattices). Inserting each candidate into a sorted list in registers
+// costs every lane of a wavefront a pass over the list whenever one lane takes it,
+// and one lane a node leaves a small cloud's few wavefronts waiting for cells and
+// nodes in turn: 909 us against 209 on 262,144 nodes, K 30, and 182 against 20 on
+// 10,201, K 25.
+constexpr int kKnnLanes = 8;
+template <int CAP>
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(CAP == 32 ? 7 : CAP == 64 ? 6 : 4))) void k_knn(
+    const Geo *__restrict__ geo, const double *__restrict__ xs, const double *__restrict__ ys,
+    const int32_t *__restrict__ perm, const int32_t *__restrict__ cstart,
+    const int32_t *__restrict__ cend, int n, int K, int32_t *__restrict__ redo,
+    int32_t *__restrict__ nbr) {
+    constexpr int G = kKnnLanes, QB = 256 / G;
+    __shared__ double s_d[QB][CAP + 1];   // (odd strides: the groups read distinct banks)
+    __shared__ int s_q[QB][CAP + 1];
+    __shared__ int s_cnt[QB];
+    __shared__ unsigned s_occ[QB][2];
+    const int64_t nb = ((int64_t)n + QB - 1) / QB, blk = xcd_tile(nb);
+    if (blk >= nb) return;
+    const int grp = threadIdx.x / G;
+    const int64_t pt = blk * QB + grp;
+    const bool live = pt < n;
+    const int p = live ? (int)pt : n - 1;
+    const KnnList l{s_d[grp], s_q[grp], &s_cnt[grp], s_occ[grp]};
+    if (!knn_by_radius<CAP, G>(*geo, xs, ys, perm, cstart, cend, n, K, p, live, l, nbr) &&
+        live && threadIdx.x % G == 0)
+        redo[1 + atomicAdd(&redo[0], 1)] = p;
+}
+
+// The nodes that k_knn left, a wavefront each: redo[0] of them, from redo[1] on.
+// The search of 20,000 nodes, ms, with this, with sixteen radii by eight lanes, and
+// by rings of cells, one lane a node: eight dense clusters K 12 1.1, 19, 12, K 45
+// 1.4, 32, 40; a strip of 0.003 of the domain and 20 nodes outside, K 12 0.8, 98, 36;
+// one node far off the others 0.4, 10, 17. An empty list costs a launch of 5 us.
+__global__ __launch_bounds__(64) void k_knn_redo(
+    const Geo *__restrict__ geo, const double *__restrict__ xs, const double *__restrict__ ys,
+    const int32_t *__restrict__ perm, const int32_t *__restrict__ cstart,
+    const int32_t *__restrict__ cend, int n, int K, const int32_t *__restrict__ redo,
+    int32_t *__restrict__ nbr) {
+    constexpr int CAP = 96;
+    __shared__ double s_d[CAP];
+    __shared__ int s_q[CAP];
+    __shared__ int s_cnt;
+    __shared__ unsigned s_occ[2];
+    const int count = min(redo[0], n);
+    const KnnList l{s_d, s_q, &s_cnt, s_occ};
+    for (int i = blockIdx.x; i < count; i += gridDim.x) {
+        knn_by_radius<CAP, 64>(*geo, xs, ys, perm, cstart, cend, n, K, redo[1 + i], true, l, nbr);
+        wave_lds_sync();   // the next node takes the list's place
+    }
 }
 
 // Owner of each departure point x_p - e_k dx (k = 1..8): the closest node,
@@ -1903,7 +1981,7 @@ hipError_t launch_order(const BuildOrder &o, hipStream_t s) {
 }
 
 hipError_t launch_knn(const Geo *geo, const double *xs, const double *ys,
-                      const int32_t *perm, const int32_t *iperm, const int32_t *cstart,
+                      const int32_t *perm, const int32_t *cstart,
                       const int32_t *cend, int n, int K, void *tmp, size_t tmp_bytes, int32_t *nbr,
                       hipStream_t s) {
     int32_t *redo = OwnedLists(tmp, tmp_bytes, n).ptr;   // emptied by launch_order
@@ -1912,8 +1990,8 @@ hipError_t launch_knn(const Geo *geo, const double *xs, const double *ys,
     hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, geo, xs, ys, perm, cstart, cend, n, K, redo, nbr);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_knn_redo, dim3(64), dim3(64), 0, s, geo, xs, ys, perm, iperm, cstart, cend, n,
-                       K, redo, nbr);
+    hipLaunchKernelGGL(k_knn_redo, dim3(1024), dim3(64), 0, s, geo, xs, ys, perm, cstart, cend, n, K,
+                       redo, nbr);
     return hipGetLastError();
 }
 

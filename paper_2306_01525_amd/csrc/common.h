@@ -328,7 +328,7 @@ struct BuildOrder {
 };
 hipError_t launch_order(const BuildOrder &o, hipStream_t s);
 hipError_t launch_knn(const Geo *geo, const double *xs, const double *ys,
-                      const int32_t *perm, const int32_t *iperm, const int32_t *cstart,
+                      const int32_t *perm, const int32_t *cstart,
                       const int32_t *cend, int n, int K, void *tmp, size_t tmp_bytes, int32_t *nbr,
                       hipStream_t s);   // tmp: of rbf_temp_bytes
 hipError_t launch_owner(const Geo *geo, const double *xs, const double *ys,

@@ -667,3 +667,35 @@ def test_transposed_rows_of_clustered_clouds(n, K, m, precision):
         out.append((one.step_adjoint(f, lam, torch.empty_like(f), dtau), dtau))
         one.close()
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("K", [6, 20, 48])
+@pytest.mark.parametrize("which", ["strip", "clusters", "outliers"])
+def test_stencil_search_around_dense_parts(which, K):
+    """Few nodes around dense parts, whose radius has to be found within a thousandth:
+    stencils and owners bit-exact against the oracle's. The plan is captured, so
+    that a singular local system does not end the build."""
+    from paper_2306_01525_amd import Params, Plan
+    r = np.random.default_rng(6)
+    n, period = 4000, (1.0, 1.0)
+    x, y = r.uniform(0, 1, n), r.uniform(0, 1, n)
+    if which == "strip":
+        x[20:] *= 0.003
+    elif which == "clusters":
+        at, c = r.uniform(0.2, 0.8, (8, 2)), r.integers(0, 8, n)
+        q = at[c] + 1e-3 * r.standard_normal((n, 2))
+        x[400:], y[400:] = q[400:].T
+    else:
+        period = (0.0, 0.0)
+        x[:5] += 30.0
+        y[3:7] -= 200.0
+    m = 4 if K > 32 else 3 if K > 16 else 2
+    st, z = torch.cuda.Stream(), np.zeros(n)
+    plan, _, _, _ = Plan.build_graph([(x, y, period, None)],
+                                     [Params(dx=0.015, K=K, degree=m, tau=0.8)], z, z, 0, st)
+    plan.graph_launch(st)
+    torch.cuda.synchronize()
+    say("cloud", which, "K", K, "searched")
+    np.testing.assert_array_equal(plan.export("nbr"), oracle.knn(x, y, period, K))
+    np.testing.assert_array_equal(plan.export("owner"), oracle.owners(x, y, period, 0.015, 0))
+    plan.close()
