@@ -1148,17 +1148,15 @@ mlbm_status mlbm_lbm_step(int32_t nx, int32_t ny, int32_t precision, double tau,
     if (!g_a || !g_b || g_a == g_b) return fail(MLBM_EINVAL, "two distinct state buffers needed");
     if (!(tau > 0.5)) return fail(MLBM_EINVAL, "tau must exceed 1/2");
     if (n_steps < 0) return fail(MLBM_EINVAL, "negative step count");
-    // as few launches as their steps allow, but even in number when n_steps
-    // is even: the result is in g_b after an odd number of steps
-    const int32_t most = lbm_steps_per_launch(nx, ny, precision);
-    int32_t launches = n_steps / most + (n_steps % most ? 1 : 0);
-    launches += (launches ^ n_steps) & 1;
+    const LbmSteps groups = lbm_steps(nx, ny, precision, n_steps);
     void *a = g_a, *b = g_b;
-    for (int32_t i = 0; i < launches; ++i) {
-        const int32_t steps = n_steps / launches + (i < n_steps % launches ? 1 : 0);
-        MLBM_HIP(launch_lbm_step(nx, ny, precision, tau, rho0, steps, a, b, s));
-        std::swap(a, b);
-    }
+    for (int u = 0; u < kLbmGroups; ++u)
+        for (int32_t i = 0; i < groups.count[u]; ++i)
+            for (int steps : kLbmGroup[u]) {
+                if (steps == 0) continue;
+                MLBM_HIP(launch_lbm_step(nx, ny, precision, tau, rho0, steps, a, b, s));
+                std::swap(a, b);
+            }
     if (result_in_b) *result_in_b = (n_steps & 1) ? 1 : 0;
     return MLBM_OK;
 }

@@ -391,8 +391,14 @@ hipError_t launch_residual(const CloudPlan &cp, int precision, const void *g, do
 hipError_t launch_interpolate(const CloudPlan &cp, const double *field, int64_t out_stride,
                               double *out, hipStream_t s);
 // standard lattice Boltzmann on a periodic nx x ny lattice, state [9][ny][nx]
-// steps <= lbm_steps_per_launch
-int lbm_steps_per_launch(int nx, int ny, int precision);
+// n_steps as groups of launches (steps of the first, and of a second or 0)
+constexpr int kLbmGroups = 5;
+constexpr int kLbmGroup[kLbmGroups][2] = {{1, 0}, {3, 0}, {2, 2}, {2, 4}, {4, 4}};
+struct LbmSteps {
+    int32_t count[kLbmGroups];
+};
+LbmSteps lbm_steps(int nx, int ny, int precision, int32_t n_steps);
+// steps: 1 to 4
 hipError_t launch_lbm_step(int nx, int ny, int precision, double tau, double rho0, int steps,
                            const void *g, void *go, hipStream_t s);
 hipError_t launch_lbm_init(int n, int precision, double rho0, const double *rho, const double *ux,

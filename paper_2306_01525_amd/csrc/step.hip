@@ -1462,10 +1462,10 @@ __device__ __forceinline__ void lbm_collide(double (&f)[kQ], double (&v)[kQ], do
 // and so are the bits.
 // A step alone is bound by memory, 72 (FP32) or 144 bytes a node, or on a
 // small lattice by its launch and two trips to memory; S steps share those.
-// 3 or 4 of them: FP32 2048^2 49.2 -> 28.3 us a step, 1024^2 12.1 -> 8.6,
-// 512^2 4.5 -> 3.6, 160^2 3.4 -> 1.8; FP64 115 -> 51.7, 23.1 -> 12.1, 7.1 ->
-// 4.9, 3.5 -> 2.0. What bounds them now is the arithmetic of the block and the
-// nodes around it, at 512 threads and three workgroups a CU.
+// 3 or 4 of them: FP32 2048^2 49.0 -> 26.8 us a step, 1024^2 10.9 -> 8.4, 512^2
+// 4.2 -> 3.8, 160^2 2.6 -> 1.6; FP64 115 -> 49.4, 23.2 -> 11.0, 6.6 -> 4.6, 2.9 ->
+// 1.7. What bounds them now is the arithmetic of the block and the nodes around
+// it, at 512 threads and three workgroups a CU.
 template <class T, int TX, int CAP, int NTH, int S>
 __global__ __launch_bounds__(NTH) void k_lbm_steps(int nx, int ny, int64_t nblocks,
                                                    const T *__restrict__ g, T *__restrict__ go,
@@ -1764,16 +1764,83 @@ hipError_t launch_l2_final(const double *part, int64_t nparts, double *out, hipS
     return hipGetLastError();
 }
 
-// Steps per launch and blocks. Up to 131,072 nodes blocks of about 500 nodes,
-// of which more CUs get one (160^2: 1.8 us a step against 2.6 with the large
-// ones; 512^2: 4.1 against 3.6); above, blocks that fill a third of a CU's LDS.
-// Four steps in a launch, three in between where four lose to the nodes that
-// neighbouring blocks compute twice (FP32 512^2 3.6 against 4.1 us; FP64
-// 1024^2 12.1 against 13.2).
-constexpr int64_t kLbmSmall = 131072;
-int lbm_steps_per_launch(int nx, int ny, int precision) {
-    const int64_t n = (int64_t)nx * ny;
-    return n > kLbmSmall && n <= (precision == MLBM_FP64 ? 1 << 21 : 1 << 20) ? 3 : 4;
+// Launches of several steps: small blocks of at most 512 nodes, one a thread, or, in
+// FP32, large ones that fill a third of a CU's LDS.
+struct LbmBlock {
+    int tx, cap;
+};
+constexpr LbmBlock kLbmSmall{32, 512}, kLbmLarge{64, 1456};
+
+// Time of a launch of `steps` steps, us, from its shape: a fixed part, and a part per
+// node that the busiest CU computes (whole blocks, the nodes around them with
+// them), fitted to lattices of 256 to 4,194,304 nodes, square and thin; most lie within
+// 10 %. A block of steps that its lattice does not fill, or a last CU round that
+// is nearly empty, can cost more than the passes over memory that it saves, so
+// neither the size alone nor the number of steps decides. us a step, single
+// steps, 2, 3 and 4 in a launch:
+//   FP64 2048x65 4.5, 3.9 3.2 3.5; 512^2 6.6, 4.9 4.6 4.5; 2048^2 115, 64 50 49
+//   FP32 2048x65 3.5, small blocks 3.1 2.6 3.0, large 4.0 3.4 2.9
+//   FP32 512^2 4.2, small 4.0 3.8 4.0, large 4.0 3.4 4.0
+//   FP32 1024^2 10.9, small 9.5 9.4 11.3, large 10.0 8.4 8.2; 2048^2 49, large 36 29 27
+double lbm_launch_us(int nx, int ny, int precision, int steps, const LbmBlock &b) {
+    const double n = (double)nx * ny;
+    const bool f64 = precision == MLBM_FP64;
+    if (steps == 1)   // + populations that the caches no longer hold, + workgroups of short rows
+        return 2.4 + (f64 ? 16e-6 * n + 11e-6 * std::max(0.0, n - 3e5)
+                          : 8e-6 * n + 6e-6 * std::max(0.0, n - 2.1e6)) +
+               450e-6 * ((double)ny * ((nx + 255) / 256) - n / 256);
+    const int r = steps - 1, w = b.tx + 2 * r, h = b.cap / w, ty = h - 2 * r;
+    const int64_t blocks = (int64_t)((nx + b.tx - 1) / b.tx) * ((ny + ty - 1) / ty);
+    const double nodes = (double)((blocks + 255) / 256) * w * h;   // of the busiest CU
+    constexpr double fixed64[3] = {1.9, 3.0, 3.4}, each64[3] = {5.4e-3, 5.5e-3, 5.6e-3};
+    constexpr double fixedS[3] = {2.5, 3.5, 3.4}, eachS[3] = {3.6e-3, 3.9e-3, 4.9e-3};
+    constexpr double fixedL[3] = {3.0, 5.1, 5.2}, eachL[3] = {3.4e-3, 3.5e-3, 3.9e-3};
+    const int k = steps - 2;
+    if (f64) return fixed64[k] + each64[k] * nodes;
+    return b.tx == kLbmSmall.tx ? fixedS[k] + eachS[k] * nodes : fixedL[k] + eachL[k] * nodes;
+}
+
+bool lbm_large(int nx, int ny, int precision, int steps) {
+    return precision != MLBM_FP64 && lbm_launch_us(nx, ny, precision, steps, kLbmLarge) <
+                                         lbm_launch_us(nx, ny, precision, steps, kLbmSmall);
+}
+
+// A number of launches that is even where the number of steps is leaves the result
+// in the buffer that single steps leave it in: launches of two and four steps come
+// in pairs, those of one and three alone. The cheapest groups for n_steps: the
+// cheapest one a step, and the best mix for what is left. On flat lattices (fewer
+// rows of blocks than XCDs) a single step between others finds its populations in
+// other XCDs' caches and leaves its own there, about 22 ns per 1,000 nodes in FP32
+// (16384x17, three steps and one: 15 us expected, 21).
+LbmSteps lbm_steps(int nx, int ny, int precision, int32_t n_steps) {
+    double us[5], cost[kLbmGroups];
+    for (int k = 1; k < 5; ++k)
+        us[k] = lbm_launch_us(nx, ny, precision, k, lbm_large(nx, ny, precision, k) ? kLbmLarge : kLbmSmall);
+    auto steps = [](int u) { return kLbmGroup[u][0] + kLbmGroup[u][1]; };
+    int bulk = 0;
+    for (int u = 0; u < kLbmGroups; ++u) {
+        cost[u] = us[kLbmGroup[u][0]] + (kLbmGroup[u][1] ? us[kLbmGroup[u][1]] : 0.0);
+        if (u == 0 && ny < 112) cost[u] += (precision == MLBM_FP64 ? 44e-6 : 22e-6) * std::min(3e5, (double)nx * ny);
+        if (cost[u] / steps(u) < cost[bulk] / steps(bulk)) bulk = u;
+    }
+    constexpr int REST = 24;
+    LbmSteps out{};
+    if (n_steps >= REST) out.count[bulk] = (n_steps - REST) / steps(bulk) + 1;
+    int left = n_steps - out.count[bulk] * steps(bulk);   // < REST
+    double best[REST] = {};
+    int last[REST] = {};
+    for (int t = 1; t <= left; ++t) {
+        best[t] = 1e300;
+        for (int u = 0; u < kLbmGroups; ++u)
+            if (steps(u) <= t && best[t - steps(u)] + cost[u] < best[t]) {
+                best[t] = best[t - steps(u)] + cost[u];
+                last[t] = u;
+            }
+    }
+    const double total = best[left] + out.count[bulk] * cost[bulk];
+    for (; left > 0; left -= steps(last[left])) ++out.count[last[left]];
+    if (n_steps * us[1] <= total) out = LbmSteps{{n_steps}};
+    return out;
 }
 
 template <class T, int TX, int CAP, int NTH>
@@ -1797,14 +1864,12 @@ hipError_t launch_lbm_step(int nx, int ny, int precision, double tau, double rho
                                nblocks, (const float *)g, (float *)go, rtau, rho0);
         return hipGetLastError();
     }
-    const bool small = (int64_t)nx * ny <= kLbmSmall;
-    if (precision == MLBM_FP64) {
-        if (small) launch_lbm_fused<double, 32, 512, 256>(nx, ny, rtau, rho0, steps, g, go, s);
-        else launch_lbm_fused<double, 32, 728, 256>(nx, ny, rtau, rho0, steps, g, go, s);
-    } else {
-        if (small) launch_lbm_fused<float, 32, 512, 256>(nx, ny, rtau, rho0, steps, g, go, s);
-        else launch_lbm_fused<float, 64, 1456, 512>(nx, ny, rtau, rho0, steps, g, go, s);
-    }
+    if (precision == MLBM_FP64)
+        launch_lbm_fused<double, kLbmSmall.tx, kLbmSmall.cap, 512>(nx, ny, rtau, rho0, steps, g, go, s);
+    else if (lbm_large(nx, ny, precision, steps))
+        launch_lbm_fused<float, kLbmLarge.tx, kLbmLarge.cap, 512>(nx, ny, rtau, rho0, steps, g, go, s);
+    else
+        launch_lbm_fused<float, kLbmSmall.tx, kLbmSmall.cap, 512>(nx, ny, rtau, rho0, steps, g, go, s);
     return hipGetLastError();
 }
 

@@ -106,3 +106,10 @@ def test_steps_in_one_launch_equal_single_steps(nx, ny, precision):
         res = lat.step(a, b, steps)
         assert res is (b if steps % 2 else a)
         assert torch.equal(res, one), steps
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("nx,ny", [(1024, 768), (1025, 768), (32, 24577), (24577, 33)])
+def test_steps_in_one_launch_at_the_line_between_blocks(nx, ny, precision):
+    """As the test above, either side of 786,432 nodes and on thin lattices."""
+    test_steps_in_one_launch_equal_single_steps(nx, ny, precision)
