@@ -373,8 +373,9 @@ mlbm_status mlbm_init_adjoint(const mlbm_plan *plan, const double *u0x, const do
  * NULL, room for MLBM_STEP_VARIANTS floats) receives the measured milliseconds
  * per step of each variant, *n_variants (host, may be NULL) their count. The contents of
  * g_a and g_b are advanced (start again from mlbm_init afterwards). Synchronous. FP64 plans have a single variant.
- * Clouds of up to 49,152 nodes that are not stepped as a batch take one kernel
- * whatever the variant, so theirs time alike. */
+ * Small clouds and batches (up to 24,576 to 49,152 nodes, by stencil size) take
+ * one kernel whatever the variant: it is timed once, every entry of ms_out holds
+ * that time, and the plan keeps its variant. */
 mlbm_status mlbm_autotune(mlbm_plan *plan, void *g_a, void *g_b, int32_t n_steps,
                           float *ms_out, int32_t *n_variants, hipStream_t stream);
 

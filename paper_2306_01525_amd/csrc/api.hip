@@ -1277,11 +1277,15 @@ mlbm_status mlbm_autotune(mlbm_plan *plan, void *g_a, void *g_b, int32_t n_steps
         (void)hipEventDestroy(e0);
         return hip_fail(err, "hipEventCreate");
     }
+    // where the small-cloud step takes the plan, one time stands for all variants
+    // and the plan keeps its own
+    const bool alike = step_ignores_variant(*plan);
     int best = 0;
     float best_ms = 0.0f;
     mlbm_status st = MLBM_OK;
-    for (int v = 0; v < nv && st == MLBM_OK; ++v) {
-        for (auto &cp : plan->c) cp.variant = v;
+    for (int v = 0; v < (alike ? 1 : nv) && st == MLBM_OK; ++v) {
+        if (!alike)
+            for (auto &cp : plan->c) cp.variant = v;
         int32_t rb = 0;
         st = mlbm_step(plan, g_a, g_b, 1, &rb, s);               // warm-up
         if (st != MLBM_OK) break;
@@ -1294,15 +1298,16 @@ mlbm_status mlbm_autotune(mlbm_plan *plan, void *g_a, void *g_b, int32_t n_steps
         float ms = 0.0f;
         if ((err = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess) { st = hip_fail(err, "hipEventElapsedTime"); break; }
         ms /= (float)n_steps;
-        if (ms_out) ms_out[v] = ms;
-        if (v == 0 || ms < best_ms) {
+        if (ms_out) std::fill(ms_out + v, ms_out + (alike ? nv : v + 1), ms);
+        if (!alike && (v == 0 || ms < best_ms)) {
             best_ms = ms;
             best = v;
         }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
-    for (auto &cp : plan->c) cp.variant = best;
+    if (!alike)
+        for (auto &cp : plan->c) cp.variant = best;
     drop_graph(plan);
     return st;
 }

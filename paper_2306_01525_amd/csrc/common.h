@@ -375,6 +375,8 @@ hipError_t launch_step(const CloudPlan &cp, int precision, const void *gin, void
 Step32Args step32_args(const CloudPlan &cp, void *frec);
 hipError_t launch_step_batch(const mlbm_plan &plan, const void *gin, void *gout,
                              hipStream_t s);
+// every cloud takes the small-cloud step, whatever its variant
+bool step_ignores_variant(const mlbm_plan &plan);
 hipError_t launch_init_batch(const mlbm_plan &plan, const double *rho, const double *ux,
                              const double *uy, void *g, hipStream_t s);
 hipError_t launch_moments_batch(const mlbm_plan &plan, const void *g, double *rho, double *ux,

@@ -1335,11 +1335,15 @@ void launch_wide_batch(const mlbm_plan &plan, const void *gin, void *gout, hipSt
 // whatever the variant. K 20 to 30, us a step, best tile kernel and this: 2 clouds
 // of 3,232 nodes together 9.5 and 5.1, 8 of 15,247 9.7 and 6.6, 4 of 38,054 16.7
 // and 12.9; 8 of 76,924 nodes stay with the tile kernels (18.5).
-template <int MODE>
-void launch32_batch_v(const mlbm_plan &plan, const void *gin, void *gout, hipStream_t s) {
+int wide_dirs_batch(const mlbm_plan &plan) {
     int K = kMaxK;
     for (const CloudPlan &cp : plan.c) K = std::min(K, cp.K);
-    if (const int dirs = wide_dirs(plan.total_tiles * kTile, K, MLBM_FP32_DEV, true)) {
+    return wide_dirs(plan.total_tiles * kTile, K, MLBM_FP32_DEV, true);
+}
+
+template <int MODE>
+void launch32_batch_v(const mlbm_plan &plan, const void *gin, void *gout, hipStream_t s) {
+    if (const int dirs = wide_dirs_batch(plan)) {
         if (dirs == 1) launch_wide_batch<MODE, 1>(plan, gin, gout, s);
         else launch_wide_batch<MODE, 2>(plan, gin, gout, s);
         return;
@@ -1643,6 +1647,13 @@ hipError_t launch_step_batch(const mlbm_plan &plan, const void *gin, void *gout,
     else
         launch32_batch_v<MLBM_STENCIL_PAPER>(plan, gin, gout, s);
     return hipGetLastError();
+}
+
+bool step_ignores_variant(const mlbm_plan &plan) {
+    if (plan.batched) return wide_dirs_batch(plan) != 0;
+    for (const CloudPlan &cp : plan.c)
+        if (!wide_dirs(cp.n, cp.K, plan.precision)) return false;
+    return true;
 }
 
 hipError_t launch_init_batch(const mlbm_plan &plan, const double *rho, const double *ux,

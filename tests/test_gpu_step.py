@@ -427,3 +427,26 @@ def test_tile_kernel_variants_agree_with_walls_and_force(wall):
     say("wall", wall, "n", c.n, "largest |g|", float(g.abs().max()))
     assert plan.device_error() == 0
     plan.close()
+
+
+def test_autotune_keeps_the_variant_where_all_run_one_kernel():
+    """A small cloud and a small batch: one time for all ten variants, and the plan
+    keeps the one it had; a cloud above the small-cloud sizes gets its fastest."""
+    from paper_2306_01525_amd import Plan
+    c, ux, uy = tgv_case(40, 20, 3, 0)
+    p = _params(c.h, 20, 3, 0, 0, 0.8)
+    small = Plan.build(c.x, c.y, c.period, p)
+    batch = Plan.build_batch([(c.x, c.y, c.period, None)] * 3, [p] * 3)
+    for plan, k in ((small, 1), (batch, 3)):
+        first = plan.info.variant
+        for v in (first, 4):
+            plan.set_variant(v)
+            ms = plan.autotune(plan.init(np.tile(ux, k), np.tile(uy, k)), plan.new_state(), 5)
+            assert len(ms) == 10 and len(set(ms)) == 1 and ms[0] > 0
+            assert plan.info.variant == v
+        plan.close()
+    c, ux, uy = tgv_case(223, 20, 3, 0)
+    plan = Plan.build(c.x, c.y, c.period, _params(c.h, 20, 3, 0, 0, 0.8))
+    ms = plan.autotune(plan.init(ux, uy), plan.new_state(), 5)
+    assert len(set(ms)) > 1 and ms[plan.info.variant] == min(ms)
+    plan.close()
