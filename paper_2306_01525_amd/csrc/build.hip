@@ -1889,12 +1889,6 @@ hipError_t launch_links(const uint8_t *ntype, const int32_t *perm, const double 
     return hipGetLastError();
 }
 
-hipError_t launch_geo_bbox(Geo *geo, const double *x, const double *y, int n, int gx, int gy,
-                           int hb, hipStream_t s) {
-    hipLaunchKernelGGL(k_geo_bbox, dim3(1), dim3(1024), 0, s, geo, x, y, n, gx, gy, hb);
-    return hipGetLastError();
-}
-
 hipError_t launch_reset(int32_t *err, int32_t *stats, int nstats, hipStream_t s) {
     hipLaunchKernelGGL(k_reset, dim3(blocks_for(std::max(nstats, 1), 256)), dim3(256), 0, s, err, stats,
                        nstats);
