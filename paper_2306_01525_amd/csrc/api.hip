@@ -1148,7 +1148,7 @@ mlbm_status mlbm_lbm_step(int32_t nx, int32_t ny, int32_t precision, double tau,
     if (!g_a || !g_b || g_a == g_b) return fail(MLBM_EINVAL, "two distinct state buffers needed");
     if (!(tau > 0.5)) return fail(MLBM_EINVAL, "tau must exceed 1/2");
     if (n_steps < 0) return fail(MLBM_EINVAL, "negative step count");
-    const LbmSteps groups = lbm_steps(nx, ny, precision, n_steps);
+    const LbmSteps groups = lbm_steps(nx, ny, precision, n_steps, capturing(s));
     void *a = g_a, *b = g_b;
     for (int u = kLbmGroups - 1; u >= 0; --u)   // (the longest first: 2048^2 20 steps 1 % faster)
         for (int32_t i = 0; i < groups.count[u]; ++i)

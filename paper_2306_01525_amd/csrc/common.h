@@ -399,7 +399,7 @@ constexpr int kLbmGroup[kLbmGroups][2] = {{1, 0}, {3, 0}, {2, 2}, {2, 4}, {4, 4}
 struct LbmSteps {
     int32_t count[kLbmGroups];
 };
-LbmSteps lbm_steps(int nx, int ny, int precision, int32_t n_steps);
+LbmSteps lbm_steps(int nx, int ny, int precision, int32_t n_steps, bool captured);
 // steps: 1 to 4
 hipError_t launch_lbm_step(int nx, int ny, int precision, double tau, double rho0, int steps,
                            const void *g, void *go, hipStream_t s);

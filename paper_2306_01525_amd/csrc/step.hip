@@ -1803,11 +1803,12 @@ double lbm_launch_us(int nx, int ny, int precision, int steps, const LbmBlock &b
     const int r = steps - 1, w = b.tx + 2 * r, h = b.cap / w, ty = h - 2 * r;
     const int64_t blocks = (int64_t)((nx + b.tx - 1) / b.tx) * ((ny + ty - 1) / ty);
     const double nodes = (double)((blocks + 255) / 256) * w * h;   // of the busiest CU
-    constexpr double fixed64[3] = {1.9, 3.0, 3.4}, each64[3] = {5.4e-3, 5.5e-3, 5.6e-3};
+    constexpr double fixed64[3] = {1.9, 3.0, 3.4}, each64[3] = {4.8e-3, 4.8e-3, 5.3e-3};
+    constexpr double far64[3] = {10e-6, 7e-6, 0.0};   // a node that the caches do not hold
     constexpr double fixedS[3] = {2.5, 3.5, 3.4}, eachS[3] = {3.6e-3, 3.9e-3, 4.9e-3};
     constexpr double fixedL[3] = {3.0, 5.1, 5.2}, eachL[3] = {3.4e-3, 3.5e-3, 3.9e-3};
     const int k = steps - 2;
-    if (f64) return fixed64[k] + each64[k] * nodes;
+    if (f64) return fixed64[k] + each64[k] * nodes + far64[k] * std::max(0.0, n - 1.2e6);
     return b.tx == kLbmSmall.tx ? fixedS[k] + eachS[k] * nodes : fixedL[k] + eachL[k] * nodes;
 }
 
@@ -1819,18 +1820,28 @@ bool lbm_large(int nx, int ny, int precision, int steps) {
 // A number of launches that is even where the number of steps is leaves the result
 // in the buffer that single steps leave it in: launches of two and four steps come
 // in pairs, those of one and three alone. The cheapest groups for n_steps: the
-// cheapest one a step, and the best mix for what is left. On flat lattices (fewer
-// rows of blocks than XCDs) a single step between others finds its populations in
-// other XCDs' caches and leaves its own there, about 22 ns per 1,000 nodes in FP32
-// (16384x17, three steps and one: 15 us expected, 21).
-LbmSteps lbm_steps(int nx, int ny, int precision, int32_t n_steps) {
+// cheapest one a step, and the best mix for what is left. Without a graph a launch
+// of a few microseconds waits for the host (185x331, 16 steps with initial state and
+// moments: 62 us with four launches, 66 with six that take less time themselves). A
+// single step between others finds some of its populations in other XCDs' caches (1.15: with 1, mixes
+// with single steps that measured 4 % slower were taken, 1115x1352 FP32 18 steps 284
+// us for 271), and on flat lattices (fewer rows of blocks than XCDs) most of them,
+// and leaves its own there, about 22 ns per 1,000 nodes in FP32 (16384x17, three
+// steps and one: 15 us expected, 21).
+LbmSteps lbm_steps(int nx, int ny, int precision, int32_t n_steps, bool captured) {
+    const double host_us = captured ? 0.0 : 2.0;
     double us[5], cost[kLbmGroups];
     for (int k = 1; k < 5; ++k)
-        us[k] = lbm_launch_us(nx, ny, precision, k, lbm_large(nx, ny, precision, k) ? kLbmLarge : kLbmSmall);
+        us[k] = host_us +
+                lbm_launch_us(nx, ny, precision, k, lbm_large(nx, ny, precision, k) ? kLbmLarge : kLbmSmall);
+    // (FP64: four steps lose to three where rows of blocks do not start on whole lines,
+    // 1986x897 26 us a step for 24, and win little elsewhere)
+    if (precision == MLBM_FP64 && (int64_t)nx * ny > 300000) us[4] *= 1.06;
     auto steps = [](int u) { return kLbmGroup[u][0] + kLbmGroup[u][1]; };
     int bulk = 0;
     for (int u = 0; u < kLbmGroups; ++u) {
         cost[u] = us[kLbmGroup[u][0]] + (kLbmGroup[u][1] ? us[kLbmGroup[u][1]] : 0.0);
+        if (u == 0) cost[u] *= 1.15;
         if (u == 0 && ny < 112) cost[u] += (precision == MLBM_FP64 ? 44e-6 : 22e-6) * std::min(3e5, (double)nx * ny);
         if (cost[u] / steps(u) < cost[bulk] / steps(bulk)) bulk = u;
     }
