@@ -1557,7 +1557,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
         monomials<M>(sx[h], sy[h], P[h]);
     }
     const double line = 1e6 * DBL_EPSILON * (8 * K + M);   // for the pivots of S
-    bool bad = false;
     auto store_row = [&](int at, int h) {
         double *o = rows + at * RS;
 #pragma unroll
@@ -1597,7 +1596,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
 #pragma unroll
         for (int c = 0; c < M; ++c)
             if (c >= t) U[c] = rows[t * RS + c];
-        if (!(fabs(U[t]) > kSetPivot)) bad = true;
         const double pi = recip(U[t]);
         if (ll == t) uinv = pi;
 #pragma unroll
@@ -1609,6 +1607,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
                 if (c > t) P[h][c] = __builtin_fma(-l, U[c], P[h][c]);
         }
     });
+    bool bad = !(fabs(uinv) < 1.0 / kSetPivot);   // lane t: pivot t
     // set 2 behind set 1, in stencil order
     {
         const uint32_t f0 = (uint32_t)(__ballot(!used[0]) >> (16 * grp)) & 0xFFFFu;
@@ -1701,7 +1700,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(2))) void k_
         for (int r = NS - 1; r > rk; --r) fmac_lane<k % 16, k + 1, NP>(S[r], S[rk], nl[r]);
         fmac_self<k % 16, k + 1, NP>(S[rk], nl[rk]);
     });
-    if (bad && count > 0 && ll == 0) redo[1 + atomicAdd(&redo[0], 1)] = s;
+    if (((uint32_t)(__ballot(bad) >> (16 * grp)) & 0xFFFFu) != 0 && count > 0 && ll == 0)
+        redo[1 + atomicAdd(&redo[0], 1)] = s;
     double ST[NP][NS];   // S by column
 #pragma unroll
     for (int c = 0; c < NP; ++c)
