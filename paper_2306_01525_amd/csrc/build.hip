@@ -195,33 +195,6 @@ __global__ void k_fill_i32(int32_t *p, int32_t v, int64_t n) {
     if (i < n) p[i] = v;
 }
 
-// Ordered insertion of (d, u) into the ascending list held in registers. The
-// live entries occupy the tail of the array; the head holds sentinels with
-// distance -1 that nothing displaces, so the worst live entry is always the
-// last element. Branch-free: entry q of the new list is the old entry q-1
-// when the new pair sorts before it, else the new pair when it sorts before
-// the old entry q, else the old entry q (the comparisons are independent, so
-// the list stays in registers).
-template <int KMAX>
-__device__ __forceinline__ void topk_insert(double (&bd)[KMAX], int (&bu)[KMAX], double d,
-                                            int u) {
-    if (!(d < bd[KMAX - 1] || (d == bd[KMAX - 1] && u < bu[KMAX - 1]))) return;
-    bool lt[KMAX];
-#pragma unroll
-    for (int q = 0; q < KMAX; ++q) lt[q] = d < bd[q] || (d == bd[q] && u < bu[q]);
-#pragma unroll
-    for (int q = KMAX - 1; q > 0; --q) {
-        const double dq = lt[q - 1] ? bd[q - 1] : (lt[q] ? d : bd[q]);
-        const int uq = lt[q - 1] ? bu[q - 1] : (lt[q] ? u : bu[q]);
-        bd[q] = dq;
-        bu[q] = uq;
-    }
-    if (lt[0]) {
-        bd[0] = d;
-        bu[0] = u;
-    }
-}
-
 // Cell of Chebyshev ring r around (cx, cy) number t (0 <= t < 8r, or t = 0 for
 // r = 0): its index, or -1 where an open axis has no such cell. Periodic axes
 // wrap.
