@@ -398,8 +398,8 @@ mlbm_status mlbm_build_graph(const mlbm_cloud *clouds, const mlbm_params *params
                              hipStream_t stream);
 
 /* Select an FP32 step variant by index; drops a created graph. Results are the
- * same for all of them; a plan starts with the one that is fastest over most
- * sizes (info.variant). */
+ * same for all of them; a plan starts with the one that measured faster over
+ * most clouds of its kind of stencils, stencil size and nodes (info.variant). */
 mlbm_status mlbm_plan_set_variant(mlbm_plan *plan, int32_t variant);
 
 /* ---- graphs ------------------------------------------------------------- */

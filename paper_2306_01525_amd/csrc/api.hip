@@ -116,6 +116,7 @@ void layout_cloud(const mlbm_cloud &c, const mlbm_params &p, int precision, Carv
     cp.K = K;
     cp.m = p.degree;
     cp.M = poly_count(p.degree);
+    cp.variant = start_variant(p.stencil_mode, K, n, false);
     cp.Lx = c.period_x;
     cp.Ly = c.period_y;
     cp.has_walls = p.wall_kind == 1;
@@ -400,6 +401,9 @@ void layout_plan(const mlbm_cloud *clouds, const mlbm_params *params, int32_t n_
     plan.batched = batchable(params, n_clouds);
     plan.batch_mode = params[0].stencil_mode;
     if (plan.batched) {
+        int longest = 0;
+        for (const auto &cp : L.cps) longest = std::max(longest, cp.K);
+        for (auto &cp : L.cps) cp.variant = start_variant(plan.batch_mode, longest, off, true);
         plan.descs = pl.take<Step32Args>(n_clouds);
         plan.tile2cloud = pl.take<int32_t>(tiles);
     }

@@ -69,14 +69,27 @@ inline int64_t head_nodes(int n) { return ((int64_t)n + 63) / 64 * 64; }
 constexpr int kTile = 256;      // nodes per workgroup in the step kernels
 constexpr int kHaloCap = 1024;  // largest halo a tile stages (10-bit positions)
 constexpr int kStepVariants = MLBM_STEP_VARIANTS; // FP32 step tuning variants
-// The variant of a plan that has not been tuned: two lanes a node, streamed
-// weights, two index words at a time. Against variant 0 (us a step): 50,176
-// nodes, K 30 18.4 -> 16.7; 65,536, K 20 14.6 -> 13.1; 160,000, K 25 24.7 ->
-// 23.9; 262,144, K 30 45.8 -> 45.0, K 45 92.8 -> 88.8; 518,400, K 20 75.3 ->
-// 71.7; 1,048,576, K 30 219.8 -> 215.7. Own-node stencils gain less (65,536, K 12
-// 9.0 -> 8.3; 262,144, K 30 42.9 -> 42.6) and lose at 1,048,576, K 12 (102.5 ->
-// 103.7).
-constexpr int kStartVariant = 9;
+// The variant of a plan that has not been tuned. Two lanes a node with streamed
+// weights, two index words at a time (9) gain nearly everywhere over one lane a
+// node with cached weights (0), us a step: 50,176 nodes, K 30 18.4 -> 16.7;
+// 65,536, K 20 14.6 -> 13.1; 160,000, K 25 24.7 -> 23.9; 262,144, K 30 45.8 ->
+// 45.0, K 45 92.8 -> 88.8; 518,400, K 20 75.3 -> 71.7; 1,048,576, K 30 219.8 ->
+// 215.7. With short stencils a lane has too little to do for halving it to pay,
+// and own-node stencils read no owners, whose latency the second lane hides. One
+// plan of own-node stencils, 0 against 9: K 6 5.6 : 5.1 at 52,900 nodes, 5.8 : 6.1
+// at 78,400, 22.3 : 23.2 at 524,176, 47.1 : 50.5 at 1,048,576; K 8 11.8 : 11.6 at
+// 160,000, 21.2 : 22.0 at 384,400, 69.7 : 74.6 at 1,048,576; K 12 14.6 : 14.5,
+// 28.0 : 28.4, 99.7 : 103.0; K 20 20.6 : 20.1, 44.8 : 47.3, 152.5 : 154.3 (77.0 :
+// 72.1 at 524,176); K 25 24.2 : 23.5, 60.1 : 65.1; K 30 27.8 : 27.2, 85.4 : 78.4.
+// Batches of them, by nodes in all: K 6 6.3 : 6.4 at 80,000, 48.8 : 52.8 at
+// 1,048,576; K 12 10.6 : 10.3, 97.0 : 100.6; K 18 13.7 : 13.0, 138.4 : 136.4.
+// Paper stencils of K 6: 59.1 : 59.0 at 1,048,576 in one plan, 61.0 : 61.9 in a
+// batch, 92.4 : 93.0 at 1,440,000 in one plan.
+inline int start_variant(int mode, int K, int64_t nodes, bool batched) {
+    const int64_t line = mode == MLBM_STENCIL_OWN ? (K < 8 ? 65536 : 200000) : 1000000;
+    const int longest = mode == MLBM_STENCIL_OWN ? (batched ? 12 : 25) : 7;
+    return K <= longest && nodes >= line ? 0 : 9;
+}
 constexpr int kBuildLanes = 4;   // clouds of one plan built concurrently
 constexpr int kStats = 5;        // build records per cloud (tile tables)
 
@@ -123,7 +136,7 @@ struct CloudPlan {
     unsigned lds_bytes = 0;       // dynamic LDS of the step launch (0: no tables)
     int nh_max = 0;               // largest |H_t| of a tile with tables
     int fallback_tiles = -1;      // tiles stepped with global gathers (-1: unknown)
-    int variant = kStartVariant;  // FP32 step tuning variant (mlbm_autotune)
+    int variant = 0;              // FP32 step tuning variant (mlbm_autotune)
     // transposed streaming (adjoint): per direction k = 1..8, CSR over the
     // source node m of (arriving node i, weight)
     int32_t *tr_ptr = nullptr;  // [8n+1] row offsets, row (k-1)*n + m

@@ -450,3 +450,27 @@ def test_autotune_keeps_the_variant_where_all_run_one_kernel():
     ms = plan.autotune(plan.init(ux, uy), plan.new_state(), 5)
     assert len(set(ms)) > 1 and ms[plan.info.variant] == min(ms)
     plan.close()
+
+
+@pytest.mark.parametrize("mode,K,nx,variant", [
+    (1, 6, 255, 9), (1, 6, 256, 0), (1, 8, 447, 9), (1, 8, 448, 0), (1, 25, 448, 0),
+    (1, 26, 448, 9), (0, 6, 999, 9), (0, 6, 1000, 0), (0, 8, 1000, 9)])
+def test_first_variant_follows_the_stencils_and_the_nodes(mode, K, nx, variant):
+    """Either side of each line of the variant that an untuned plan steps with."""
+    from paper_2306_01525_amd import Plan
+    c, _, _ = tgv_case(nx, K, 2, mode, jitter=0.1)
+    plan = Plan.build(c.x, c.y, c.period, _params(c.h, K, 2, mode, 0, 0.8))
+    assert plan.info.variant == variant
+    plan.close()
+
+
+def test_first_variant_of_batches_follows_the_longest_stencil_and_all_nodes():
+    from paper_2306_01525_amd import Plan
+    for mode, sizes, stencils, variant in (
+            (1, (300, 300), (8, 8), 9), (1, (320, 320), (8, 12), 0), (1, (320, 320), (8, 13), 9),
+            (1, (200, 200), (6, 6), 0), (0, (320, 320), (8, 12), 9)):
+        cs = [tgv_case(nx, K, 2, mode, jitter=0.1)[0] for nx, K in zip(sizes, stencils)]
+        plan = Plan.build_batch([(c.x, c.y, c.period, None) for c in cs],
+                                [_params(c.h, K, 2, mode, 0, 0.8) for c, K in zip(cs, stencils)])
+        assert plan.info.variant == variant, (mode, sizes, stencils)
+        plan.close()
