@@ -120,9 +120,12 @@ typedef struct {
     int64_t n_total;          /* sum of n over clouds                             */
     int32_t K, degree, stencil_mode, precision;   /* of cloud 0                    */
     size_t state_bytes;       /* bytes of one state array g (9 populations)        */
-    int64_t tile_nodes;       /* nodes per workgroup of the step kernel            */
-    int32_t step_lds_bytes;   /* LDS per workgroup of the FP32 step (0: the step
-                                 gathers from global memory only)                  */
+    int64_t tile_nodes;       /* nodes per tile of the gather tables; a workgroup
+                                 of the step takes one tile, or a part of one on
+                                 small clouds                                      */
+    int32_t step_lds_bytes;   /* LDS per workgroup of the FP32 step that takes a
+                                 whole tile (0: the step gathers from global
+                                 memory only)                                      */
     int32_t fallback_tiles;   /* tiles whose gather tables exceed the LDS caps and
                                  gather from global memory (-1: not known)         */
     int32_t variant;          /* FP32 step variant in use (mlbm_autotune)          */
@@ -144,8 +147,11 @@ mlbm_status mlbm_weights_query(const mlbm_cloud *clouds, const mlbm_params *para
  *  3. owner of every departure point x_i - e_k dx: its closest node, ties to
  *     the lower user index (paper mode), or node i (own mode) (Sec. 2.3);
  *  4. shape vectors w_L(p) = first K entries of Phi^{-1} phi_L(p) with Phi the
- *     (K+M)x(K+M) collocation matrix of r^3 plus monomials, solved in FP64 by
- *     Gaussian elimination with partial pivoting (Sec. 2.2-2.3).
+ *     (K+M)x(K+M) collocation matrix of r^3 plus monomials, solved in FP64:
+ *     in the null space of the polynomials for stencils of up to 32 nodes (31
+ *     at degree 4), by Gaussian elimination with partial pivoting for longer
+ *     ones and for systems that may be singular, which are those with a pivot
+ *     of at most 1e3 eps ||Phi|| in that elimination (Sec. 2.2-2.3).
  * plan_buf (device, plan_bytes) must stay allocated while the plan is used;
  * workspace (device, workspace_bytes) is free again when the stream reaches
  * the end of this call's work. *out receives a host object to release with

@@ -246,7 +246,7 @@ __device__ __forceinline__ int64_t unit_entry(int64_t u0, int c, int r, int k) {
 
 constexpr int kEllMaxLw = kMaxK + 4;
 constexpr int kFinRows = 16;    // nodes of a workgroup of k_tr_finish
-constexpr int kFinLen = 64;     // row entries ranked in LDS; longer rows take one lane
+constexpr int kFinLen = 64;     // row entries ranked in LDS; longer rows: sort_long_row
 constexpr int kFinPitch = 68;   // their stride (16-byte aligned, rows on other banks)
 
 // Sorts a row by column (no two equal), one wavefront, in place: blocks of 64
@@ -421,7 +421,7 @@ __global__ __launch_bounds__(256) void k_tr_finish(int n, int lw, const int32_t 
         }
         longest = ln;
     }
-    // rows longer than that (not met with K <= 48 on clouds of even spacing)
+    // rows longer than that: clouds of uneven spacing
     const int mine = s_row[wv][p16 + 1] - s_row[wv][p16];
     if (__ballot(mine > kFinLen) != 0) {
         for (int r = 0; r < NR; ++r) {
