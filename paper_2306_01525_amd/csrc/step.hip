@@ -619,6 +619,7 @@ template <class T> struct WideArgs {
     const int32_t *perm;
     int uoff;
     int nhcap;   // halo nodes that the launch's LDS holds
+    int direct;  // longest own-node stencil that gathers from memory (wide_direct)
 };
 
 // A value at a byte offset from a uniform base: a scalar address and a 32-bit
@@ -663,7 +664,7 @@ __device__ __forceinline__ void wide_finish(const WideArgs<double> &a, int p, do
 // so the states are bitwise the same. 6,400 nodes, K 25: FP64 32.4 -> 6.1 us
 // a step, FP32 8.3 -> 5.4; 1,600 nodes, K 12: FP32 5.6 -> 4.7, FP64 8.8 -> 4.8.
 // Of those, 2.7 us go by for a launch and one trip to memory, two more for the
-// halo's. Own-node stencils of few nodes gather from global memory instead:
+// halo's. Short own-node stencils gather from global memory instead (wide_direct):
 // 1,600 nodes, K 12, 4.7 -> 4.0 (FP32) and 4.8 -> 4.5 us (FP64); at K 20 both
 // ways cost the same, at K 30 the halo is cheaper (FP64 6.0 against 6.3), and
 // with two directions a lane it is at every K (22,500 nodes FP64 6.4 / 8.4).
@@ -692,9 +693,9 @@ __device__ __forceinline__ void wide_group(const WideArgs<T> &a, const T *__rest
     const T *wbase = a.W + (int64_t)row * n * EPR;
     const uint32_t woff = (uint32_t)(p * EPR + (lane % LPR) * D) * sizeof(T);
     auto weights = [&](int j) { return load_at<TD>(wbase + (int64_t)j * 8 * n, woff); };
-    // own-node stencils of up to 18 nodes: a lane's populations are fewer than
-    // its share of the halo, and need the stencil alone (no halo list, no LDS)
-    const bool direct = MODE == MLBM_STENCIL_OWN && D == 1 && K <= 3 * CH;
+    // short own-node stencils: a lane's populations are fewer than its share of the
+    // halo, and need the stencil alone (no halo list, no LDS)
+    const bool direct = MODE == MLBM_STENCIL_OWN && D == 1 && K <= a.direct;
     int q[U] = {};
     if (a.tdesc && !direct) {   // (every tile has room for kHaloCap entries: no wait for its count)
         const int32_t *hl = a.hlist + tile * (int64_t)a.hcap;
@@ -866,7 +867,7 @@ __global__ __launch_bounds__(256) void k_step_wide_batch(const Step32Args *__res
                                                          const int32_t *__restrict__ tile2cloud,
                                                          const float *__restrict__ g,
                                                          float *__restrict__ go, int64_t nblocks,
-                                                         int nhcap) {
+                                                         int nhcap, int direct) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int PER = kTile / (32 * D);
     const int64_t b = xcd_tile(nblocks);
@@ -892,6 +893,7 @@ __global__ __launch_bounds__(256) void k_step_wide_batch(const Step32Args *__res
     a.perm = s.perm;
     a.uoff = s.uoff;
     a.nhcap = nhcap;
+    a.direct = direct;
     wide_group<float, MODE, false, 0, false, D>(a, g + s.soff, go + s.soff, t - s.tile_begin,
                                                 (int)(b % PER) * 32 * D, smem);
 }
@@ -1241,6 +1243,15 @@ template <class T> int wide_halo(int nh_max) {
     return std::min(nh_max, (int)(65536 / sizeof(T) - 2) / 8);
 }
 
+// Longest own-node stencils that gather from memory with one direction a lane. The
+// more workgroups a CU has, the more of the halo's trip is covered. FP32, us a step,
+// gathers / halo: K 6 3.5 / 4.1 at 16,384 nodes, 4.4 / 5.1 at 31,684; K 12 4.2 / 4.4 at
+// 16,384, 5.0 / 4.9 at 18,225; K 15 4.3 / 4.4 at 8,100, 4.8 / 4.6 at 10,000, 6.0 / 5.3 at
+// 24,336. FP64 K 12 4.1 / 4.4 at 8,100, K 15 4.7 / 4.7, K 30 at 6,400 6.3 / 6.0.
+inline int wide_direct(int64_t n) {
+    return n <= 8192 ? 18 : n <= 16384 ? 12 : n <= 32768 ? 6 : 0;
+}
+
 template <class T> WideArgs<T> wide_args(const CloudPlan &cp, void *frec) {
     WideArgs<T> a{};
     a.n = cp.n;
@@ -1269,6 +1280,7 @@ template <class T> WideArgs<T> wide_args(const CloudPlan &cp, void *frec) {
     a.perm = cp.perm;
     a.uoff = (int)cp.off;
     a.nhcap = wide_halo<T>(cp.nh_max);
+    a.direct = wide_direct(cp.n);
     return a;
 }
 
@@ -1290,34 +1302,49 @@ void launch_wide(const CloudPlan &cp, int dirs, const void *gin, void *gout, voi
                        nb);
 }
 
-// Directions a lane takes in the small-cloud step, 0 for the tile kernels.
-// One (32 nodes a workgroup) as long as that gives every CU at most one
-// workgroup, in FP32 up to three; two (64 nodes) until the halos that each
-// workgroup stages for itself cost more than the tile kernels' unfilled chip. us
-// per step, of the FP32 tile kernels the fastest variant, paper stencils:
-//   FP32 K 30 at 8,464 / 17,956 / 24,649 / 40,000 / 48,841 nodes
-//     one 5.8 / 7.0 / 8.2 / 12.0 / 14.4, two 6.4 / 8.6 / 8.9 / 12.6 / 14.1, tile 8.7 / 10.3 / 13.2 / 16.0 / 16.6
-//   FP32 K 15 at 17,956 / 24,649 / 33,124 / 48,841
-//     one 5.8 / 6.4 / 8.0 / 10.0, two 6.5 / 6.6 / 7.8 / 8.3, tile 6.3 / 6.5 / 8.9 / 9.0
-//   FP64 K 30 at 8,100 / 12,100 / 44,100 / 102,400 / 144,400
-//     one 6.2 / 8.2 / 20.8 / 27.2 / 69.6, two 7.1 / 7.5 / 20.1 / 25.8 / 61.9, tile 38 / 38 / 41 / 29 / 58
-// Staging the halo does not shrink with K, so short stencils return to the tile
-// kernels earlier (two, tile): FP32 K 10 at 24,649 nodes 5.6, 5.6 and at 40,000
-// 6.7, 6.3; K 12 at 40,000 6.9, 7.0 and at 48,841 6.9, 6.7. FP64 K 6 at 65,536
-// nodes 10.2, 13.1 and at 78,400 (own stencils) 14.4, 13.2; own K 10 and 12 at
-// 90,000 18.9, 18.9 and 20.3, 21.5, at 102,400 21.9, 19.6 and 23.1, 22.1; K 48 at
-// 102,400 78.0, 76.3.
-// Batches of K below 18 return at 32,768 nodes, counted in whole tiles: K 12 at
-// 30,752 5.7, 6.2 and at 40,000 6.7, 6.4; K 15 at 30,752 6.4, 6.6 and at 45,000
-// 7.8, 6.9; K 18 at 45,000 8.4, 9.9.
-inline int wide_dirs(int64_t n, int K, int precision, bool batch = false) {
+// Directions a lane takes in the small-cloud step, 0 for the tile kernels: one (32
+// nodes a workgroup) while that leaves few workgroups a CU, then two (64), until the
+// halos that each workgroup stages for itself cost more than the tile kernels'
+// unfilled chip. The lines lie where a CU takes another workgroup: 24,576, 32,768
+// and 40,960 nodes are three to five of 32 nodes a CU, 81,920 and 98,304 five and
+// six of 64. Work grows by chunks of six slots, the halo not at all with K, so short
+// stencils return to the tile kernels earlier, and own-node stencils earlier still,
+// whose tile kernels have smaller halos. us a step, one / two / tile kernels (of the
+// FP32 ones the fastest variant), paper stencils:
+//   FP32    16,384             28,900             36,481              48,841
+//   K 6     4.3 / 4.2 / 4.9    5.4 / 4.8 / 5.0    6.7 / 5.5 / 5.1     7.4 / 5.6 / 5.2
+//   K 10    4.7 / 4.7 / 5.6    6.0 / 5.7 / 5.7    7.4 / 6.8 / 5.8     8.2 / 6.9 / 5.9
+//   K 12    4.7 / 4.8 / 5.8    6.1 / 5.8 / 6.0    7.4 / 6.8 / 6.1     8.6 / 7.1 / 7.0
+//   K 13    5.1 / 5.3 / 6.1    6.7 / 6.7 / 6.2    8.0 / 7.8 / 6.4     9.5 / 8.2 / 7.7
+//   K 15    5.1 / 5.3 / 6.3    6.7 / 6.7 / 6.8    8.0 / 7.9 / 7.1     10.0 / 8.4 / 9.1
+//   K 17    5.2 / 5.4 / 6.9    6.7 / 6.8 / 8.3    8.5 / 8.1 / 9.0     10.4 / 8.7 / 10.8
+//   K 25    6.2 / 7.5 / 7.9    8.5 / 9.0 / 12.9   10.7 / 11.1 / 13.7  13.5 / 13.1 / 14.8
+//   FP64    8,100              65,536             84,100              98,596
+//   K 6     4.3 / 4.3 / 7.7    13 / 10.4 / 13.0   17 / 14.7 / 14.8    19 / 16.7 / 15.4
+//   K 8     4.6 / 4.8 / 8.5    15 / 13.2 / 15.7   19 / 17.5 / 17.7    22 / 19.4 / 18.5
+//   K 12    4.8 / 5.0 / 10.4   17 / 15.1 / 20.6   21 / 19.5 / 24.6    23 / 21.5 / 25.7
+//   K 30    6.0 / 6.8 / 21     27 / 26 / 44       33 / 33 / 47        37 / 36 / 49
+//   K 48    8.3 / 9.9 / 47     40 / 40 / 65       57 / 59 / 72        76 / 75 / 75
+// Own-node stencils, FP32 at 28,900 nodes: K 6 4.4 / 4.7 / 4.7, K 13 5.9 / 6.1 / 5.8,
+// K 15 5.9 / 6.1 / 6.1; FP64, two / tile kernels: K 8 at 65,536 nodes 12.9 / 14.2 and at
+// 68,644 16.2 / 15.3, K 9 at 78,961 16.6 / 17.2 and at 84,100 18.7 / 17.4, K 12 at
+// 96,100 20.7 / 22.2 and at 98,596 23.0 / 22.2.
+inline int wide_dirs(int64_t n, int K, int mode, int precision) {
+    const bool own = mode == MLBM_STENCIL_OWN;
     if (precision == MLBM_FP64) {
         if (n <= 8192) return 1;
-        return n <= (K <= 8 ? 65536 : K <= 12 ? 90112 : K <= 44 ? 102400 : 94208) ? 2 : 0;
+        const int most = own ? (K <= 8 ? 65536 : K <= 9 ? 81920 : K <= 14 ? 98304 : 102400)
+                             : (K <= 7 ? 81920 : K <= 9 ? 98304 : 102400);
+        return n <= (K > 45 ? 98304 : most) ? 2 : 0;
+    }
+    if (K <= 6) {
+        if (n <= (own ? 32768 : 8192)) return 1;
+        return n <= 32768 && !own ? 2 : 0;
     }
     if (n <= 24576) return 1;
-    const int most = batch && K < 18 ? 32768 : K <= 12 ? 40960 : 49152;
-    return K > 10 && n <= most ? 2 : 0;
+    if (n <= 32768) return K >= 15 || (own && K >= 13) ? 1 : K == 11 || K == 12 ? 2 : 0;
+    if (n <= 40960) return K >= 22 ? 1 : K >= 17 ? 2 : 0;
+    return n <= 49152 && K >= 15 ? 2 : 0;
 }
 
 template <int MODE, int D>
@@ -1328,17 +1355,23 @@ void launch_wide_batch(const mlbm_plan &plan, const void *gin, void *gout, hipSt
     nh = wide_halo<float>(nh);
     hipLaunchKernelGGL((k_step_wide_batch<MODE, D>), dim3(xcd_grid(nb)), dim3(256),
                        wide_lds<float>(nh, 32 * D), s, plan.descs, plan.tile2cloud,
-                       (const float *)gin, (float *)gout, nb, nh);
+                       (const float *)gin, (float *)gout, nb, nh,
+                       wide_direct(plan.total_tiles * kTile));
 }
 
-// Small batches take the small-cloud kernel by their tiles and shortest stencils,
-// whatever the variant. K 20 to 30, us a step, best tile kernel and this: 2 clouds
+// Small batches take the small-cloud kernel by their nodes, counted in whole tiles, and
+// shortest stencils, whatever the variant, where their tile kernels fill the chip
+// differently (two / tile kernels, us a step): K 10 at 24,649 nodes 5.6 / 5.6; K 12 at
+// 30,752 5.7 / 6.2 and at 40,000 6.7 / 6.4; K 15 at 30,752 6.4 / 6.6 and at 45,000 7.8 /
+// 6.9; K 18 at 45,000 8.4 / 9.9. K 20 to 30, us a step, best tile kernel and this: 2 clouds
 // of 3,232 nodes together 9.5 and 5.1, 8 of 15,247 9.7 and 6.6, 4 of 38,054 16.7
 // and 12.9; 8 of 76,924 nodes stay with the tile kernels (18.5).
 int wide_dirs_batch(const mlbm_plan &plan) {
     int K = kMaxK;
     for (const CloudPlan &cp : plan.c) K = std::min(K, cp.K);
-    return wide_dirs(plan.total_tiles * kTile, K, MLBM_FP32_DEV, true);
+    const int64_t n = plan.total_tiles * kTile;
+    if (n <= 24576) return 1;
+    return K > 10 && n <= (K < 18 ? 32768 : 49152) ? 2 : 0;
 }
 
 template <int MODE>
@@ -1367,7 +1400,7 @@ hipError_t step_variant(const CloudPlan &cp, int precision, const void *gin, voi
                         void *frec, hipStream_t s) {
     const int n = cp.n;
     const int64_t nblocks = (n + kTile - 1) / kTile;
-    if (const int dirs = wide_dirs(n, cp.K, precision)) {
+    if (const int dirs = wide_dirs(n, cp.K, MODE, precision)) {
         if (precision == MLBM_FP64)
             launch_wide<double, MODE, FORCE, WALL, REC>(cp, dirs, gin, gout, frec, s);
         else
@@ -1652,7 +1685,7 @@ hipError_t launch_step_batch(const mlbm_plan &plan, const void *gin, void *gout,
 bool step_ignores_variant(const mlbm_plan &plan) {
     if (plan.batched) return wide_dirs_batch(plan) != 0;
     for (const CloudPlan &cp : plan.c)
-        if (!wide_dirs(cp.n, cp.K, plan.precision)) return false;
+        if (!wide_dirs(cp.n, cp.K, cp.prm.stencil_mode, plan.precision)) return false;
     return true;
 }
 

@@ -474,3 +474,25 @@ def test_first_variant_of_batches_follows_the_longest_stencil_and_all_nodes():
                                 [_params(c.h, K, 2, mode, 0, 0.8) for c, K in zip(cs, stencils)])
         assert plan.info.variant == variant, (mode, sizes, stencils)
         plan.close()
+
+
+# either side of the lines by kind of stencils: FP32 8,192, 24,576, 32,768, 40,960 and
+# 49,152 nodes, and 8,192 and 16,384 where short own-node stencils stop gathering from
+# memory; FP64 81,920, 98,304 and 102,400
+KIND_LINES = [
+    (n, K, m, mode, prec)
+    for K, m, mode, prec, lines in (
+        (6, 2, 0, 0, (8192, 32768)), (6, 2, 1, 0, (32768,)), (12, 2, 1, 0, (16384, 32768)),
+        (13, 2, 1, 0, (32768,)), (13, 2, 0, 0, (24576,)), (15, 2, 0, 0, (32768, 40960, 49152)),
+        (17, 2, 0, 0, (32768,)), (18, 3, 1, 0, (8192, 40960)), (25, 3, 0, 0, (40960,)),
+        (7, 2, 0, 1, (81920,)), (9, 2, 1, 1, (81920,)), (9, 2, 0, 1, (98304,)),
+        (14, 2, 1, 1, (98304,)), (15, 2, 1, 1, (102400,)), (46, 4, 0, 1, (98304,)))
+    for line in lines for n in (line, line + 256)]
+
+
+@pytest.mark.parametrize("n,K,m,mode,prec", KIND_LINES,
+                         ids=["%d-K%d-%d-f%d" % (n, k, o, 64 if p else 32)
+                              for n, k, _, o, p in KIND_LINES])
+def test_step_kernels_on_either_side_of_the_lines_by_kind(n, K, m, mode, prec):
+    """As the test of the edges of their sizes."""
+    test_step_kernels_at_the_edges_of_their_sizes(256, n // 256, K, m, mode, prec)
