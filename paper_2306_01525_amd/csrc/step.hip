@@ -1360,18 +1360,19 @@ void launch_wide_batch(const mlbm_plan &plan, const void *gin, void *gout, hipSt
 }
 
 // Small batches take the small-cloud kernel by their nodes, counted in whole tiles, and
-// shortest stencils, whatever the variant, where their tile kernels fill the chip
-// differently (two / tile kernels, us a step): K 10 at 24,649 nodes 5.6 / 5.6; K 12 at
-// 30,752 5.7 / 6.2 and at 40,000 6.7 / 6.4; K 15 at 30,752 6.4 / 6.6 and at 45,000 7.8 /
-// 6.9; K 18 at 45,000 8.4 / 9.9. K 20 to 30, us a step, best tile kernel and this: 2 clouds
-// of 3,232 nodes together 9.5 and 5.1, 8 of 15,247 9.7 and 6.6, 4 of 38,054 16.7
-// and 12.9; 8 of 76,924 nodes stay with the tile kernels (18.5).
+// shortest stencils, whatever the variant: one direction a lane up to 24,576 nodes,
+// then two. us a step, this / best tile kernel: paper stencils of K 6 at 30,720 nodes
+// (eight clouds) 4.8 / 5.1, K 10 5.7 / 5.9, K 12 5.8 / 6.3, K 15 6.6 / 6.8; K 12 at 36,864
+// (sixteen) 6.8 / 6.3 and K 15 7.9 / 6.8; K 20 there 9.5 / 8.8, but 9.8 / 11.2 at 40,960
+// (four) and 10.6 / 13.1 at 49,152. K 20 to 30, 2 clouds of 3,232 nodes together 5.1 /
+// 9.5, 8 of 15,247 6.6 / 9.7, 4 of 38,054 12.9 / 16.7; 8 of 76,924 nodes stay with the
+// tile kernels (18.5).
 int wide_dirs_batch(const mlbm_plan &plan) {
     int K = kMaxK;
     for (const CloudPlan &cp : plan.c) K = std::min(K, cp.K);
     const int64_t n = plan.total_tiles * kTile;
     if (n <= 24576) return 1;
-    return K > 10 && n <= (K < 18 ? 32768 : 49152) ? 2 : 0;
+    return n <= (K < 18 ? 32768 : 49152) ? 2 : 0;
 }
 
 template <int MODE>

@@ -496,3 +496,25 @@ KIND_LINES = [
 def test_step_kernels_on_either_side_of_the_lines_by_kind(n, K, m, mode, prec):
     """As the test of the edges of their sizes."""
     test_step_kernels_at_the_edges_of_their_sizes(256, n // 256, K, m, mode, prec)
+
+
+@pytest.mark.parametrize("nclouds,side", [(8, 55), (8, 64), (4, 91)])
+@pytest.mark.parametrize("mode", [0, 1])
+def test_batches_of_short_stencils_on_either_side_of_their_lines(mode, nclouds, side):
+    """24,576 nodes in whole tiles and a little more, 32,768 and a little more, K 6 and 8:
+    every cloud bitwise as its single-cloud plan."""
+    from paper_2306_01525_amd import Plan
+    clouds, params, u = [], [], []
+    for k in range(nclouds):
+        K = (6, 8)[k % 2]
+        c, ux, uy = tgv_case(side, K, 2, mode, seed=k, jitter=0.1)
+        clouds.append((c.x, c.y, c.period, None))
+        params.append(_params(c.h, K, 2, mode, 0, 0.8))
+        u.append((ux, uy))
+    bp = Plan.build_batch(clouds, params)
+    g = bp.step(bp.init(*(np.concatenate(a) for a in zip(*u))), bp.new_state(), 3)
+    for k in range(nclouds):
+        sp = Plan.build(*clouds[k][:3], params[k])
+        assert torch.equal(sp.step(sp.init(*u[k]), sp.new_state(), 3), bp.cloud_view(g, k)), k
+        sp.close()
+    bp.close()
